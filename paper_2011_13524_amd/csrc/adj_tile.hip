@@ -234,101 +234,88 @@ __global__ void __launch_bounds__(kAdjTileThreads)
 // and write one FP64 partial per (row, workgroup) at the end of the pass.
 constexpr int kAdjMaxRows = 64;  // gradient rows per pass (LDS slots)
 
-// X/Y rotation on register bit P: share of -Im<lambda|P|psi>, then
-// psi, lambda <- u psi, u lambda (u = exp(-i t P/2)); writes every slot of os, ol.
-// u = c I - i s' P has a real diagonal c and off-diagonals s' (Y: real, -s'
-// below the diagonal) or i s' (X), so each output takes two real products
-// per component instead of a complex 2x2 product. The gradient share is
-// summed in the amplitude precision over the thread's pairs (complex64:
-// FP32 products and 8-term sums, relative error <= 11 x 2^-24 of
-// sum |lambda_x||psi_y| <= |lambda||psi|; the caller sums in FP64).
-template <typename R, int NR, int P>
-__device__ __forceinline__ double grad_xy(const cx<R>* s, const cx<R>* l, cx<R>* os, cx<R>* ol, bool ypauli,
-                                          const cx<R>* __restrict__ u) {
-  if constexpr ((1 << P) >= NR) {  // no such register bit (never selected)
-    reg_copy<R, NR>(s, os);
-    reg_copy<R, NR>(l, ol);
-    return 0.0;
-  }
-  const R c = u[0].re, sn = ypauli ? u[1].re : u[1].im;
+// This thread's share of -Im<lambda|P|psi> for P = Y (YAX) or X on register bit
+// P: v[0] is psi, v[1] lambda. Summed in the amplitude precision over the
+// thread's pairs (complex64: FP32 products and 8-term sums, relative error <=
+// 11 x 2^-24 of sum |lambda_x||psi_y| <= |lambda||psi|; the caller sums in
+// FP64).
+template <typename R, int NR, int P, bool YAX>
+__device__ __forceinline__ R grad_xy(const cx<R> (&v)[2][NR]) {
   R acc = R(0);
+  if constexpr ((1 << P) < NR) {
 #pragma unroll
-  for (int g = 0; g < NR / 2; ++g) {
-    const int i = ins1<P>(g), j = i | (1 << P);
-    const cx<R> a0 = s[i], a1 = s[j], l0 = l[i], l1 = l[j];
-    const R im = ypauli ? fma(l1.re, a0.re, l1.im * a0.im) - fma(l0.re, a1.re, l0.im * a1.im)
-                        : fma(l0.re, a1.im, -(l0.im * a1.re)) + fma(l1.re, a0.im, -(l1.im * a0.re));
-    acc -= im;
-    if (ypauli) {  // u = [[c, s'], [-s', c]]
-      os[i] = {fma(c, a0.re, sn * a1.re), fma(c, a0.im, sn * a1.im)};
-      os[j] = {fma(c, a1.re, -(sn * a0.re)), fma(c, a1.im, -(sn * a0.im))};
-      ol[i] = {fma(c, l0.re, sn * l1.re), fma(c, l0.im, sn * l1.im)};
-      ol[j] = {fma(c, l1.re, -(sn * l0.re)), fma(c, l1.im, -(sn * l0.im))};
-    } else {  // u = [[c, i s'], [i s', c]]
-      os[i] = {fma(c, a0.re, -(sn * a1.im)), fma(c, a0.im, sn * a1.re)};
-      os[j] = {fma(c, a1.re, -(sn * a0.im)), fma(c, a1.im, sn * a0.re)};
-      ol[i] = {fma(c, l0.re, -(sn * l1.im)), fma(c, l0.im, sn * l1.re)};
-      ol[j] = {fma(c, l1.re, -(sn * l0.im)), fma(c, l1.im, sn * l0.re)};
-    }
-  }
-  return double(acc);
-}
-
-// Z rotation: the bit of the target is register bit P (P >= 0) or `fixed`;
-// share of -Im<lambda|Z|psi> (summed in the amplitude precision over the
-// thread's elements, as for grad_xy), then the diagonal u on both states.
-template <typename R, int NR, int P>
-__device__ __forceinline__ double grad_z(const cx<R>* s, const cx<R>* l, cx<R>* os, cx<R>* ol, int fixed,
-                                         const cx<R>* __restrict__ u) {
-  if constexpr (P >= 0 && (1 << P) >= NR) {  // no such register bit (never selected)
-    reg_copy<R, NR>(s, os);
-    reg_copy<R, NR>(l, ol);
-    return 0.0;
-  }
-  const cx<R> f0 = u[0], f1 = u[3];
-  R acc = R(0);
-#pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const int bit = P >= 0 ? (i >> P) & 1 : fixed;
-    const cx<R> a = s[i], c = l[i];
-    const R im = fma(c.re, a.im, -(c.im * a.re));
-    acc -= bit ? -im : im;
-    const cx<R> f = csel(bit != 0, f1, f0);
-    os[i] = f * a;
-    ol[i] = f * c;
-  }
-  return double(acc);
-}
-
-// Gradient op: share of the gradient from (s, l), the rotation applied into
-// (os, ol) (every element written).
-template <typename R, int NR>
-__device__ __forceinline__ double grad_apply(const cx<R>* s, const cx<R>* l, cx<R>* os, cx<R>* ol,
-                                             const RegOpDev& op, uint32_t tau, uint64_t base,
-                                             const cx<R>* __restrict__ u) {
-  double acc = 0.0;
-  if (op.kind == 5) {
-    const bool y = op.k == 2;
-    switch (op.p1) {
-      case 0: acc = grad_xy<R, NR, 0>(s, l, os, ol, y, u); break;
-      case 1: acc = grad_xy<R, NR, 1>(s, l, os, ol, y, u); break;
-      case 2: acc = grad_xy<R, NR, 2>(s, l, os, ol, y, u); break;
-      default: acc = grad_xy<R, NR, 3>(s, l, os, ol, y, u); break;
-    }
-  } else {
-    int fixed = 0, p = -1;
-    if (op.dsrc[0] == 0) p = op.dbit[0];
-    else if (op.dsrc[0] == 1) fixed = int((tau >> op.dbit[0]) & 1);
-    else fixed = int((base >> op.dbit[0]) & 1);
-    switch (p) {
-      case 0: acc = grad_z<R, NR, 0>(s, l, os, ol, 0, u); break;
-      case 1: acc = grad_z<R, NR, 1>(s, l, os, ol, 0, u); break;
-      case 2: acc = grad_z<R, NR, 2>(s, l, os, ol, 0, u); break;
-      case 3: acc = grad_z<R, NR, 3>(s, l, os, ol, 0, u); break;
-      default: acc = grad_z<R, NR, -1>(s, l, os, ol, fixed, u); break;
+    for (int g = 0; g < NR / 2; ++g) {
+      const int i = ins1<P>(g), j = i | (1 << P);
+      const cx<R> a0 = v[0][i], a1 = v[0][j], l0 = v[1][i], l1 = v[1][j];
+      if constexpr (YAX)
+        acc += fma(l0.re, a1.re, l0.im * a1.im) - fma(l1.re, a0.re, l1.im * a0.im);
+      else
+        acc += fma(l0.im, a1.re, -(l0.re * a1.im)) + fma(l1.im, a0.re, -(l1.re * a0.im));
     }
   }
   return acc;
+}
+
+// Adds the wavefront's sum of `acc` to the wavefront's slot of a gradient row.
+template <int TB>
+__device__ __forceinline__ void add_row(double acc, double* wslot, int row, uint32_t tau) {
+  const double w = wave_sum_to_last(acc);
+  if ((tau & 63) == 63) wslot[row * (1 << (TB - 6))] += w;
+}
+
+// The rotations of a kind-11 op with their gradients: per register bit, the
+// gradient's share from both states, then the uncompute exp(-i t P/2) of both.
+template <typename R, int RB, int TB, int P = 0>
+__device__ __forceinline__ void grad_layer(cx<R> (&v)[2][1 << RB], uint32_t rot, const RegOpDev& op,
+                                           const cx<R>* __restrict__ coef, double* wslot, uint32_t tau) {
+  if constexpr (P < RB) {
+    if (rot >> (16 + P) & 1u) {
+      double acc;
+      if (rot >> P & 1u) acc = double(grad_xy<R, 1 << RB, P, true>(v));
+      else acc = double(grad_xy<R, 1 << RB, P, false>(v));
+      add_row<TB>(acc, wslot, op.aux[P], tau);
+    }
+    const cx<R> c = coef[P];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if constexpr (RB == 3) rot8_bit<P>(v[s], c, rot);
+      else rot16_bit<P>(v[s], c, rot);
+    }
+    grad_layer<R, RB, TB, P + 1>(v, rot, op, coef, wslot, tau);
+  }
+}
+
+// Gradient rows of the Z rotations of a phase op: -Im<lambda|Z_q|psi> =
+// -sum_x (-1)^(x_q) w_x, w_x = Im(conj(lambda_x) psi_x). Diagonal factors of
+// modulus one leave w alone, so the rows of every rotation that waits in the
+// op share one evaluation of w: its sums with the sign of each register bit
+// (s[0..RB-1]) and without (s[RB]) come from one tree of additions, and a row
+// on a thread bit or a non-local qubit takes the plain sum with its sign.
+template <typename R, int RB, int TB>
+__device__ __forceinline__ void phase_rows(const cx<R> (&v)[2][1 << RB], const RegHeadDev& hd,
+                                           const PhaseEntDev* __restrict__ ents, double* wslot, uint32_t tau,
+                                           uint64_t base) {
+  constexpr int NR = 1 << RB;
+  R w[NR], s[RB + 1];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) w[r] = fma(v[1][r].im, v[0][r].re, -(v[1][r].re * v[0][r].im));
+#pragma unroll
+  for (int b = RB - 1; b >= 0; --b) {
+    R d = w[0] - w[1 << b];
+#pragma unroll
+    for (int r = 1; r < (1 << b); ++r) d += w[r] - w[r | (1 << b)];
+    s[b] = d;
+#pragma unroll
+    for (int r = 0; r < (1 << b); ++r) w[r] += w[r | (1 << b)];
+  }
+  s[RB] = w[0];
+  for (int e = hd.row_begin; e < hd.row_begin + hd.row_count; ++e) {
+    const PhaseEntDev E = ents[e];
+    R x = s[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) x = E.ra == b ? s[b] : x;
+    add_row<TB>(double(sgn_xor(x, ph_par(tau, E.tm, base, E.gm) << 31)), wslot, E.moff, tau);
+  }
 }
 
 // Re-map of one state's registers through LDS (write in the old layout with
@@ -336,8 +323,8 @@ __device__ __forceinline__ double grad_apply(const cx<R>* s, const cx<R>* l, cx<
 // close: a cross-wave re-map ends with a workgroup barrier (another state's
 // re-map writes next); otherwise that barrier is left to the next LDS write.
 template <typename R, int RB, int TB>
-__device__ __forceinline__ void adj_remap(cx<R> (&v)[1 << RB], const LdsMap<R, RB, TB>& mo,
-                                          const LdsMap<R, RB, TB>& mn, bool xw, bool close, char* smem) {
+__device__ __forceinline__ void adj_remap(cx<R> (&v)[1 << RB], const LdsMap<R, RB>& mo,
+                                          const LdsMap<R, RB>& mn, bool xw, bool close, char* smem) {
 #pragma unroll
   for (int i = 0; i < (1 << RB); ++i) mo.put(smem, i, v[i]);
   if (xw) __syncthreads();
@@ -348,45 +335,51 @@ __device__ __forceinline__ void adj_remap(cx<R> (&v)[1 << RB], const LdsMap<R, R
   else if (close) __syncthreads();
 }
 
-// A block applied through LDS to one state held in registers (v in, o out).
+// A block applied through LDS to one state held in registers.
 template <typename R, int RB, int TB, int KMAX, typename SW>
-__device__ __forceinline__ void adj_lds_op(const cx<R>* v, cx<R>* o, const LdsMap<R, RB, TB>& ms,
-                                           char* smem, const TileOpDev& op, const cx<R>* pool, int L,
-                                           uint64_t base, SW sw) {
+__device__ __forceinline__ void adj_lds_op(cx<R>* v, const LdsMap<R, RB>& ms, char* smem, const TileOpDev& op,
+                                           const cx<R>* pool, int L, uint64_t base, SW sw) {
 #pragma unroll
   for (int i = 0; i < (1 << RB); ++i) ms.put(smem, i, v[i]);
   __syncthreads();
   lds_op<R, KMAX>(reinterpret_cast<cx<R>*>(smem), op, pool, L, base, sw);
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < (1 << RB); ++i) o[i] = ms.get(smem, i);
+  for (int i = 0; i < (1 << RB); ++i) v[i] = ms.get(smem, i);
   __syncthreads();
 }
 
-// One op of the reverse sweep on both states: reads (s, l) and writes every
-// element of (os, ol); gradient ops add this wavefront's share to its slot.
+// An op of the reverse sweep on both states, in place; gradient ops add this
+// wavefront's share to its slot. Kind 11:
+template <typename R, int RB, int TB>
+__device__ __forceinline__ void adj_super(const RegHeadDev& hd, const RegOpDev& op, cx<R> (&v)[2][1 << RB],
+                                          uint32_t tau, uint64_t base, const PhaseEntDev* __restrict__ ents,
+                                          const cx<R>* __restrict__ pool, double* wslot) {
+  if (hd.flags & 8u) phase_rows<R, RB, TB>(v, hd, ents, wslot, tau, base);
+  phase_apply<R, RB, 2>(v, hd, op, ents, pool, tau, base);
+  grad_layer<R, RB, TB>(v, su(hd.rot), op, pool + hd.roff, wslot, tau);
+  const uint64_t xm = exchange_mask(hd.xch, op, tau, base);
+  exchange<R, RB>(v[0], su(hd.xch), xm);
+  exchange<R, RB>(v[1], su(hd.xch), xm);
+}
+
+// and the others.
 template <typename R, int RB, int KMAX, int TB>
-__device__ __forceinline__ void adj_step(const RegOpDev& opr, const cx<R>* s, const cx<R>* l, cx<R>* os,
-                                         cx<R>* ol, const RegSegDev& S, uint32_t tau, uint64_t base,
-                                         Swz<sizeof(R) == 4 ? 5 : 4> sw, char* smem,
-                                         const TileOpDev* __restrict__ lops, const cx<R>* __restrict__ pool,
-                                         int L, double* wslot) {
+__device__ __forceinline__ void adj_general(const RegOpDev& op, cx<R> (&v)[2][1 << RB], const RegSegDev& S,
+                                            const ThrMask<TB>& tm, uint32_t tau, uint64_t base, Swz<sizeof(R) == 4 ? 5 : 4> sw, char* smem,
+                                            const TileOpDev* __restrict__ lops, const cx<R>* __restrict__ pool, int L,
+                                            double* wslot) {
   constexpr int NR = 1 << RB;
-  const RegOpDev op = opr;  // (one burst of scalar loads)
-  if ((base & op.gcm) != op.gcv) {  // non-local controls: uniform per tile
-    reg_copy<R, NR>(s, os);
-    reg_copy<R, NR>(l, ol);
-    return;
-  }
   const cx<R>* m = pool + op.moff;
+  if ((base & op.gcm) != op.gcv) return;  // non-local controls: uniform per tile
   if (op.kind == 8) {
     // Pauli-string gradient: psi staged in LDS in this segment's layout; the
     // partner x ^ f of element i is at its address XOR pf_lds (the swizzle is
     // linear over XOR and the tile starts at LDS address 0)
-    const LdsMap<R, RB, TB> ms(S.get_reg, S.get_tcol, 0u, tau);
+    const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
     __syncthreads();  // (a preceding cross-wave re-map's reads are done)
 #pragma unroll
-    for (int i = 0; i < NR; ++i) ms.put(smem, i, s[i]);
+    for (int i = 0; i < NR; ++i) ms.put(smem, i, v[0][i]);
     __syncthreads();
     typedef R R2 __attribute__((ext_vector_type(2)));
     typedef __attribute__((address_space(3))) R2 lds_r2;
@@ -395,46 +388,40 @@ __device__ __forceinline__ void adj_step(const RegOpDev& opr, const cx<R>* s, co
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const R2 av = *reinterpret_cast<lds_r2*>(uintptr_t(reinterpret_cast<uintptr_t>(ms.at(smem, i)) ^ op.pf_lds));
-      const cx<R> c = l[i];
+      const cx<R> c = v[1][i];
       const double wr = double(c.re) * av.x + double(c.im) * av.y;
       const double wi = double(c.re) * av.y - double(c.im) * av.x;
       const bool neg = ((uint32_t(__popc(uint32_t(i) & op.pz_reg)) ^ tpar) & 1u) != 0;
       sr += neg ? -wr : wr;
       si += neg ? -wi : wi;
-      os[i] = s[i];
-      ol[i] = c;
     }
     __syncthreads();  // every read done before the LDS tile is written again
-    const double acc = wave_sum_to_last(neg_im_phase(sr, si, op.pph));
-    if ((tau & 63) == 63) wslot[op.aux * (1 << (TB - 6))] += acc;
-    return;
-  }
-  if (op.kind == 5 || op.kind == 6) {
-    const double acc = wave_sum_to_last(grad_apply<R, NR>(s, l, os, ol, op, tau, base, m));
-    if ((tau & 63) == 63) wslot[op.aux * (1 << (TB - 6))] += acc;
+    add_row<TB>(neg_im_phase(sr, si, op.pph), wslot, op.aux[0], tau);
     return;
   }
   if (op.kind == 3) {
-    const LdsMap<R, RB, TB> ms(S.get_reg, S.get_tcol, 0u, tau);
+    const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
     __syncthreads();  // (a preceding cross-wave re-map's reads are done)
-    adj_lds_op<R, RB, TB, KMAX>(s, os, ms, smem, lops[op.lop], pool, L, base, sw);
-    adj_lds_op<R, RB, TB, KMAX>(l, ol, ms, smem, lops[op.lop], pool, L, base, sw);
+    adj_lds_op<R, RB, TB, KMAX>(v[0], ms, smem, lops[op.lop], pool, L, base, sw);
+    adj_lds_op<R, RB, TB, KMAX>(v[1], ms, smem, lops[op.lop], pool, L, base, sw);
     return;
   }
   cx<R> gtab[4];
   int a = op.p1, bb = op.p2;
   if (op.kind == 2) diag_table<R>(op, m, tau, base, gtab, a, bb);
   const bool lane = (tau & op.ti_cm) == op.ti_cv;
-  reg_apply<R, NR, false>(s, os, op.key, m, gtab, op.ri_cm, op.ri_cv, lane, pool, op.lm);
-  reg_apply<R, NR, false>(l, ol, op.key, m, gtab, op.ri_cm, op.ri_cv, lane, pool, op.lm);
+  reg_apply<R, NR>(v[0], op.key, m, gtab, op.ri_cm, op.ri_cv, lane);
+  reg_apply<R, NR>(v[1], op.key, m, gtab, op.ri_cm, op.ri_cv, lane);
 }
 
+// KMAX 0: passes of kind-11 ops only.
 template <typename R, int RB, int KMAX, int TB>
 __global__ void __launch_bounds__(1 << TB)
     k_adj_reg(R* __restrict__ psi, R* __restrict__ lam, const TilePassDev* __restrict__ passes, int pass_idx,
-              const RegSegDev* __restrict__ segs, const RegOpDev* __restrict__ rops,
-              const TileOpDev* __restrict__ lops, const cx<R>* __restrict__ pool,
-              const int* __restrict__ prow, double* __restrict__ partial, uint64_t ntiles) {
+              const RegSegDev* __restrict__ segs, const RegHeadDev* __restrict__ heads,
+              const RegOpDev* __restrict__ rops, const TileOpDev* __restrict__ lops, const PhaseEntDev* __restrict__ ents,
+              const cx<R>* __restrict__ pool, const int* __restrict__ prow, double* __restrict__ partial,
+              uint64_t ntiles) {
   constexpr int NR = 1 << RB;
   constexpr int NW = 1 << (TB - 6);  // wavefronts per workgroup
   constexpr int SB = sizeof(R) == 4 ? 5 : 4;
@@ -446,6 +433,7 @@ __global__ void __launch_bounds__(1 << TB)
   const int L = P.L;
   double(*slot)[NW] = reinterpret_cast<double(*)[NW]>(smem + (size_t(1) << L) * sizeof(cx<R>));
   const uint32_t tau = threadIdx.x;
+  const ThrMask<TB> tm(tau);
   const int wave = int(tau >> 6);
   for (int i = int(tau); i < kAdjMaxRows * NW; i += blockDim.x) slot[i / NW][i % NW] = 0.0;
   // tiles of this workgroup: a contiguous range (fixed order of its partial sums)
@@ -474,7 +462,7 @@ __global__ void __launch_bounds__(1 << TB)
       if ((i >> k) & 1) x |= s.gcol_r[k];
     return x;
   };
-  cx<R> vs[NR], vl[NR], ws[NR], wl[NR];
+  cx<R> v[2][NR];  // psi, lambda
   for (uint64_t g = g0; g < gend; ++g) {
     if (g > g0) base = ((base | ~gmask) + 1) & gmask;
     // HBM -> registers in the first segment's layout
@@ -482,43 +470,55 @@ __global__ void __launch_bounds__(1 << TB)
 #pragma unroll
       for (int i = 0; i < NR; i += 2) {
         const uint64_t x = addr(*S0, th0, base, i);
-        AmpIO<R, 2>::load(psi, x, &vs[i]);
-        AmpIO<R, 2>::load(lam, x, &vl[i]);
+        AmpIO<R, 2>::load(psi, x, &v[0][i]);
+        AmpIO<R, 2>::load(lam, x, &v[1][i]);
       }
     } else {
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
         const uint64_t x = addr(*S0, th0, base, i);
-        AmpIO<R, 1>::load(psi, x, &vs[i]);
-        AmpIO<R, 1>::load(lam, x, &vl[i]);
+        AmpIO<R, 1>::load(psi, x, &v[0][i]);
+        AmpIO<R, 1>::load(lam, x, &v[1][i]);
       }
     }
     __syncthreads();  // the previous tile's last LDS reads are done (and the slots cleared)
     const RegSegDev* S = S0;
+    int oi = S0->op_begin;
+    RegHeadDev next = heads[oi];  // the next op's head, read one op ahead
     for (int sgi = 0; sgi < P.seg_count; ++sgi) {
       const RegSegDev* Sn = &segs[P.seg_begin + sgi];
       if (sgi > 0) {
         // re-map both states through LDS (folded X / CNOT ops applied to both)
         const bool xw = (Sn->xwave & 1) != 0;
-        if (Sn->xwave & 2) __syncthreads();
-        const LdsMap<R, RB, TB> mo(Sn->put_reg, Sn->put_tcol, Sn->put_tcst, tau);
-        const LdsMap<R, RB, TB> mn(Sn->get_reg, Sn->get_tcol, 0u, tau);
-        adj_remap<R, RB, TB>(vs, mo, mn, xw, true, smem);
-        adj_remap<R, RB, TB>(vl, mo, mn, xw, false, smem);
+        const bool xpre = (Sn->xwave & 2) != 0;
+        const uint32_t j = tm.map(Sn->tcst, Sn->tcol);
+        const LdsMap<R, RB> mo(Sn->put_reg, j & 0xffffu);
+        const LdsMap<R, RB> mn(Sn->get_reg, j >> 16);
+        if (xpre) __syncthreads();
+        adj_remap<R, RB, TB>(v[0], mo, mn, xw, true, smem);
+        adj_remap<R, RB, TB>(v[1], mo, mn, xw, false, smem);
       }
       S = Sn;
-      // ops alternate between the register arrays (vs, vl) and (ws, wl)
-      const int oc = S->op_count, ob = S->op_begin;
-      for (int o = 0; o < oc; o += 2) {
-        adj_step<R, RB, KMAX, TB>(rops[ob + o], vs, vl, ws, wl, *S, tau, base, sw, smem, lops, pool, L,
-                                  &slot[0][wave]);
-        if (o + 1 < oc) {
-          adj_step<R, RB, KMAX, TB>(rops[ob + o + 1], ws, wl, vs, vl, *S, tau, base, sw, smem, lops, pool, L,
-                                    &slot[0][wave]);
-        } else {
-          reg_copy<R, NR>(ws, vs);
-          reg_copy<R, NR>(wl, vl);
+      for (const int oe = S->op_begin + S->op_count; oi < oe;) {
+        const RegHeadDev hd = next;
+        const RegOpDev& op = rops[oi];
+        next = heads[++oi];
+        if constexpr (KMAX > 0) {
+          if ((hd.flags >> 24) != 11) {
+            adj_general<R, RB, KMAX, TB>(op, v, *S, tm, tau, base, sw, smem, lops, pool, L, &slot[0][wave]);
+            continue;
+          }
         }
+        adj_super<R, RB, TB>(hd, op, v, tau, base, ents, pool, &slot[0][wave]);
+      }
+    }
+    if (P.scale_off >= 0) {  // the sign left by the pass's rotations, when no phase op took it
+      const R f = pool[P.scale_off].re;
+      if (f != R(1)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int i = 0; i < NR; ++i) v[s][i] = {f * v[s][i].re, f * v[s][i].im};
       }
     }
     // registers -> HBM in the last segment's layout
@@ -526,15 +526,15 @@ __global__ void __launch_bounds__(1 << TB)
 #pragma unroll
       for (int i = 0; i < NR; i += 2) {
         const uint64_t x = addr(*SL, thL, base, i);
-        AmpIO<R, 2>::store(psi, x, &vs[i]);
-        AmpIO<R, 2>::store(lam, x, &vl[i]);
+        AmpIO<R, 2>::store(psi, x, &v[0][i]);
+        AmpIO<R, 2>::store(lam, x, &v[1][i]);
       }
     } else {
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
         const uint64_t x = addr(*SL, thL, base, i);
-        AmpIO<R, 1>::store(psi, x, &vs[i]);
-        AmpIO<R, 1>::store(lam, x, &vl[i]);
+        AmpIO<R, 1>::store(psi, x, &v[0][i]);
+        AmpIO<R, 1>::store(lam, x, &v[1][i]);
       }
     }
   }
@@ -574,10 +574,13 @@ __global__ void k_zero_doubles(double* __restrict__ p, uint64_t n) {
 namespace {
 
 struct BOp {
-  int kind;  // 0 dense, 1 diagonal, 2 gradient
+  int kind;  // 0 dense, 1 diagonal, 2 gradient, 3 gradient of a Pauli string;
+             // register-resident sweep: 4 rotation, 5 phase (TileOpDev)
   std::vector<int> targets, controls, ctrl_vals;
-  std::vector<cd> val;  // dense: matrix; diagonal: diagonal entries
-  int pauli = 0, row = -1;
+  std::vector<cd> val;  // dense: matrix; diagonal: diagonal entries; 4, 5: as TileOpDev
+  int pauli = 0, row = -1;  // (row >= 0: with a gradient)
+  int sub = 0;              // kind 5
+  bool xswap = false;       // kind 0: Pauli X on the target
   std::vector<int> paulis;  // kind 3: Pauli ids (1..3) of the string on targets
 };
 
@@ -603,12 +606,21 @@ template <typename R>
 int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state* psi, qsv_state* lam,
                            std::vector<int>& row_slot, std::vector<double>& rows) {
   const int n = c->n;
+  // complex64 states of at least one 2^12 tile (complex128: 2^11) run
+  // register-resident: 256 threads x 16 (8) amplitudes per state
+  const int Lc = sizeof(R) == 4 ? 12 : 11;
+  const int L = std::min(n, Lc);
+  const bool reg = n >= Lc;
+  const SegCfg cfg{sizeof(R) == 4 ? 4 : 3, 8, sizeof(R) == 4};
+  const int b = std::min(L, sizeof(R) == 4 ? 4 : 3);  // 128-byte contiguous runs
+  const double utol = sizeof(R) == 4 ? 1e-9 : 2e-15;
   // reversed, daggered op list with gradient terms
   std::vector<BOp> ops;
   row_slot.clear();
   std::vector<cd> m;
   for (int gi = int(c->gates.size()) - 1; gi >= 0; --gi) {
     const Gate& g = c->gates[gi];
+    const double t = g.kind == Gate::MATRIX ? 0.0 : (g.slot >= 0 ? theta[g.slot] : g.fixed_angle);
     if (g.kind == Gate::PAULI && g.slot >= 0) {
       // gradient term -Im<lambda|P|psi> of exp(i t P/2) (its own op), then the
       // uncompute exp(-i t P/2) as an ordinary gate below
@@ -620,17 +632,41 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
       row_slot.push_back(g.slot);
       ops.push_back(gr);
     }
-    if (g.kind == Gate::ROTATION && g.slot >= 0) {
-      // gradient term fused with the uncompute exp(-i t P/2)
+    if (g.kind == Gate::ROTATION && (reg || g.slot >= 0)) {
+      // gradient term (parametric) fused with the uncompute exp(-i t P/2)
       BOp gr;
-      gr.kind = 2;
       gr.pauli = g.pauli;
       gr.targets = g.targets;
-      gr.row = int(row_slot.size());
-      row_slot.push_back(g.slot);
+      if (g.slot >= 0) {
+        gr.row = int(row_slot.size());
+        row_slot.push_back(g.slot);
+      }
       gr.val.resize(4);
-      rotation_matrix(g.pauli, -theta[g.slot], gr.val.data());
+      if (!reg) {
+        gr.kind = 2;
+        rotation_matrix(g.pauli, -t, gr.val.data());
+      } else if (g.pauli == 3) {
+        gr.kind = 5;
+        gr.sub = PH_DIAG1;
+        rotation_matrix(3, -t, gr.val.data());
+        gr.val[1] = gr.val[3];
+        gr.val.resize(2);
+      } else {
+        gr.kind = 4;
+        rotation_shears(-t, gr.val.data());
+        gr.val.resize(2);
+      }
       ops.push_back(gr);
+      continue;
+    }
+    if (reg && g.kind == Gate::PAULI && g.targets.size() > 1 &&
+        std::all_of(g.paulis.begin(), g.paulis.end(), [](int p) { return p == 3; })) {
+      BOp z;
+      z.kind = 5;
+      z.sub = PH_ZSTR;
+      z.targets = g.targets;
+      z.val = {{std::cos(t / 2), -std::sin(t / 2)}};
+      ops.push_back(z);
       continue;
     }
     gate_matrix(g, theta, m);
@@ -655,71 +691,71 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
         op.controls.push_back(q);
         op.ctrl_vals.push_back(int(cv >> q & 1));
       }
+    const bool exch = tq.size() == 1 && m[0].re == 0 && m[0].im == 0 && m[1].re == 1 && m[1].im == 0 &&
+                      m[2].re == 1 && m[2].im == 0 && m[3].re == 0 && m[3].im == 0;
     if (diag) {
       if (tq.size() > 5) return fail(QSV_EINVAL, "diagonal gate too wide for the tiled sweep");
       for (int i = 0; i < D; ++i) op.val.push_back(m[size_t(i) * D + i]);
+      if (reg && tq.size() == 1 && cm == 0) {
+        op.kind = 5;
+        op.sub = PH_DIAG1;
+      } else if (reg && tq.size() == 1 && op.controls.size() == 1 && cv == cm && m[0].re == 1 && m[0].im == 0 &&
+                 m[3].re == -1 && m[3].im == 0) {
+        op.kind = 5;
+        op.sub = PH_CZ;
+        op.targets.push_back(op.controls[0]);
+        op.controls.clear();
+        op.ctrl_vals.clear();
+        op.val.clear();
+      }
+    } else if (reg && tq.size() == 1 && cm == 0 && !exch && is_unitary2(m.data(), utol)) {
+      // diagonal, rotation, diagonal
+      cd u[6];
+      unitary_to_rotation(m.data(), u);
+      op.kind = 5;
+      op.sub = PH_DIAG1;
+      op.val = {u[0], u[1]};
+      ops.push_back(op);
+      op.kind = 4;
+      op.pauli = 2;
+      op.val = {u[2], u[3]};
+      ops.push_back(op);
+      op.kind = 5;
+      op.val = {u[4], u[5]};
     } else {
       op.val = m;
+      op.xswap = exch;
     }
     ops.push_back(op);
   }
-  // passes (as in the forward planner): dense targets must be local. complex64
-  // states of at least one 2^12 tile run register-resident (256 threads x 16
-  // amplitudes per state), at most kAdjMaxRows gradient rows per pass
-  const int Lc = sizeof(R) == 4 ? 12 : 11;
-  const int L = std::min(n, Lc);
-  // complex64: 256 threads x 16 amplitudes per state; complex128: 256 x 8
-  const bool reg = n >= Lc;
-  SegCfg cfg{sizeof(R) == 4 ? 4 : 3, 8, sizeof(R) == 4, sizeof(R) == 4 && tile_mfma_default()};
-  cfg.layers = false;  // (k_adj_reg has no layer variants)
-  const int b = std::min(L, sizeof(R) == 4 ? 4 : 3);  // 128-byte contiguous runs
-  const uint64_t low = (uint64_t(1) << b) - 1;
+  // passes (as in the forward planner): dense targets must be local, at most
+  // kAdjMaxRows gradient rows per register-resident pass
   std::vector<std::vector<int>> pass_ops;
   std::vector<uint64_t> pass_local;
-  std::vector<int> rem(ops.size());
-  for (size_t i = 0; i < ops.size(); ++i) rem[i] = int(i);
-  while (!rem.empty()) {
-    uint64_t local = low, blocked = 0;
-    std::vector<int> take, deferred;
-    int nrow = 0;
-    for (int oi : rem) {
-      const BOp& o = ops[oi];
-      const uint64_t all = qmask_of(o.targets) | qmask_of(o.controls);
-      if (all & blocked) {
-        deferred.push_back(oi);
-        blocked |= all;
-        continue;
-      }
-      uint64_t dense = 0;
-      if (o.kind == 0 || (o.kind == 2 && o.pauli != 3)) dense = qmask_of(o.targets);
+  {
+    std::vector<PassOp> po(ops.size());
+    for (size_t i = 0; i < ops.size(); ++i) {
+      const BOp& o = ops[i];
+      const uint64_t t = qmask_of(o.targets), cq = qmask_of(o.controls);
+      uint64_t flip = t;  // qubits acted on non-diagonally
+      if (o.kind == 1 || o.kind == 5 || (o.kind == 2 && o.pauli == 3)) flip = 0;
       if (o.kind == 3)  // the X/Y qubits of the string: pairs x, x ^ f in one tile
         for (size_t j = 0; j < o.targets.size(); ++j)
-          if (o.paulis[j] != 3) dense |= uint64_t(1) << o.targets[j];
-      const uint64_t need = dense & ~local;
-      const bool grad = o.kind == 2 || o.kind == 3;
-      const bool rows_full = reg && grad && nrow >= kAdjMaxRows;
-      if (!rows_full && __builtin_popcountll(local | need) <= L) {
-        if (grad) ++nrow;
-        local |= need;
-        take.push_back(oi);
-      } else {
-        deferred.push_back(oi);
-        blocked |= all;
-      }
+          if (o.paulis[j] == 3) flip &= ~(uint64_t(1) << o.targets[j]);
+      po[i].nd = po[i].local = flip;
+      po[i].dg = (t & ~flip) | cq;
+      po[i].lazy = o.kind == 5;
+      po[i].rows = o.row >= 0 ? 1 : 0;
     }
-    if (take.empty()) return fail(QSV_EINVAL, "internal: tiled sweep made no progress");
-    for (int q = 0; q < n && __builtin_popcountll(local) < L; ++q) local |= uint64_t(1) << q;
-    pass_ops.push_back(take);
-    pass_local.push_back(local);
-    rem.swap(deferred);
+    const int rc = schedule_passes(po, n, L, b, reg ? kAdjMaxRows : 1 << 30, pass_ops, pass_local);
+    if (rc) return rc;
   }
   // device tables
   std::vector<TilePassDev> hp;
   std::vector<TileOpDev> ho;
-  std::vector<cx<R>> pool;
+  std::vector<cd> vals;  // host values of the ops
   std::vector<int> prow;  // gradient rows of each pass, in slot order
-  std::vector<RegSegDev> segs;
-  std::vector<RegOpDev> rops;
+  SegBuild sb;
   int kmax = 1;
   for (size_t pi = 0; pi < pass_ops.size(); ++pi) {
     const uint64_t local = pass_local[pi];
@@ -738,6 +774,7 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
     for (int q = 0; q < n; ++q)
       if (!(local >> q & 1)) d.gpos[d.ng++] = q;
     pass_runs(d);
+    d.scale_off = -1;
     d.op_begin = int(ho.size());
     d.op_count = int(pass_ops[pi].size());
     d.row_begin = int(prow.size());
@@ -780,8 +817,8 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
         t.ins[0] = o.row;
         t.ins[1] = d.row_count++;
         prow.push_back(o.row);
-        t.moff = int(pool.size());
-        for (const cd& v : o.val) pool.push_back({R(v.re), R(v.im)});
+        t.moff = int(vals.size());
+        vals.insert(vals.end(), o.val.begin(), o.val.end());
         const int q = o.targets[0];
         if (lpos[q] >= 0) t.lt[0] = lpos[q];
         else t.gq[0] = q;
@@ -789,9 +826,17 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
         continue;
       }
       t.kind = o.kind;
+      t.sub = o.sub;
       t.k = int(o.targets.size());
-      t.moff = int(pool.size());
-      for (const cd& v : o.val) pool.push_back({R(v.re), R(v.im)});
+      t.moff = int(vals.size());
+      vals.insert(vals.end(), o.val.begin(), o.val.end());
+      t.xswap = o.kind == 4 ? o.pauli : (o.xswap ? 1 : 0);
+      if (o.kind >= 4 && o.row >= 0) {
+        t.m = 1;
+        t.ins[0] = o.row;
+        t.ins[1] = d.row_count++;
+        prow.push_back(o.row);
+      }
       for (size_t j = 0; j < o.controls.size(); ++j) {
         const int q = o.controls[j];
         if (lpos[q] >= 0) {
@@ -825,19 +870,34 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
       ho.push_back(t);
     }
     if (reg) {
-      d.seg_begin = int(segs.size());
+      d.seg_begin = int(sb.segs.size());
       d.seg_count = 0;
-      const int rc = build_reg_segments(cfg, ho, d, segs, rops);
+      const int rc = build_reg_segments(cfg, ho, d, sb);
       if (rc) return rc;
     }
     hp.push_back(d);
   }
+  std::vector<cx<R>> pool;
+  {
+    std::vector<cd> pv;
+    if (reg) assemble_pool(sb, vals, pv);
+    else pv.swap(vals);
+    pool.resize(pv.size());
+    for (size_t i = 0; i < pv.size(); ++i) pool[i] = {R(pv[i].re), R(pv[i].im)};
+  }
+  const std::vector<RegSegDev>& segs = sb.segs;
+  const std::vector<RegOpDev>& rops = sb.rops;
+  const std::vector<PhaseEntDev>& ents = sb.ents;
+  const std::vector<RegHeadDev> heads = op_heads(sb);
   const int nrows = int(row_slot.size());
   const uint64_t tiles = dim(n - L);
   // register-resident passes: tile + gradient slots in LDS
   const size_t reg_lds = (size_t(1) << L) * sizeof(cx<R>) + size_t(kAdjMaxRows) * (256 / 64) * sizeof(double);
   constexpr int RBs = sizeof(R) == 4 ? 4 : 3;
-  const void* reg_fn = kmax <= 2   ? reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 2, 8>)
+  bool general = false;
+  for (const TilePassDev& p : hp) general |= p.general != 0;
+  const void* reg_fn = !general    ? reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 0, 8>)
+                       : kmax <= 2   ? reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 2, 8>)
                        : kmax <= 3 ? reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 3, 8>)
                                    : reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 5, 8>);
   // persistent grid: for the register sweep, eight rounds of the workgroups
@@ -858,13 +918,15 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
   }
   if (const char* e = std::getenv("QSV_ADJOINT_GRID")) gmax = uint64_t(std::max(1, std::atoi(e)));
   const int G = int(std::min<uint64_t>(tiles, gmax));
-  // one device allocation: passes | ops | pool | segs | rops | prow | partial[nrows x G] | rows[nrows]
+  // one device allocation: passes | ops | pool | segs | rops | ents | heads | prow | partial[nrows x G] | rows[nrows]
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t o_ops = al(hp.size() * sizeof(TilePassDev));
   const size_t o_pool = o_ops + al(std::max<size_t>(1, ho.size()) * sizeof(TileOpDev));
   const size_t o_segs = o_pool + al(std::max<size_t>(1, pool.size()) * sizeof(cx<R>));
   const size_t o_rops = o_segs + al(std::max<size_t>(1, segs.size()) * sizeof(RegSegDev));
-  const size_t o_prow = o_rops + al(std::max<size_t>(1, rops.size()) * sizeof(RegOpDev));
+  const size_t o_ents = o_rops + al(std::max<size_t>(1, rops.size()) * sizeof(RegOpDev));
+  const size_t o_heads = o_ents + al(std::max<size_t>(1, ents.size()) * sizeof(PhaseEntDev));
+  const size_t o_prow = o_heads + al(heads.size() * sizeof(RegHeadDev));
   const size_t o_part = o_prow + al(std::max<size_t>(1, prow.size()) * sizeof(int));
   const size_t o_rows = o_part + al(std::max<size_t>(1, size_t(nrows) * G) * sizeof(double));
   const size_t total = o_rows + al(std::max(1, nrows) * sizeof(double));
@@ -888,6 +950,10 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
                                        hipMemcpyHostToDevice, st) != hipSuccess) ||
       (!rops.empty() && hipMemcpyAsync(d + o_rops, rops.data(), rops.size() * sizeof(RegOpDev),
                                        hipMemcpyHostToDevice, st) != hipSuccess) ||
+      (!ents.empty() && hipMemcpyAsync(d + o_ents, ents.data(), ents.size() * sizeof(PhaseEntDev),
+                                       hipMemcpyHostToDevice, st) != hipSuccess) ||
+      hipMemcpyAsync(d + o_heads, heads.data(), heads.size() * sizeof(RegHeadDev), hipMemcpyHostToDevice, st) !=
+          hipSuccess ||
       (!prow.empty() && hipMemcpyAsync(d + o_prow, prow.data(), prow.size() * sizeof(int),
                                        hipMemcpyHostToDevice, st) != hipSuccess))
     return fin(fail(QSV_EHIP, "tiled sweep table upload failed"));
@@ -903,11 +969,14 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state*
                        static_cast<R*>(psi->ptr), static_cast<R*>(lam->ptr),                      \
                        reinterpret_cast<const TilePassDev*>(d), int(pi),                          \
                        reinterpret_cast<const RegSegDev*>(d + o_segs),                            \
+                       reinterpret_cast<const RegHeadDev*>(d + o_heads),                          \
                        reinterpret_cast<const RegOpDev*>(d + o_rops),                             \
                        reinterpret_cast<const TileOpDev*>(d + o_ops),                             \
+                       reinterpret_cast<const PhaseEntDev*>(d + o_ents),                          \
                        reinterpret_cast<const cx<R>*>(d + o_pool),                                \
                        reinterpret_cast<const int*>(d + o_prow), part, tiles)
-        if (kmax <= 2) QSV_ADJR_LAUNCH(2);
+        if (!hp[pi].general) QSV_ADJR_LAUNCH(0);
+        else if (kmax <= 2) QSV_ADJR_LAUNCH(2);
         else if (kmax <= 3) QSV_ADJR_LAUNCH(3);
         else QSV_ADJR_LAUNCH(5);
 #undef QSV_ADJR_LAUNCH

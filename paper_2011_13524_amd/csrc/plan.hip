@@ -346,503 +346,199 @@ static int build_plan(qsv_plan* p) {
     if (B.targets.size() > size_t(5)) return fail(QSV_EINVAL, "block wider than 5 qubits");
   }
 
-  // stage 3: passes
-  const int L = p->L, b = p->b;
-  p->passes.clear();
-  std::vector<int> rem(blocks.size());
-  for (size_t i = 0; i < blocks.size(); ++i) rem[i] = int(i);
-  const uint64_t low = (b >= 64) ? ~0ull : ((uint64_t(1) << b) - 1);
-  while (!rem.empty()) {
-    qsv_plan::Pass P;
-    uint64_t local = low;
-    // qubits of the blocks deferred so far, and of the non-diagonal ones: a
-    // block may run ahead of deferred blocks it commutes with -- those on
-    // other qubits, and for a diagonal block also diagonal ones on its qubits
-    uint64_t blocked = 0, blocked_dense = 0;
-    std::vector<int> deferred;
-    auto defer = [&](int bi) {
-      deferred.push_back(bi);
-      blocked |= bq[bi];
-      if (!blocks[bi].diagonal) blocked_dense |= bq[bi];
-    };
-    for (int bi : rem) {
-      const Block& B = blocks[bi];
-      const uint64_t all = bq[bi];
-      if (all & (B.diagonal ? blocked_dense : blocked)) {
-        defer(bi);
-        continue;
-      }
-      const uint64_t dense = B.diagonal ? 0 : qmask(B.targets);
-      const uint64_t need = dense & ~local;
-      if (__builtin_popcountll(local | need) <= L) {
-        local |= need;
-        P.blocks.push_back(bi);
-      } else {
-        defer(bi);
-      }
-    }
-    if (P.blocks.empty()) return fail(QSV_EINVAL, "planner made no progress (tile too small)");
-    // fill the local set up to L qubits with the lowest unused qubits
-    for (int q = 0; q < n && __builtin_popcountll(local) < L; ++q) local |= uint64_t(1) << q;
-    P.local = mask_list(local);
-    p->passes.push_back(P);
-    rem.swap(deferred);
-  }
   return QSV_OK;
 }
 
-// Split a pass's ops into register-resident segments.
-//
-// Scheduling: ops that commute may run in any order. Two ops commute when
-// every local qubit they share is acted on diagonally by both (a control, or a
-// diagonal target); otherwise the later op depends on the earlier one. A
-// segment fixes reg_bits register bits and takes, by list scheduling over
-// this dependency order, every ready op whose register needs (the targets of
-// one- and two-qubit dense ops; diagonal and LDS ops need none) still fit;
-// when no ready op fits, the next segment starts.
-//
-// Folding: an X gate, or an X with one local control, permutes the tile's
-// local indices by an affine map over GF(2) (x_t ^= x_c, or ^= 1). Such an op
-// moves no data: it is folded into the next re-map through LDS, whose write
-// addresses go through the composed map. Ops that depend on a folded op wait
-// for the next segment; ops that commute with it are unaffected.
-//
-// Layouts: the first segment is the layout the tile is read in and the last
-// the one it is written in, so both put the low local bits that form
-// contiguous 128-byte runs on lanes 0..2 (and, for complex64, local bit 0 in
-// registers: amplitude pairs are 16-byte vectors). A segment's wave bits
-// (thread-index bits above the 64 lanes) are chosen so that consecutive
-// segments share them where possible: a re-map between two such layouts
-// moves data only within each wavefront and needs no workgroup barrier.
-void pass_runs(TilePassDev& d) {
-  d.nrun = 0;
-  for (int j = 0; j < d.ng; ++j) {
-    if (j > 0 && d.gpos[j] == d.gpos[j - 1] + 1) {
-      ++d.rlen[d.nrun - 1];
+// ------------------------------------------------------------------ elementary ops
+
+// The plan's blocks as elementary ops. For register-resident passes a
+// one-qubit unitary becomes a rotation between diagonals, and diagonal blocks
+// fall apart into phases that the segment builder merges again wherever they
+// are due together; every other block stays one op.
+static void build_lops(qsv_plan* p) {
+  const qsv_circuit& C = p->circ_copy;
+  p->lops.clear();
+  p->nvals = 0;
+  auto add = [&](Lop l, int nv) {
+    l.voff = p->nvals;
+    p->nvals += nv;
+    p->lops.push_back(std::move(l));
+  };
+  // rounding-level tolerance: a matrix further from unitary keeps the general product
+  const double tol = p->dtype == QSV_C64 ? 1e-9 : 2e-15;
+  for (size_t bi = 0; bi < p->blocks.size(); ++bi) {
+    const Block& B = p->blocks[bi];
+    Lop whole;
+    whole.kind = B.diagonal ? 1 : 0;
+    whole.xswap = B.xswap;
+    whole.targets = B.targets;
+    whole.controls = B.controls;
+    whole.ctrl_vals = B.ctrl_vals;
+    whole.block = int(bi);
+    const int nv = B.diagonal ? 1 << B.targets.size() : 1 << (2 * B.targets.size());
+    if (p->reg_bits == 0) {
+      add(whole, nv);
       continue;
     }
-    d.rsrc[d.nrun] = j;
-    d.rdst[d.nrun] = d.gpos[j];
-    d.rlen[d.nrun] = 1;
-    ++d.nrun;
-  }
-}
-
-bool tile_mfma_default() {
-  const char* e = std::getenv("QSV_TILE_MFMA");
-  return !(e && e[0] == '0');
-}
-
-int build_reg_segments(const SegCfg& cfg, const std::vector<TileOpDev>& ho, TilePassDev& d,
-                       std::vector<RegSegDev>& out_segs, std::vector<RegOpDev>& out_rops) {
-  const int RB = cfg.reg_bits, TB = cfg.thread_bits, L = d.L;
-  const int NW = TB - 6;
-  const bool c64 = cfg.c64;
-  const uint32_t full = (1u << L) - 1;
-  const uint32_t io_reg = c64 ? 1u : 0u;
-  const uint32_t io_lane = c64 ? 0xEu : 0x7u;
-  const int nops = d.op_count;
-
-  // dependency order
-  std::vector<uint32_t> need(nops), nd(nops), dg(nops);
-  for (int i = 0; i < nops; ++i) {
-    const TileOpDev& o = ho[d.op_begin + i];
-    uint32_t tg = 0;
-    if (o.kind != 2)
-      for (int j = 0; j < o.k && j < 5; ++j)
-        if (o.lt[j] >= 0) tg |= 1u << o.lt[j];
-    if (o.kind == 2) {  // gradient rotation of the reverse sweep: k = Pauli id, target lt[0]/gq[0]
-      const uint32_t t1 = o.lt[0] >= 0 ? (1u << o.lt[0]) : 0u;
-      nd[i] = o.k == 3 ? 0u : t1;
-      dg[i] = o.k == 3 ? t1 : 0u;
-      need[i] = o.k == 3 ? 0u : t1;
-    } else if (o.kind == 3) {  // Pauli-string gradient: X/Y qubits non-diagonal, Z diagonal
-      nd[i] = o.off[0];
-      dg[i] = o.off[1] & ~o.off[0];
-      need[i] = 0;
-    } else if (o.kind == 0) {
-      nd[i] = tg;
-      dg[i] = o.lcm;
-      need[i] = o.k <= 2 ? tg : 0u;
-    } else {
-      nd[i] = 0;
-      dg[i] = tg | o.lcm;
-      need[i] = 0;
-    }
-  }
-  std::vector<std::vector<int>> preds(nops);
-  for (int j = 0; j < nops; ++j)
-    for (int i = 0; i < j; ++i)
-      if ((nd[i] & (nd[j] | dg[j])) | (dg[i] & nd[j])) preds[j].push_back(i);
-  std::vector<char> foldable(nops, 0);
-  for (int i = 0; i < nops; ++i) {
-    const TileOpDev& o = ho[d.op_begin + i];
-    foldable[i] = o.kind == 0 && o.k == 1 && o.xswap && o.gcm == 0 && __builtin_popcount(o.lcm) <= 1;
-  }
-
-  // list scheduling into segments; state 1: executed or folded into an
-  // earlier re-map, 2: folded into the re-map after the current segment
-  struct Seg {
-    uint32_t regs = 0;  // register positions the ops need (+ IO constraints)
-    bool io = false;
-    std::vector<int> ops;
-    std::vector<int> fold;  // ops folded into the re-map after this segment
-    uint32_t w = 0;         // wave positions
-    bool xwave = false;
-  };
-  std::vector<Seg> segs;
-  std::vector<char> st(nops, 0);
-  int left = nops;
-  do {
-    Seg s;
-    const bool first = segs.empty();
-    s.io = first;
-    s.regs = first ? io_reg : 0u;
-    const uint32_t forbid = first ? io_lane : 0u;
-    for (bool progress = true; progress;) {
-      progress = false;
-      for (int i = 0; i < nops; ++i) {
-        if (st[i]) continue;
-        bool exec_ready = true, fold_ready = true;
-        for (int q : preds[i]) {
-          exec_ready = exec_ready && st[q] == 1;
-          fold_ready = fold_ready && st[q] != 0;
+    if (B.diagonal) {
+      std::vector<std::pair<int, std::vector<int>>> one;               // qubit -> its diagonal gates
+      std::vector<std::pair<std::vector<int>, int>> cz;                // pair -> how often
+      std::vector<std::pair<std::vector<int>, std::vector<int>>> str;  // qubits -> Z strings
+      bool ok = true;
+      for (int gi : B.gates) {
+        const Gate& g = C.gates[size_t(gi)];
+        if (g.kind == Gate::PAULI && g.targets.size() > 1) {
+          std::vector<int> t = g.targets;
+          std::sort(t.begin(), t.end());
+          auto it = std::find_if(str.begin(), str.end(), [&](const auto& x) { return x.first == t; });
+          if (it == str.end()) str.push_back({t, {gi}});
+          else it->second.push_back(gi);
+          continue;
         }
-        if (foldable[i] && fold_ready) {
-          st[i] = 2;
-          s.fold.push_back(i);
+        const GateInfo I = analyse(g);
+        if (I.targets.size() == 1 && I.controls.empty()) {
+          auto it = std::find_if(one.begin(), one.end(), [&](const auto& x) { return x.first == I.targets[0]; });
+          if (it == one.end()) one.push_back({I.targets[0], {gi}});
+          else it->second.push_back(gi);
+        } else if (I.targets.size() == 1 && I.controls.size() == 1 && I.ctrl_vals[0] == 1 && I.mat[0].re == 1 &&
+                   I.mat[0].im == 0 && I.mat[3].re == -1 && I.mat[3].im == 0) {
+          std::vector<int> t = {std::min(I.targets[0], I.controls[0]), std::max(I.targets[0], I.controls[0])};
+          auto it = std::find_if(cz.begin(), cz.end(), [&](const auto& x) { return x.first == t; });
+          if (it == cz.end()) cz.push_back({t, 1});
+          else ++it->second;
         } else {
-          const uint32_t u = s.regs | need[i];
-          if (!exec_ready || (need[i] & forbid) || __builtin_popcount(u) > RB) continue;
-          s.regs = u;
-          s.ops.push_back(i);
-          st[i] = 1;
-        }
-        --left;
-        progress = true;
-      }
-    }
-    if (s.ops.empty() && s.fold.empty() && !first) return fail(QSV_EINVAL, "internal: segment scheduling stalled");
-    for (int i : s.fold) st[i] = 1;
-    segs.push_back(std::move(s));
-  } while (left > 0);
-  {
-    Seg& last = segs.back();
-    // ops folded after the last segment need a re-map; when it would be the
-    // only reason for one, run them as register exchanges instead
-    if (!last.fold.empty() && (last.io || ((last.regs & io_lane) == 0 &&
-                                           __builtin_popcount(last.regs | io_reg) <= RB))) {
-      uint32_t u = last.regs | io_reg;
-      for (int i : last.fold) u |= need[i] | (1u << ho[d.op_begin + i].lt[0]);
-      if ((u & io_lane) == 0 && __builtin_popcount(u) <= RB) {
-        last.regs = u;
-        for (int i : last.fold) last.ops.push_back(i);
-        last.fold.clear();
-      }
-    }
-    if (!last.io || !last.fold.empty()) {
-      if (last.fold.empty() && (last.regs & io_lane) == 0 && __builtin_popcount(last.regs | io_reg) <= RB) {
-        last.regs |= io_reg;
-        last.io = true;
-      } else {
-        Seg s;
-        s.regs = io_reg;
-        s.io = true;
-        segs.push_back(std::move(s));
-      }
-    }
-  }
-  // affine map of each re-map (into segment k: the folds of segment k-1):
-  // image of local basis vector p, and the constant
-  const int K = int(segs.size());
-  std::vector<std::vector<uint32_t>> mcol(K, std::vector<uint32_t>(L));
-  std::vector<uint32_t> mcst(K, 0), ftarget(K, 0);
-  for (int k = 0; k < K; ++k) {
-    for (int q = 0; q < L; ++q) mcol[k][q] = 1u << q;
-    if (k == 0) continue;
-    for (int i : segs[k - 1].fold) {
-      const TileOpDev& o = ho[d.op_begin + i];
-      const uint32_t t = 1u << o.lt[0];
-      ftarget[k] |= t;
-      // x_t ^= x_c (control value 1) or x_t ^= x_c ^ 1 (value 0); no control: x_t ^= 1
-      auto apply = [&](uint32_t y) -> uint32_t {
-        if (o.lcm == 0) return y;
-        return (y & o.lcm) ? (y ^ t) : y;
-      };
-      for (int q = 0; q < L; ++q) mcol[k][q] = apply(mcol[k][q]);
-      mcst[k] = apply(mcst[k]);
-      if (o.lcm == 0 || (o.lcv & o.lcm) == 0) mcst[k] ^= t;
-    }
-  }
-
-  // wave bits: maximal runs of segments sharing NW available positions;
-  // prefer positions off the low lanes (longer contiguous HBM runs)
-  // (a run continues into segment k only if no op folded into the re-map
-  // before k targets a wave bit: that re-map would move data across waves)
-  std::vector<uint32_t> avail(K);
-  for (int k = 0; k < K; ++k) avail[k] = full & ~segs[k].regs & ~(segs[k].io ? (io_lane | io_reg) : 0u);
-  for (int k = 0; k < K;) {
-    uint32_t I = avail[k];
-    int m = k + 1;
-    while (m < K && __builtin_popcount(I & avail[m] & ~ftarget[m]) >= NW) {
-      I &= avail[m] & ~ftarget[m];
-      ++m;
-    }
-    uint32_t w = 0;
-    for (int pass = 0; pass < 2 && __builtin_popcount(w) < NW; ++pass)
-      for (int pos = L - 1; pos >= 0 && __builtin_popcount(w) < NW; --pos) {
-        const bool low = pos >= 1 && pos <= 6;
-        if ((I >> pos & 1) && (pass == 1 || !low)) w |= 1u << pos;
-      }
-    if (__builtin_popcount(w) != NW) return fail(QSV_EINVAL, "internal: no wave bits");
-    for (int t = k; t < m; ++t) {
-      segs[t].w = w;
-      segs[t].xwave = (t == k && k > 0);
-    }
-    k = m;
-  }
-  // A cross-wave re-map writes with the folded map, which may move elements
-  // into other wavefronts' regions of the old layout; after a wave-local re-map
-  // (no trailing barrier) those wavefronts may still be reading there, so such
-  // a re-map also waits for the workgroup before writing.
-  // A cross-wave re-map does not close with a barrier: waves go on with the
-  // segment's register ops, and the barrier moves to the next LDS write (the
-  // next re-map's, or an op through LDS, which always waits first). Until then
-  // other waves may still read any region, so the next re-map waits first.
-  std::vector<char> pre(K, 0);
-  for (int k = 2; k < K; ++k) {
-    if (segs[k].xwave && !segs[k - 1].xwave && (ftarget[k] & segs[k - 1].w)) pre[k] = 1;
-    if (segs[k - 1].xwave) pre[k] = 1;
-  }
-
-  for (Seg& s : segs) {
-    RegSegDev sd{};
-    uint32_t regs = s.regs;
-    const uint32_t keep_off = s.w | (s.io ? io_lane : 0u);
-    for (int pos = L - 1; pos >= 0 && __builtin_popcount(regs) < RB; --pos)
-      if (!(keep_off >> pos & 1)) regs |= 1u << pos;
-    if (__builtin_popcount(regs) != RB) return fail(QSV_EINVAL, "internal: bad segment layout");
-    int nr = 0, nt = 0;
-    int regidx[32], thridx[32];
-    for (int pos = 0; pos < L; ++pos) {
-      regidx[pos] = -1;
-      thridx[pos] = -1;
-    }
-    for (int pos = 0; pos < L; ++pos)
-      if (regs >> pos & 1) {
-        regidx[pos] = nr;
-        sd.reg[nr++] = pos;
-      }
-    // lanes: the IO lane positions first, then the remaining ascending; then waves
-    const uint32_t lanes = full & ~regs & ~s.w;
-    if (s.io)
-      for (int pos = 0; pos < L; ++pos)
-        if (io_lane >> pos & 1) {
-          thridx[pos] = nt;
-          sd.thr[nt++] = pos;
-        }
-    for (int pos = 0; pos < L; ++pos)
-      if ((lanes >> pos & 1) && thridx[pos] < 0) {
-        thridx[pos] = nt;
-        sd.thr[nt++] = pos;
-      }
-    if (nt != 6) return fail(QSV_EINVAL, "internal: bad lane layout");
-    for (int pos = 0; pos < L; ++pos)
-      if (s.w >> pos & 1) {
-        thridx[pos] = nt;
-        sd.thr[nt++] = pos;
-      }
-    if (nr != RB || nt != TB) return fail(QSV_EINVAL, "internal: bad segment layout");
-    sd.xwave = (s.xwave ? 1 : 0) | (pre[&s - segs.data()] ? 2 : 0);
-    {
-      const int k = int(&s - segs.data());
-      for (int q = 0; q < L; ++q) sd.mcol[q] = mcol[k][q];
-      sd.mcst = mcst[k];
-    }
-    sd.op_begin = int(out_rops.size());
-    // runs of uncontrolled dense one-qubit ops on distinct register bits 0..3
-    // become one layer op (one dispatch: the op loop's scalar work per op --
-    // descriptor loads, control checks, the branch tree over the variants --
-    // costs as much as a one-qubit op's arithmetic)
-    const char* lay_env = std::getenv("QSV_TILE_LAYERS");  // "0": one dispatch per op (comparison)
-    const bool use_layers = cfg.layers && !(lay_env && lay_env[0] == '0');
-    int lay_mask = 0;
-    int lay_moff[4] = {0, 0, 0, 0};
-    RegOpDev lay_first{};
-    auto flush_layer = [&]() {
-      if (lay_mask == 0) return;
-      if (__builtin_popcount(lay_mask) == 1) {
-        out_rops.push_back(lay_first);
-      } else {
-        RegOpDev lr{};
-        lr.kind = 10;
-        lr.moff = lay_first.moff;
-        lr.lop = lay_first.lop;
-        for (int p = 0; p < 4; ++p) lr.lm[p] = (lay_mask >> p & 1) ? lay_moff[p] : 0;
-        lr.key = reg_key(10, lay_mask, cfg.c64 && cfg.mfma ? 1 : 0, false);
-        out_rops.push_back(lr);
-      }
-      lay_mask = 0;
-    };
-    for (int li : s.ops) {
-      const int oi = d.op_begin + li;
-      const TileOpDev& o = ho[oi];
-      RegOpDev r{};
-      r.lop = oi;
-      r.moff = o.moff;
-      r.k = o.k;
-      r.gcm = o.gcm;
-      r.gcv = o.gcv;
-      for (int pos = 0; pos < L; ++pos) {
-        if (!(o.lcm >> pos & 1)) continue;
-        const uint32_t val = (o.lcv >> pos) & 1;
-        if (regidx[pos] >= 0) {
-          r.ri_cm |= 1u << regidx[pos];
-          r.ri_cv |= val << regidx[pos];
-        } else {
-          r.ti_cm |= 1u << thridx[pos];
-          r.ti_cv |= val << thridx[pos];
+          ok = false;
         }
       }
-      r.aux = (o.kind == 2 || o.kind == 3) ? o.ins[1] : 0;  // gradient: slot of the row in the pass
-      if (o.kind == 3) {
-        // Pauli-string gradient through LDS in this segment's layout
-        r.kind = 8;
-        const int SBp = c64 ? 5 : 4;
-        const uint32_t msk = (1u << SBp) - 1, fl = o.off[0];
-        r.pf_lds = (fl ^ ((fl >> SBp) & msk) ^ ((fl >> (2 * SBp)) & msk)) * (c64 ? 8u : 16u);
-        r.pz_reg = r.pz_thr = 0;
-        for (int pos = 0; pos < L; ++pos) {
-          if (!(o.off[1] >> pos & 1)) continue;
-          if (regidx[pos] >= 0) r.pz_reg |= 1u << regidx[pos];
-          else r.pz_thr |= 1u << thridx[pos];
+      if (ok) {
+        for (auto& x : one) {
+          Lop l;
+          l.kind = 5;
+          l.sub = PH_DIAG1;
+          l.targets = {x.first};
+          l.block = int(bi);
+          l.lv = LV_DIAG1;
+          l.gates = x.second;
+          add(l, 2);
         }
-        r.pph = int(o.off[2]);
-        r.pz_glob = uint64_t(o.off[3]) | (uint64_t(o.off[4]) << 32);
-      } else if (o.kind == 2 && o.k != 3) {
-        r.kind = 5;
-        r.p1 = regidx[o.lt[0]];
-        if (r.p1 < 0) return fail(QSV_EINVAL, "internal: gradient target not in registers");
-      } else if (o.kind == 2) {
-        r.kind = 6;
-        if (o.lt[0] >= 0) {
-          if (regidx[o.lt[0]] >= 0) {
-            r.dsrc[0] = 0;
-            r.dbit[0] = regidx[o.lt[0]];
-          } else {
-            r.dsrc[0] = 1;
-            r.dbit[0] = thridx[o.lt[0]];
-          }
-        } else {
-          r.dsrc[0] = 2;
-          r.dbit[0] = o.gq[0];
+        for (auto& x : cz) {
+          if (x.second % 2 == 0) continue;
+          Lop l;
+          l.kind = 5;
+          l.sub = PH_CZ;
+          l.targets = x.first;
+          l.block = int(bi);
+          l.lv = LV_NONE;
+          add(l, 0);
         }
-      } else if (o.kind == 0 && o.k <= 2) {
-        r.kind = o.k == 1 ? (o.xswap ? 4 : 0) : 1;
-        r.p1 = regidx[o.lt[0]];
-        r.p2 = o.k == 2 ? regidx[o.lt[1]] : 0;
-        if (r.p1 < 0 || (o.k == 2 && r.p2 < 0)) return fail(QSV_EINVAL, "internal: target not in registers");
-      } else if (o.kind == 1 && o.k <= 2) {
-        r.kind = 2;
-        for (int j = 0; j < o.k; ++j) {
-          if (o.lt[j] >= 0) {
-            if (regidx[o.lt[j]] >= 0) {
-              r.dsrc[j] = 0;
-              r.dbit[j] = regidx[o.lt[j]];
-            } else {
-              r.dsrc[j] = 1;
-              r.dbit[j] = thridx[o.lt[j]];
-            }
-          } else {
-            r.dsrc[j] = 2;
-            r.dbit[j] = o.gq[j];
-          }
+        for (auto& x : str) {
+          Lop l;
+          l.kind = 5;
+          l.sub = PH_ZSTR;
+          l.targets = x.first;
+          l.block = int(bi);
+          l.lv = LV_ZSTR;
+          l.gates = x.second;
+          add(l, 1);
         }
-      } else {
-        r.kind = 3;
-      }
-      if (r.kind == 0 && cfg.c64 && cfg.mfma && r.ri_cm == 0 && r.ti_cm == 0) {
-        r.key = reg_key(7, r.p1, 0, false);
-      } else if (r.kind == 0 || r.kind == 1 || r.kind == 4) {
-        r.key = reg_key(r.kind, r.p1, r.p2, r.ri_cm != 0 || r.ti_cm != 0);
-      } else if (r.kind == 2) {
-        // register-bit targets of the diagonal, ascending (-1: absent)
-        int a = -1, b = -1;
-        for (int j = 0; j < o.k; ++j) {
-          if (r.dsrc[j] != 0) continue;
-          if (a < 0) a = r.dbit[j];
-          else b = r.dbit[j];
-        }
-        if (b >= 0 && b < a) std::swap(a, b);
-        r.key = reg_key(2, a, b, r.ri_cm != 0 || r.ti_cm != 0);
-      }
-      const bool layerable = use_layers && r.kind == 0 && o.kind == 0 && o.k == 1 && !o.xswap && r.ri_cm == 0 &&
-                             r.ti_cm == 0 && r.gcm == 0 && r.p1 >= 0 && r.p1 < 4;
-      if (layerable) {
-        if (lay_mask >> r.p1 & 1) flush_layer();  // (same qubit: keep the order)
-        if (lay_mask == 0) lay_first = r;
-        lay_mask |= 1 << r.p1;
-        lay_moff[r.p1] = r.moff;
         continue;
       }
-      flush_layer();
-      out_rops.push_back(r);
+    } else if (B.targets.size() == 1 && B.controls.empty() && !B.xswap) {
+      // one-qubit block: diagonals around a single RX / RY, or any unitary
+      std::vector<int> pre, post;
+      int rot = -1, axis = 0;
+      bool single = true, unitary = true;
+      for (int gi : B.gates) {
+        const Gate& g = C.gates[size_t(gi)];
+        const GateInfo I = analyse(g);
+        if (I.targets.size() != 1 || !I.controls.empty()) single = unitary = false;
+        if (g.kind == Gate::MATRIX && unitary && !is_unitary2(I.mat.data(), tol)) unitary = false;
+        if (I.diagonal) {
+          (rot < 0 ? pre : post).push_back(gi);
+        } else if (rot < 0 && g.kind != Gate::MATRIX) {
+          rot = gi;
+          axis = g.kind == Gate::ROTATION ? g.pauli : g.paulis[0];
+        } else {
+          single = false;
+        }
+      }
+      Lop l;
+      l.targets = B.targets;
+      l.block = int(bi);
+      if (single && rot >= 0) {
+        l.kind = 5;
+        l.sub = PH_DIAG1;
+        l.lv = LV_DIAG1;
+        if (!pre.empty()) {
+          l.gates = pre;
+          add(l, 2);
+        }
+        Lop r = l;
+        r.kind = 4;
+        r.axis = axis;
+        r.lv = LV_ROT;
+        r.gates = {rot};
+        add(r, 2);
+        if (!post.empty()) {
+          l.gates = post;
+          add(l, 2);
+        }
+        continue;
+      }
+      if (unitary) {
+        const int base = p->nvals;
+        p->nvals += 6;
+        l.kind = 5;
+        l.sub = PH_DIAG1;
+        l.lv = LV_U_FIRST;
+        l.voff = base;
+        p->lops.push_back(l);
+        Lop r = l;
+        r.kind = 4;
+        r.axis = 2;
+        r.lv = LV_U_ROT;
+        r.voff = base + 2;
+        p->lops.push_back(r);
+        l.lv = LV_U_LAST;
+        l.voff = base + 4;
+        p->lops.push_back(l);
+        continue;
+      }
     }
-    flush_layer();
-    sd.op_count = int(out_rops.size()) - sd.op_begin;
-    out_segs.push_back(sd);
-    d.seg_count++;
+    add(whole, nv);
   }
-  // LDS address tables of the pass's segments: the tile's LDS index is
-  // swizzled by j ^ (j >> SB) ^ (j >> 2 SB) (low SB bits of each), linear over
-  // XOR, so the byte offset splits into a per-thread part (XOR of per-bit
-  // columns) and a per-element part
-  const int SB = c64 ? 5 : 4;
-  const uint32_t esz = c64 ? 8u : 16u;
-  auto swz = [SB](uint32_t j) {
-    const uint32_t m = (1u << SB) - 1;
-    return j ^ ((j >> SB) & m) ^ ((j >> (2 * SB)) & m);
-  };
-  auto gbit = [&](int p) { return uint64_t(1) << (p < d.b ? p : d.hq[p - d.b]); };
-  for (int si = d.seg_begin; si < d.seg_begin + d.seg_count; ++si) {
-    RegSegDev& S = out_segs[size_t(si)];
-    for (int k = 0; k < TB; ++k) S.gcol_t[k] = gbit(S.thr[k]);
-    for (int k = 0; k < RB; ++k) S.gcol_r[k] = gbit(S.reg[k]);
-    for (int k = 0; k < TB; ++k) S.get_tcol[k] = swz(1u << S.thr[k]) * esz;
-    for (int i = 0; i < (1 << RB); ++i) {
-      uint32_t x = 0;
-      for (int k = 0; k < RB; ++k)
-        if (i >> k & 1) x |= 1u << S.reg[k];
-      S.get_reg[i] = swz(x) * esz;
-    }
-    if (si == d.seg_begin) continue;
-    const RegSegDev& O = out_segs[size_t(si) - 1];  // written through S's map
-    S.put_tcst = swz(S.mcst) * esz;
-    for (int k = 0; k < TB; ++k) S.put_tcol[k] = swz(S.mcol[O.thr[k]]) * esz;
-    for (int i = 0; i < (1 << RB); ++i) {
-      uint32_t x = 0;
-      for (int k = 0; k < RB; ++k)
-        if (i >> k & 1) x ^= S.mcol[O.reg[k]];
-      S.put_reg[i] = swz(x) * esz;
-    }
+}
+
+// Passes of the plan's elementary ops.
+static int plan_passes(qsv_plan* p) {
+  build_lops(p);
+  std::vector<PassOp> ops(p->lops.size());
+  for (size_t i = 0; i < p->lops.size(); ++i) {
+    const Lop& l = p->lops[i];
+    PassOp& o = ops[i];
+    const uint64_t t = qmask(l.targets), c = qmask(l.controls);
+    const bool diag = l.kind == 1 || l.kind == 5;
+    o.nd = diag ? 0 : t;
+    o.dg = diag ? (t | c) : c;
+    o.local = diag ? 0 : t;
+    o.lazy = l.kind == 5;
+    o.weight = l.kind == 1 || l.xswap ? 1 : 4;
   }
+  std::vector<std::vector<int>> po;
+  std::vector<uint64_t> pl;
+  const int rc = schedule_passes(ops, p->n, p->L, p->b, 1 << 30, po, pl);
+  if (rc) return rc;
+  p->passes.clear();
+  for (size_t i = 0; i < po.size(); ++i) p->passes.push_back({mask_list(pl[i]), po[i]});
   return QSV_OK;
 }
 
-// Device tables for the passes and ops (matrix offsets fixed here; matrix
-// values are uploaded at apply time).
-static int upload_tables(qsv_plan* p, std::vector<int>& moffs, size_t& pool_elems) {
+// Device tables for the passes and ops (value offsets fixed here; the values
+// are uploaded at apply time).
+static int upload_tables(qsv_plan* p) {
   const int n = p->n;
   std::vector<TilePassDev> hp;
   std::vector<TileOpDev> ho;
-  moffs.assign(p->blocks.size(), 0);
-  pool_elems = 0;
-  for (size_t bi = 0; bi < p->blocks.size(); ++bi) {
-    const Block& B = p->blocks[bi];
-    moffs[bi] = int(pool_elems);
-    const size_t k = B.targets.size();
-    pool_elems += B.diagonal ? (size_t(1) << k) : (size_t(1) << (2 * k));
-  }
   for (const auto& P : p->passes) {
     TilePassDev d{};
     d.L = int(P.local.size());
@@ -855,17 +551,19 @@ static int upload_tables(qsv_plan* p, std::vector<int>& moffs, size_t& pool_elem
     for (int q = 0; q < n; ++q)
       if (!(lm >> q & 1)) d.gpos[d.ng++] = q;
     pass_runs(d);
+    d.scale_off = -1;
     d.op_begin = int(ho.size());
-    d.op_count = int(P.blocks.size());
+    d.op_count = int(P.ops.size());
     std::vector<int> lpos(64, -1);
     for (size_t i = 0; i < P.local.size(); ++i) lpos[P.local[i]] = int(i);
-    for (int bi : P.blocks) {
-      const Block& B = p->blocks[bi];
+    for (int bi : P.ops) {
+      const Lop& B = p->lops[size_t(bi)];
       TileOpDev o{};
-      o.kind = B.diagonal ? 1 : 0;
-      o.xswap = B.xswap ? 1 : 0;
+      o.kind = B.kind;
+      o.sub = B.sub;
+      o.xswap = B.kind == 4 ? B.axis : (B.xswap ? 1 : 0);
       o.k = int(B.targets.size());
-      o.moff = moffs[bi];
+      o.moff = B.voff;
       for (size_t j = 0; j < B.controls.size(); ++j) {
         const int q = B.controls[j];
         if (lpos[q] >= 0) {
@@ -885,12 +583,12 @@ static int upload_tables(qsv_plan* p, std::vector<int>& moffs, size_t& pool_elem
         if (lpos[q] >= 0) o.lt[j] = lpos[q];
         else o.gq[j] = q;
       }
+      if (o.kind == 0 || o.kind == 4)
+        for (int j = 0; j < o.k; ++j)
+          if (o.lt[j] < 0) return fail(QSV_EINVAL, "internal: dense target not local");
       if (o.kind == 0) {
         uint32_t ins = o.lcm;
-        for (int j = 0; j < o.k; ++j) {
-          if (o.lt[j] < 0) return fail(QSV_EINVAL, "internal: dense target not local");
-          ins |= 1u << o.lt[j];
-        }
+        for (int j = 0; j < o.k; ++j) ins |= 1u << o.lt[j];
         if (__builtin_popcount(ins) > 10) return fail(QSV_EINVAL, "too many local controls on one gate");
         o.m = 0;
         for (int q = 0; q < 32; ++q)
@@ -901,16 +599,15 @@ static int upload_tables(qsv_plan* p, std::vector<int>& moffs, size_t& pool_elem
             if (i >> j & 1) off |= 1u << o.lt[j];
           o.off[i] = off;
         }
+        p->kmax_dense = std::max(p->kmax_dense, o.k);
       }
-      if (o.kind == 0) p->kmax_dense = std::max(p->kmax_dense, o.k);
       ho.push_back(o);
     }
-    d.seg_begin = int(p->h_segs.size());
+    d.seg_begin = int(p->sb.segs.size());
     d.seg_count = 0;
-    if (p->reg_bits > 0 && d.L == p->reg_bits + p->thread_bits) {
-      const SegCfg cfg{p->reg_bits, p->thread_bits, p->dtype == QSV_C64,
-                       p->dtype == QSV_C64 && tile_mfma_default()};
-      int rc = build_reg_segments(cfg, ho, d, p->h_segs, p->h_rops);
+    if (p->reg_bits > 0) {
+      const SegCfg cfg{p->reg_bits, p->thread_bits, p->dtype == QSV_C64};
+      int rc = build_reg_segments(cfg, ho, d, p->sb);
       if (rc) return rc;
     }
     hp.push_back(d);
@@ -920,135 +617,197 @@ static int upload_tables(qsv_plan* p, std::vector<int>& moffs, size_t& pool_elem
   return QSV_OK;
 }
 
-// Device copies of the pass and op tables, made on the first apply so that
-// planning itself needs no device.
-static int ensure_tables(qsv_plan* p, hipStream_t stream) {
-  if (p->d_pass) return QSV_OK;
-  if (hipMalloc(reinterpret_cast<void**>(&p->d_pass), p->h_pass.size() * sizeof(TilePassDev)) != hipSuccess)
-    return fail(QSV_ENOMEM, "plan table allocation failed");
-  if (hipMalloc(reinterpret_cast<void**>(&p->d_ops),
-                std::max<size_t>(1, p->h_ops.size()) * sizeof(TileOpDev)) != hipSuccess) {
-    (void)hipFree(p->d_pass);
-    p->d_pass = nullptr;
-    return fail(QSV_ENOMEM, "plan table allocation failed");
-  }
-  if (hipMalloc(reinterpret_cast<void**>(&p->d_segs),
-                std::max<size_t>(1, p->h_segs.size()) * sizeof(RegSegDev)) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&p->d_rops),
-                std::max<size_t>(1, p->h_rops.size()) * sizeof(RegOpDev)) != hipSuccess)
-    return fail(QSV_ENOMEM, "plan table allocation failed");
-  QSV_HIP_CHECK(hipMemcpyAsync(p->d_pass, p->h_pass.data(), p->h_pass.size() * sizeof(TilePassDev),
-                               hipMemcpyHostToDevice, stream));
-  if (!p->h_ops.empty())
-    QSV_HIP_CHECK(hipMemcpyAsync(p->d_ops, p->h_ops.data(), p->h_ops.size() * sizeof(TileOpDev),
-                                 hipMemcpyHostToDevice, stream));
-  if (!p->h_segs.empty())
-    QSV_HIP_CHECK(hipMemcpyAsync(p->d_segs, p->h_segs.data(), p->h_segs.size() * sizeof(RegSegDev),
-                                 hipMemcpyHostToDevice, stream));
-  if (!p->h_rops.empty())
-    QSV_HIP_CHECK(hipMemcpyAsync(p->d_rops, p->h_rops.data(), p->h_rops.size() * sizeof(RegOpDev),
-                                 hipMemcpyHostToDevice, stream));
-  QSV_HIP_CHECK(hipStreamSynchronize(stream));
-  return QSV_OK;
-}
-
-// Block matrices (or diagonals) for parameters theta, written as complex
-// doubles in block order.
-void plan_block_values(const qsv_plan* p, const double* theta, std::vector<cd>& pool) {
+// Host values of the plan's elementary ops for parameters theta (FP64).
+static void plan_values(const qsv_plan* p, const double* theta, std::vector<cd>& vals) {
   const qsv_circuit& C = p->circ_copy;
-  pool.clear();
+  vals.assign(size_t(p->nvals), cd{0, 0});
   std::vector<cd> gm, full, acc, tmp;
-  for (const Block& B : p->blocks) {
-    const int k = int(B.targets.size());
-    const int D = 1 << k;
+  auto angle = [&](int gi) {
+    const Gate& g = C.gates[size_t(gi)];
+    return g.slot >= 0 ? theta[g.slot] : g.fixed_angle;
+  };
+  // matrix of a block's targets (its controls, if any, are apart)
+  auto block_matrix = [&](const Block& B) {
     if (B.gates.size() == 1) {
-      const Gate& g = C.gates[B.gates[0]];
-      GateInfo gi = analyse(g);
-      extracted_matrix(g, gi, theta, gm);
-      if (B.diagonal) {
-        for (int i = 0; i < D; ++i) pool.push_back(gm[size_t(i) * D + i]);
-      } else {
-        pool.insert(pool.end(), gm.begin(), gm.end());
-      }
-      continue;
+      const Gate& g = C.gates[size_t(B.gates[0])];
+      extracted_matrix(g, analyse(g), theta, acc);
+      return;
     }
+    const int D = 1 << B.targets.size();
     acc.assign(size_t(D) * D, cd{0, 0});
     for (int i = 0; i < D; ++i) acc[size_t(i) * D + i] = {1, 0};
     for (int gidx : B.gates) {
-      const Gate& g = C.gates[gidx];
-      GateInfo gi = analyse(g);
+      const Gate& g = C.gates[size_t(gidx)];
+      const GateInfo gi = analyse(g);
       extracted_matrix(g, gi, theta, gm);
       embed(gm, gi, B.targets, full);
       matmul(full, acc, D, tmp);  // later gate on the left
       acc.swap(tmp);
     }
-    if (B.diagonal) {
-      for (int i = 0; i < D; ++i) pool.push_back(acc[size_t(i) * D + i]);
-    } else {
-      pool.insert(pool.end(), acc.begin(), acc.end());
+  };
+  for (const Lop& l : p->lops) {
+    cd* v = vals.data() + l.voff;
+    switch (l.lv) {
+      case LV_NONE:
+      case LV_U_FIRST:
+      case LV_U_LAST:
+        break;
+      case LV_ROT:
+        rotation_shears(angle(l.gates[0]), v);
+        break;
+      case LV_DIAG1:
+        v[0] = v[1] = {1, 0};
+        for (int gi : l.gates) {
+          const Gate& g = C.gates[size_t(gi)];
+          if (g.kind == Gate::MATRIX) extracted_matrix(g, analyse(g), theta, gm);
+          else gate_matrix(g, theta, gm);
+          v[0] = cmul(gm[0], v[0]);
+          v[1] = cmul(gm[3], v[1]);
+        }
+        break;
+      case LV_ZSTR: {
+        double t = 0.0;
+        if (l.gates.size() == 1) {
+          t = angle(l.gates[0]);
+          v[0] = {std::cos(t / 2), std::sin(t / 2)};
+        } else {
+          v[0] = {1, 0};
+          for (int gi : l.gates) {
+            t = angle(gi);
+            v[0] = cmul(cd{std::cos(t / 2), std::sin(t / 2)}, v[0]);
+          }
+        }
+        break;
+      }
+      case LV_U_ROT:
+        block_matrix(p->blocks[size_t(l.block)]);
+        unitary_to_rotation(acc.data(), v - 2);
+        break;
+      default: {
+        const Block& B = p->blocks[size_t(l.block)];
+        block_matrix(B);
+        const int D = 1 << B.targets.size();
+        if (B.diagonal)
+          for (int i = 0; i < D; ++i) v[i] = acc[size_t(i) * D + i];
+        else
+          std::copy(acc.begin(), acc.end(), v);
+      }
     }
   }
+}
+
+// Device pool for parameters theta: the values themselves (LDS-resident
+// passes) or the tables of the register segments.
+static void plan_pool(const qsv_plan* p, const double* theta, std::vector<cd>& pool) {
+  std::vector<cd> vals;
+  plan_values(p, theta, vals);
+  if (p->reg_bits > 0) assemble_pool(p->sb, vals, pool);
+  else pool.swap(vals);
+}
+
+// Device copies of the pass and op tables, made on the first apply so that
+// planning itself needs no device; a circuit without parameters has its pool
+// uploaded here too, once.
+template <typename R>
+static int ensure_tables(qsv_plan* p, hipStream_t stream) {
+  if (p->d_pass) return QSV_OK;
+  const size_t pool_n = size_t(std::max(1, p->reg_bits > 0 ? p->sb.pool_elems + kPoolSpare : p->nvals));
+  std::vector<cx<R>> pool;
+  if (p->circ_copy.nparams == 0) {
+    std::vector<cd> vals;
+    plan_pool(p, nullptr, vals);
+    pool.resize(vals.size());
+    for (size_t i = 0; i < vals.size(); ++i) pool[i] = {R(vals[i].re), R(vals[i].im)};
+  }
+  const std::vector<RegHeadDev> heads = op_heads(p->sb);
+  void* buf[7] = {};
+  const size_t bytes[7] = {p->h_pass.size() * sizeof(TilePassDev), p->h_ops.size() * sizeof(TileOpDev),
+                           p->sb.segs.size() * sizeof(RegSegDev),  p->sb.rops.size() * sizeof(RegOpDev),
+                           p->sb.ents.size() * sizeof(PhaseEntDev), pool_n * sizeof(cx<R>),
+                           heads.size() * sizeof(RegHeadDev)};
+  const void* src[7] = {p->h_pass.data(), p->h_ops.data(), p->sb.segs.data(), p->sb.rops.data(),
+                        p->sb.ents.data(), pool.data(),    heads.data()};
+  int rc = QSV_OK;
+  for (int i = 0; i < 7 && !rc; ++i)
+    if (hipMalloc(&buf[i], std::max<size_t>(bytes[i], 16)) != hipSuccess) {
+      (void)hipGetLastError();
+      buf[i] = nullptr;
+      rc = fail(QSV_ENOMEM, "plan table allocation failed");
+    }
+  for (int i = 0; i < 7 && !rc; ++i) {
+    const size_t nb = i == 5 ? pool.size() * sizeof(cx<R>) : bytes[i];
+    if (nb && hipMemcpyAsync(buf[i], src[i], nb, hipMemcpyHostToDevice, stream) != hipSuccess)
+      rc = fail(QSV_EHIP, "plan table upload failed");
+  }
+  if (!rc && hipStreamSynchronize(stream) != hipSuccess) rc = fail(QSV_EHIP, "plan table upload failed");
+  if (rc) {
+    for (void* b : buf)
+      if (b) (void)hipFree(b);
+    return rc;
+  }
+  p->d_pass = static_cast<TilePassDev*>(buf[0]);
+  p->d_ops = static_cast<TileOpDev*>(buf[1]);
+  p->d_segs = static_cast<RegSegDev*>(buf[2]);
+  p->d_rops = static_cast<RegOpDev*>(buf[3]);
+  p->d_ents = static_cast<PhaseEntDev*>(buf[4]);
+  p->d_pool = buf[5];
+  p->d_heads = static_cast<RegHeadDev*>(buf[6]);
+  p->pool_cap = pool_n;
+  p->pass_grid.assign(p->passes.size(), 0);
+  return QSV_OK;
 }
 
 // Register-resident pass launch for the instantiated shapes (register bits,
 // thread bits): complex64 (4, 9), (4, 8), (5, 8), (4, 7); complex128 (4, 8), (4, 7).
+template <typename R>
+using TileRegFn = void (*)(R*, const TilePassDev*, int, uint32_t, const RegSegDev*, const RegHeadDev*, const RegOpDev*,
+                           const TileOpDev*, const PhaseEntDev*, const cx<R>*);
+
 template <typename R, int RB, int TB>
-static void launch_tile_reg_km(int km, dim3 grid, size_t lds, hipStream_t st, R* psi, const qsv_plan* p,
-                               int pi, const cx<R>* pool) {
-  const dim3 block(1u << TB);
-  const TilePassDev* pd = p->d_pass;
-  if (km == 2)
-    hipLaunchKernelGGL((k_tile_reg<R, RB, 2, TB>), grid, block, lds, st, psi, pd, pi, p->d_segs, p->d_rops, p->d_ops, pool);
-  else if (km == 3)
-    hipLaunchKernelGGL((k_tile_reg<R, RB, 3, TB>), grid, block, lds, st, psi, pd, pi, p->d_segs, p->d_rops, p->d_ops, pool);
-  else
-    hipLaunchKernelGGL((k_tile_reg<R, RB, 5, TB>), grid, block, lds, st, psi, pd, pi, p->d_segs, p->d_rops, p->d_ops, pool);
+static TileRegFn<R> tile_reg_km(int km) {
+  return km == 0   ? &k_tile_reg<R, RB, 0, TB>
+         : km == 2 ? &k_tile_reg<R, RB, 2, TB>
+         : km == 3 ? &k_tile_reg<R, RB, 3, TB>
+                   : &k_tile_reg<R, RB, 5, TB>;
 }
 
 template <typename R>
-static void launch_tile_reg(int rb, int tb, int km, dim3 grid, size_t lds, hipStream_t st, R* psi,
-                            const qsv_plan* p, int pi, const cx<R>* pool) {
+static TileRegFn<R> tile_reg_fn(int rb, int tb, int km) {
   if constexpr (sizeof(R) == 4) {
-    if (tb == 9) return launch_tile_reg_km<R, 4, 9>(km, grid, lds, st, psi, p, pi, pool);
-    if (tb == 8 && rb == 5) return launch_tile_reg_km<R, 5, 8>(km, grid, lds, st, psi, p, pi, pool);
+    if (tb == 9) return tile_reg_km<R, 4, 9>(km);
+    if (tb == 8 && rb == 5) return tile_reg_km<R, 5, 8>(km);
   }
-  if (tb == 7) return launch_tile_reg_km<R, 4, 7>(km, grid, lds, st, psi, p, pi, pool);
-  launch_tile_reg_km<R, 4, 8>(km, grid, lds, st, psi, p, pi, pool);
+  if (tb == 7) return tile_reg_km<R, 4, 7>(km);
+  return tile_reg_km<R, 4, 8>(km);
 }
 
 template <typename R>
 static int apply_fused_t(qsv_state* s, qsv_plan* p, const double* theta) {
-  int trc = ensure_tables(p, s->stream);
+  int trc = ensure_tables<R>(p, s->stream);
   if (trc) return trc;
-  std::vector<cd> vals;
-  plan_block_values(p, theta, vals);
-  const size_t bytes = vals.size() * sizeof(cx<R>);
-  if (p->pool_cap < vals.size()) {
-    if (p->d_pool) {
-      QSV_HIP_CHECK(hipStreamSynchronize(s->stream));
-      (void)hipFree(p->d_pool);
-      p->d_pool = nullptr;
+  const bool upload = p->circ_copy.nparams > 0;
+  if (upload) {
+    std::vector<cd> vals;
+    plan_pool(p, theta, vals);
+    const size_t bytes = vals.size() * sizeof(cx<R>);
+    if (p->stage_bytes < bytes) {
+      if (p->h_stage) {
+        if (p->stage_used) QSV_HIP_CHECK(hipEventSynchronize(p->stage_ev));
+        (void)hipHostFree(p->h_stage);
+        p->h_stage = nullptr;
+        p->stage_bytes = 0;
+      }
+      if (hipHostMalloc(&p->h_stage, std::max<size_t>(bytes, 16), hipHostMallocDefault) != hipSuccess)
+        return fail(QSV_ENOMEM, "plan staging allocation failed");
+      p->stage_bytes = bytes;
     }
-    if (hipMalloc(&p->d_pool, std::max<size_t>(bytes, 16)) != hipSuccess)
-      return fail(QSV_ENOMEM, "plan pool allocation failed");
-    p->pool_cap = vals.size();
+    if (!p->stage_ev) QSV_HIP_CHECK(hipEventCreateWithFlags(&p->stage_ev, hipEventDisableTiming));
+    if (p->stage_used) QSV_HIP_CHECK(hipEventSynchronize(p->stage_ev));
+    cx<R>* st = static_cast<cx<R>*>(p->h_stage);
+    for (size_t i = 0; i < vals.size(); ++i) st[i] = {R(vals[i].re), R(vals[i].im)};
+    if (bytes)
+      QSV_HIP_CHECK(hipMemcpyAsync(p->d_pool, p->h_stage, bytes, hipMemcpyHostToDevice, s->stream));
   }
-  if (p->stage_bytes < bytes) {
-    if (p->h_stage) {
-      if (p->stage_used) QSV_HIP_CHECK(hipEventSynchronize(p->stage_ev));
-      (void)hipHostFree(p->h_stage);
-      p->h_stage = nullptr;
-    }
-    if (hipHostMalloc(&p->h_stage, std::max<size_t>(bytes, 16), hipHostMallocDefault) != hipSuccess)
-      return fail(QSV_ENOMEM, "plan staging allocation failed");
-    p->stage_bytes = bytes;
-  }
-  if (!p->stage_ev) QSV_HIP_CHECK(hipEventCreateWithFlags(&p->stage_ev, hipEventDisableTiming));
-  if (p->stage_used) QSV_HIP_CHECK(hipEventSynchronize(p->stage_ev));
-  cx<R>* st = static_cast<cx<R>*>(p->h_stage);
-  for (size_t i = 0; i < vals.size(); ++i) st[i] = {R(vals[i].re), R(vals[i].im)};
-  if (bytes)
-    QSV_HIP_CHECK(hipMemcpyAsync(p->d_pool, p->h_stage, bytes, hipMemcpyHostToDevice, s->stream));
   const int n = s->n;
   for (size_t pi = 0; pi < p->passes.size(); ++pi) {
     const int L = int(p->passes[pi].local.size());
@@ -1058,9 +817,9 @@ static int apply_fused_t(qsv_state* s, qsv_plan* p, const double* theta) {
     if (hp.seg_count == 1) {
       // a single register-resident segment never touches LDS unless one of
       // its blocks runs through LDS: launch without it (higher occupancy)
-      const RegSegDev& sg = p->h_segs[hp.seg_begin];
+      const RegSegDev& sg = p->sb.segs[size_t(hp.seg_begin)];
       bool needs = false;
-      for (int o = sg.op_begin; o < sg.op_begin + sg.op_count; ++o) needs |= p->h_rops[o].kind == 3;
+      for (int o = sg.op_begin; o < sg.op_begin + sg.op_count; ++o) needs |= p->sb.rops[size_t(o)].kind == 3;
       if (!needs) lds = 0;
     }
     if (lds > 65536) {
@@ -1076,9 +835,20 @@ static int apply_fused_t(qsv_state* s, qsv_plan* p, const double* theta) {
     const cx<R>* pool = static_cast<const cx<R>*>(p->d_pool);
     const dim3 grid(static_cast<unsigned>(tiles));
     const int km = p->kmax_dense <= 2 ? 2 : (p->kmax_dense <= 3 ? 3 : 5);
-    if (p->h_pass[pi].seg_count > 0)
-      launch_tile_reg<R>(p->reg_bits, p->thread_bits, km, grid, lds, s->stream, psi, p, int(pi), pool);
-    else if (km == 2)
+    if (p->h_pass[pi].seg_count > 0) {
+      const TileRegFn<R> fn = tile_reg_fn<R>(p->reg_bits, p->thread_bits, hp.general ? km : 0);
+      const unsigned nt = 1u << p->thread_bits;
+      if (p->pass_grid[pi] == 0) {
+        int per = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, int(nt), lds) != hipSuccess || per < 1) per = 1;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess || cus < 1)
+          cus = 256;
+        p->pass_grid[pi] = per * cus * 8;
+      }
+      const uint64_t wgs = std::min<uint64_t>(tiles, uint64_t(p->pass_grid[pi]));
+      hipLaunchKernelGGL(fn, dim3(unsigned(wgs)), dim3(nt), lds, s->stream, psi, p->d_pass, int(pi), uint32_t(tiles), p->d_segs,
+                         p->d_heads, p->d_rops, p->d_ops, p->d_ents, pool);
+    } else if (km == 2)
       hipLaunchKernelGGL((k_tile<R, 2>), grid, dim3(256), lds, s->stream, psi, p->d_pass, int(pi), p->d_ops, pool);
     else if (km == 3)
       hipLaunchKernelGGL((k_tile<R, 3>), grid, dim3(256), lds, s->stream, psi, p->d_pass, int(pi), p->d_ops, pool);
@@ -1086,8 +856,10 @@ static int apply_fused_t(qsv_state* s, qsv_plan* p, const double* theta) {
       hipLaunchKernelGGL((k_tile<R, 5>), grid, dim3(256), lds, s->stream, psi, p->d_pass, int(pi), p->d_ops, pool);
     QSV_HIP_CHECK(hipGetLastError());
   }
-  QSV_HIP_CHECK(hipEventRecord(p->stage_ev, s->stream));
-  p->stage_used = true;
+  if (upload) {
+    QSV_HIP_CHECK(hipEventRecord(p->stage_ev, s->stream));
+    p->stage_used = true;
+  }
   return QSV_OK;
 }
 
@@ -1102,6 +874,8 @@ static void plan_release(qsv_plan* p) {
   if (p->d_ops) (void)hipFree(p->d_ops);
   if (p->d_segs) (void)hipFree(p->d_segs);
   if (p->d_rops) (void)hipFree(p->d_rops);
+  if (p->d_ents) (void)hipFree(p->d_ents);
+  if (p->d_heads) (void)hipFree(p->d_heads);
   delete p;
 }
 
@@ -1141,9 +915,8 @@ static int plan_create(const qsv_circuit* c, qsv_dtype dtype, int max_k, int til
   p->reg_bits = (rb_ok && n >= L) ? RB : 0;
   p->circ_copy = *c;
   int rc = build_plan(p);
-  std::vector<int> moffs;
-  size_t pool_elems = 0;
-  if (!rc) rc = upload_tables(p, moffs, pool_elems);
+  if (!rc) rc = plan_passes(p);
+  if (!rc) rc = upload_tables(p);
   if (rc) {
     plan_release(p);
     return rc;
@@ -1282,9 +1055,9 @@ int qsv_plan_stats(const qsv_plan* p, int* segments, int* lds_ops, int* kmax) {
   clear_error();
   if (!p) return fail(QSV_EINVAL, "null plan");
   int lo = 0;
-  for (const RegOpDev& r : p->h_rops)
+  for (const RegOpDev& r : p->sb.rops)
     if (r.kind == 3) ++lo;
-  if (segments) *segments = int(p->h_segs.size());
+  if (segments) *segments = int(p->sb.segs.size());
   if (lds_ops) *lds_ops = lo;
   if (kmax) *kmax = p->kmax_dense;
   return QSV_OK;
