@@ -93,7 +93,7 @@ int expectation_impl(qsv_state* s, const qsv_observable* o, double* out);
 int apply_observable_tiled(const qsv_state* in, const qsv_observable* o, qsv_state* out);
 int circuit_apply_unfused(qsv_state* s, const qsv_circuit* c, const double* theta);
 template <typename R>
-int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, qsv_state* psi, qsv_state* lam,
+int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, double energy, qsv_state* psi, qsv_state* lam,
                            std::vector<int>& row_slot, std::vector<double>& rows);
 
 namespace {
@@ -150,7 +150,7 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
   if (n >= tiled_min && !wide) {
     std::vector<int> rs;
     std::vector<double> rv;
-    if ((rc = adjoint_backward_tiled<R>(c, theta, psi, lam, rs, rv))) return rc;
+    if ((rc = adjoint_backward_tiled<R>(c, theta, re, psi, lam, rs, rv))) return rc;
     for (int i = 0; i < c->nparams; ++i) grad[i] = 0.0;
     for (size_t r = 0; r < rs.size(); ++r) grad[rs[r]] += rv[r];
     return QSV_OK;

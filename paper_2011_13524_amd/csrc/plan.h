@@ -252,6 +252,32 @@ struct PassOp {
 int schedule_passes(const std::vector<PassOp>& ops, int n, int L, int b, int max_rows,
                     std::vector<std::vector<int>>& pass_ops, std::vector<uint64_t>& pass_local);
 
+// A host value that depends on a parameter: type 0 a rotation's shears and sign
+// (two values), 1 a rotation about Z's diagonal (two values), 2 the phase of a
+// string of Z's (one value), at voff, for the angle sgn * theta[slot].
+struct DynVal {
+  int type, voff, slot;
+  double sgn;
+};
+
+// Tables of a reverse sweep (host side; the values for the theta given, or
+// with theta null the constant ones).
+struct AdjTables {
+  int L = 0, kmax = 1;
+  bool reg = false;
+  std::vector<TilePassDev> hp;
+  std::vector<TileOpDev> ho;
+  SegBuild sb;
+  std::vector<cd> vals;
+  std::vector<DynVal> dyn;
+  std::vector<int> prow;      // gradient rows of each pass, in slot order
+  std::vector<int> row_slot;  // parameter slot of each row
+};
+template <typename R>
+int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T);
+
+constexpr int kAdjMaxRows = 64;  // gradient rows per pass (LDS slots)
+
 // A fused block: gates (indices into the circuit) applied in order, acting on
 // `qubits` (ascending). Single-gate blocks keep the gate's control structure.
 struct Block {
@@ -294,6 +320,7 @@ struct qsv_plan {
   qsv_dtype dtype = QSV_C128;
   int max_k = 2;
   bool heavy = false;  // commutation-aware merging (QSV_PLAN_HEAVY)
+  bool nomerge = false;  // every gate its own block (values follow parameters one by one)
   int L = 12, b = 5;
   const qsv_circuit* circ = nullptr;  // borrowed structure snapshot below
   qsv_circuit circ_copy;
@@ -328,3 +355,11 @@ struct qsv_plan {
   hipEvent_t stage_ev = nullptr;
   bool stage_used = false;
 };
+
+namespace qsv {
+// Host-side plan of a circuit without merged gates (the caller deletes it), and
+// its host values: the constant ones, and those that depend on parameters.
+int plan_unmerged(const qsv_circuit* c, qsv_dtype dtype, qsv_plan** out);
+void plan_free(qsv_plan* p);
+void plan_symbolic(const qsv_plan* p, std::vector<cd>& vals, std::vector<DynVal>& dyn);
+}  // namespace qsv

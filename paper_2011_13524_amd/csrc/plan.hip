@@ -300,7 +300,7 @@ static int build_plan(qsv_plan* p) {
         if (!passes) break;
       }
     } else {
-      int cand = -2;
+      int cand = p->nomerge ? -1 : -2;
       for (int q : mask_list(I.qubits)) {
         if (last[q] < 0) continue;
         if (cand == -2) cand = last[q];
@@ -882,7 +882,7 @@ static void plan_release(qsv_plan* p) {
 // Plan with an explicit register tile shape (thread bits TB); tile_qubits /
 // low_qubits 0 select the defaults.
 static int plan_create(const qsv_circuit* c, qsv_dtype dtype, int max_k, int tile_qubits, int low_qubits,
-                       int TB, qsv_plan** out, bool heavy = false) {
+                       int TB, qsv_plan** out, bool heavy = false, bool nomerge = false) {
   *out = nullptr;
   const int n = c->n;
   int L = tile_qubits > 0 ? tile_qubits : 12;
@@ -902,6 +902,7 @@ static int plan_create(const qsv_circuit* c, qsv_dtype dtype, int max_k, int til
   p->dtype = dtype;
   p->max_k = max_k;
   p->heavy = heavy;
+  p->nomerge = nomerge;
   p->L = L;
   p->b = b;
   // (blocks of 4-5 qubits run through LDS with 32-amplitude temporaries: the
@@ -923,6 +924,25 @@ static int plan_create(const qsv_circuit* c, qsv_dtype dtype, int max_k, int til
   }
   *out = p;
   return QSV_OK;
+}
+
+int plan_unmerged(const qsv_circuit* c, qsv_dtype dtype, qsv_plan** out) {
+  return plan_create(c, dtype, 1, 12, 0, kRegThreadBits, out, false, true);
+}
+
+void plan_free(qsv_plan* p) { plan_release(p); }
+
+void plan_symbolic(const qsv_plan* p, std::vector<cd>& vals, std::vector<DynVal>& dyn) {
+  const qsv_circuit& C = p->circ_copy;
+  const std::vector<double> zero(size_t(std::max(1, C.nparams)), 0.0);
+  plan_values(p, zero.data(), vals);
+  dyn.clear();
+  for (const Lop& l : p->lops)
+    if (l.lv == LV_ROT || l.lv == LV_DIAG1 || l.lv == LV_ZSTR) {
+      const Gate& g = C.gates[size_t(l.gates[0])];  // (unmerged: one gate)
+      if (g.kind != Gate::MATRIX && g.slot >= 0)
+        dyn.push_back({l.lv == LV_ROT ? 0 : (l.lv == LV_ZSTR ? 2 : 1), l.voff, g.slot, 1.0});
+    }
 }
 
 }  // namespace qsv

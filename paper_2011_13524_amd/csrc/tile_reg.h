@@ -856,16 +856,14 @@ __device__ __forceinline__ uint64_t pass_base(const TilePassDev& P, uint32_t g) 
 // matrix products in two register arrays (3320 to 4740 instructions) it took
 // 5.6 to 6.3 ms, over fresh workgroups per tile.
 template <typename R, int RB, int KMAX, int TB>
-__global__ void __launch_bounds__(1 << TB, (tile_waves_per_simd<R, RB>()))
-    k_tile_reg(R* __restrict__ psi, const TilePassDev* __restrict__ passes, int pass_idx, uint32_t ntiles,
-               const RegSegDev* __restrict__ segs, const RegHeadDev* __restrict__ heads,
-               const RegOpDev* __restrict__ rops, const TileOpDev* __restrict__ lops, const PhaseEntDev* __restrict__ ents,
-               const cx<R>* __restrict__ pool) {
+__device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev& P, uint32_t g, uint32_t step,
+                                          uint32_t ntiles, const RegSegDev* __restrict__ segs,
+                                          const RegHeadDev* __restrict__ heads, const RegOpDev* __restrict__ rops,
+                                          const TileOpDev* __restrict__ lops, const PhaseEntDev* __restrict__ ents,
+                                          const cx<R>* __restrict__ pool, char* smem) {
   constexpr int NR = 1 << RB;
   constexpr int SB = sizeof(R) == 4 ? 5 : 4;
   const Swz<SB> sw;
-  extern __shared__ __align__(16) char smem[];
-  const TilePassDev& P = passes[pass_idx];
   const int L = P.L;
   const uint32_t tau = threadIdx.x;
   const ThrMask<TB> tm(tau);
@@ -879,13 +877,12 @@ __global__ void __launch_bounds__(1 << TB, (tile_waves_per_simd<R, RB>()))
     thL |= SL->gcol_t[k] & on;
   }
   cx<R> v[1][NR], pf[NR];
-  uint32_t g = blockIdx.x;  // (the grid has at most ntiles workgroups)
   uint64_t base = pass_base(P, g);
   tile_io<R, RB, false>(psi, pf, base | th0, *S0);
   for (;;) {
 #pragma unroll
     for (int i = 0; i < NR; ++i) v[0][i] = pf[i];
-    const uint32_t gn = g + gridDim.x;  // (ntiles <= 2^27: no overflow)
+    const uint32_t gn = g + step;  // (ntiles <= 2^27: no overflow)
     const uint64_t nbase = gn < ntiles ? pass_base(P, gn) : 0;
     if (gn < ntiles) tile_io<R, RB, false>(psi, pf, nbase | th0, *S0);
     const RegSegDev* S = S0;
@@ -944,6 +941,18 @@ __global__ void __launch_bounds__(1 << TB, (tile_waves_per_simd<R, RB>()))
     base = nbase;
     __syncthreads();  // every wavefront has read its last re-map: LDS is free
   }
+}
+
+template <typename R, int RB, int KMAX, int TB>
+__global__ void __launch_bounds__(1 << TB, (tile_waves_per_simd<R, RB>()))
+    k_tile_reg(R* __restrict__ psi, const TilePassDev* __restrict__ passes, int pass_idx, uint32_t ntiles,
+               const RegSegDev* __restrict__ segs, const RegHeadDev* __restrict__ heads,
+               const RegOpDev* __restrict__ rops, const TileOpDev* __restrict__ lops, const PhaseEntDev* __restrict__ ents,
+               const cx<R>* __restrict__ pool) {
+  extern __shared__ __align__(16) char smem[];
+  // (the grid has at most ntiles workgroups)
+  tile_pass<R, RB, KMAX, TB>(psi, passes[pass_idx], blockIdx.x, gridDim.x, ntiles, segs, heads, rops, lops, ents, pool,
+                             smem);
 }
 
 }  // namespace qsv
