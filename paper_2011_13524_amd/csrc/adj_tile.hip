@@ -551,14 +551,11 @@ template int adjoint_tables<double>(const qsv_circuit*, const double*, AdjTables
 // Reverse sweep by tile passes. On entry psi = psi_L, lam = H psi_L and energy =
 // <psi|lam>; on
 // return both are uncomputed and rows[r] holds the gradient term of the r-th
-// parametric rotation counted from the end (row_slot maps rows to slots).
+// parametric rotation counted from the end (T.row_slot maps rows to slots).
 template <typename R>
-int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, double energy, qsv_state* psi, qsv_state* lam,
-                           std::vector<int>& row_slot, std::vector<double>& rows) {
-  const int n = c->n;
-  AdjTables T;
-  if (const int e = adjoint_tables<R>(c, theta, T)) return e;
-  row_slot = T.row_slot;
+int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, qsv_state* lam,
+                           std::vector<double>& rows) {
+  const std::vector<int>& row_slot = T.row_slot;
   const int L = T.L, kmax = T.kmax;
   const bool reg = T.reg;
   const std::vector<TilePassDev>& hp = T.hp;
@@ -706,9 +703,7 @@ int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, double ene
   return fin(rc);
 }
 
-template int adjoint_backward_tiled<float>(const qsv_circuit*, const double*, double, qsv_state*, qsv_state*,
-                                           std::vector<int>&, std::vector<double>&);
-template int adjoint_backward_tiled<double>(const qsv_circuit*, const double*, double, qsv_state*, qsv_state*,
-                                            std::vector<int>&, std::vector<double>&);
+template int adjoint_backward_tiled<float>(AdjTables&, int, double, qsv_state*, qsv_state*, std::vector<double>&);
+template int adjoint_backward_tiled<double>(AdjTables&, int, double, qsv_state*, qsv_state*, std::vector<double>&);
 
 }  // namespace qsv

@@ -93,8 +93,8 @@ int expectation_impl(qsv_state* s, const qsv_observable* o, double* out);
 int apply_observable_tiled(const qsv_state* in, const qsv_observable* o, qsv_state* out);
 int circuit_apply_unfused(qsv_state* s, const qsv_circuit* c, const double* theta);
 template <typename R>
-int adjoint_backward_tiled(const qsv_circuit* c, const double* theta, double energy, qsv_state* psi, qsv_state* lam,
-                           std::vector<int>& row_slot, std::vector<double>& rows);
+int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, qsv_state* lam,
+                           std::vector<double>& rows);
 
 namespace {
 
@@ -131,28 +131,39 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
   }
   // lambda = H psi
   if ((rc = apply_obs(psi, o, lam))) return rc;
-  // E = Re <psi|lambda>
-  double re = 0.0, im = 0.0;
-  if ((rc = qsv_inner(psi, lam, &re, &im))) return rc;
-  *energy = re;
-  // backward
+  // backward (planned while the device works)
   int nrot = 0;
   bool wide = false;  // Pauli rotations on more than 5 qubits: per-gate sweep only
   for (const Gate& g : c->gates) {
     if ((g.kind == Gate::ROTATION || g.kind == Gate::PAULI) && g.slot >= 0) ++nrot;
     if (g.kind == Gate::PAULI && g.targets.size() > 5) wide = true;
   }
-  // large states: reverse sweep by tile passes (both states streamed once per
-  // pass); small states keep one launch per gate, which spreads better
-  const int Ltile = sizeof(R) == 4 ? 12 : 11;
-  int tiled_min = Ltile + 8;
-  if (const char* e = std::getenv("QSV_ADJOINT_TILED_MIN")) tiled_min = std::atoi(e);  // testing
-  if (n >= tiled_min && !wide) {
-    std::vector<int> rs;
+  // reverse sweep by register tile passes (both states streamed once per pass)
+  // wherever there is a full tile; smaller states take one launch per gate.
+  // Measured, 8-layer ansatz, per gate against passes: complex64 12 qubits 1.19
+  // and 0.48 ms, 16 qubits 1.77 and 0.84, 20 qubits 3.03 and 1.28; complex128 11
+  // qubits 1.27 and 0.63 ms, 20 qubits 5.08 and 1.32. At 11 qubits complex64,
+  // through the LDS sweep, both take 1.30 ms.
+  int tiled_min = sizeof(R) == 4 ? 12 : 11;
+  int tiled_must = tiled_min + 8;  // no per-gate sweep from here on
+  if (const char* e = std::getenv("QSV_ADJOINT_TILED_MIN")) tiled_min = tiled_must = std::atoi(e);  // testing
+  AdjTables T;
+  bool tiled = n >= tiled_min && !wide;
+  if (tiled && (rc = adjoint_tables<R>(c, theta, T))) {
+    // (a gate with more local controls than the passes take)
+    if (n >= tiled_must) return rc;
+    clear_error();
+    tiled = false;
+  }
+  // E = Re <psi|lambda>
+  double re = 0.0, im = 0.0;
+  if ((rc = qsv_inner(psi, lam, &re, &im))) return rc;
+  *energy = re;
+  if (tiled) {
     std::vector<double> rv;
-    if ((rc = adjoint_backward_tiled<R>(c, theta, re, psi, lam, rs, rv))) return rc;
+    if ((rc = adjoint_backward_tiled<R>(T, n, re, psi, lam, rv))) return rc;
     for (int i = 0; i < c->nparams; ++i) grad[i] = 0.0;
-    for (size_t r = 0; r < rs.size(); ++r) grad[rs[r]] += rv[r];
+    for (size_t r = 0; r < rv.size(); ++r) grad[T.row_slot[r]] += rv[r];
     return QSV_OK;
   }
   const int B = adj_blocks(N / 2);

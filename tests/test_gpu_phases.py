@@ -113,3 +113,23 @@ def test_parametric_phases_follow_theta_and_differentiate(dt, monkeypatch):
     assert np.max(np.abs(g - ref)) <= RED_TOL[dt] * scale
     # psi is uncomputed to |0...0>, its sign included
     assert abs(psi.store()[0] - 1.0) <= 10 * AMP_TOL[dt]
+
+
+@pytest.mark.parametrize("dt,n", [("c64", 11), ("c64", 12), ("c64", 13), ("c128", 10), ("c128", 11), ("c128", 12)])
+def test_gradients_around_the_smallest_full_tile(dt, n):
+    # one tile, two tiles, and the size below (one launch per gate); then with a
+    # gate of more local controls than the passes take (the per-gate sweep does)
+    rng = np.random.default_rng(n)
+    g, npar = phase_circuit(n, 50, 5 + n, parametric=True)
+    ctrl = {"op": "dense", "q": [0], "mat": W.haar_unitary(rng, 2), "controls": list(range(1, n)),
+            "ctrl_vals": [int(v) for v in rng.integers(0, 2, n - 1)]}
+    obs = W.random_pauli_observable(n, 12, (1, 4), seed_key=(n, 3)) + [(0.4, [])]
+    theta = rng.uniform(-6.3, 6.3, npar)
+    scale = sum(abs(c) for c, _ in obs)
+    for gates in (g, g[:25] + [ctrl] + g[25:]):
+        psi, lam = State(n, dt), State(n, dt)
+        e, gr = adjoint_gradient(Circuit.from_records(n, gates), theta, Observable(n, obs), psi, lam)
+        assert abs(e - O.energy(n, gates, theta, obs)) <= RED_TOL[dt] * scale
+        slots = sorted({0, 1, npar // 2, npar - 1})
+        ref = O.param_shift_grad(n, gates, theta, obs, slots=slots)
+        assert np.max(np.abs(gr[slots] - ref)) <= RED_TOL[dt] * scale
