@@ -34,7 +34,8 @@ struct MItem {
   int theta, grad, nparams;
   int grp_begin, grp_count;
   int index;
-  int chunk0, nchunk;     // partials of the energy
+  int chunk0, nchunk;     // partials of the energy and the norm
+  int unitary;            // the norm that rounding left is divided out
 };
 
 // A distinct circuit of the batch: where its tables start.
@@ -213,13 +214,13 @@ __global__ void __launch_bounds__(1 << kRegThreadBits)
 template <typename R>
 __global__ void __launch_bounds__(kLamThreads) k_item_lam(MArgs a, const MWork* __restrict__ work, cx<R>* __restrict__ states,
                                                           double* __restrict__ epart) {
-  __shared__ double red[kLamThreads / 64];
+  __shared__ double red[2][kLamThreads / 64];
   constexpr int J = 8;
   const MWork w = work[blockIdx.x];
   const MItem& I = a.items[w.item];
   const cx<R>* __restrict__ psi = states + I.psi;
   cx<R>* __restrict__ lam = states + I.lam;
-  double e = 0.0;
+  double e = 0.0, nn = 0.0;
   for (int h = 0; h < kLamAmps / (J * kLamThreads); ++h) {
     const uint32_t base = w.g * kLamAmps + uint32_t(h) * (J * kLamThreads);
     const uint32_t y = base | threadIdx.x;
@@ -262,28 +263,44 @@ __global__ void __launch_bounds__(kLamThreads) k_item_lam(MArgs a, const MWork* 
       const cx<R> p = psi[y + j * kLamThreads], l{R(ar[j]), R(ai[j])};
       lam[y + j * kLamThreads] = l;
       e += double(p.re) * double(l.re) + double(p.im) * double(l.im);
+      nn += double(p.re) * double(p.re) + double(p.im) * double(p.im);
     }
   }
   e = wave_sum_to_last(e);
-  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = e;
+  nn = wave_sum_to_last(nn);
+  if ((threadIdx.x & 63) == 63) {
+    red[0][threadIdx.x >> 6] = e;
+    red[1][threadIdx.x >> 6] = nn;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 2) {
     double s = 0.0;
-    for (int i = 0; i < kLamThreads / 64; ++i) s += red[i];
-    epart[I.chunk0 + int(w.g)] = s;
+    for (int i = 0; i < kLamThreads / 64; ++i) s += red[threadIdx.x][i];
+    epart[2 * (I.chunk0 + int(w.g)) + int(threadIdx.x)] = s;
   }
 }
 
-// One wavefront per sum, in a fixed order.
-__global__ void __launch_bounds__(64) k_item_energy(MArgs a, const double* __restrict__ epart, double* __restrict__ energies) {
+// One wavefront per sum, in a fixed order: the energy, and the norm that the
+// gradients are divided by.
+__global__ void __launch_bounds__(64) k_item_energy(MArgs a, const double* __restrict__ epart, double* __restrict__ energies,
+                                                    double* __restrict__ norms) {
   const MItem& I = a.items[blockIdx.x];
-  double s = 0.0;
-  for (int i = int(threadIdx.x); i < I.nchunk; i += 64) s += epart[I.chunk0 + i];
+  double s = 0.0, nn = 0.0;
+  for (int i = int(threadIdx.x); i < I.nchunk; i += 64) {
+    s += epart[2 * (I.chunk0 + i)];
+    nn += epart[2 * (I.chunk0 + i) + 1];
+  }
   s = wave_sum_to_last(s);
-  if (threadIdx.x == 63) energies[I.index] = s;
+  nn = wave_sum_to_last(nn);
+  if (threadIdx.x == 63) {
+    const double d = I.unitary && nn > 0.0 && isfinite(nn) ? nn : 1.0;
+    energies[I.index] = s / d;
+    norms[blockIdx.x] = d;
+  }
 }
 
-__global__ void __launch_bounds__(256) k_item_grads(MArgs a, int nparams, const double* __restrict__ part, double* __restrict__ grads) {
+__global__ void __launch_bounds__(256) k_item_grads(MArgs a, int nparams, const double* __restrict__ part,
+                                                    const double* __restrict__ norms, double* __restrict__ grads) {
   const int p = int(blockIdx.x * 4 + (threadIdx.x >> 6));
   if (p >= nparams) return;
   const MItem& I = a.items[a.param_item[p]];
@@ -296,7 +313,7 @@ __global__ void __launch_bounds__(256) k_item_grads(MArgs a, int nparams, const 
     for (uint32_t c = lane; c < cols; c += 64) s += row[c];
   }
   s = wave_sum_to_last(s);
-  if (lane == 63) grads[I.grad + slot] = s;
+  if (lane == 63) grads[I.grad + slot] = s / norms[a.param_item[p]];
 }
 
 // ------------------------------------------------------------------ host
@@ -318,7 +335,7 @@ struct BatchTiles {
   cx<double>* d_vals = nullptr;
   const MWork* d_work = nullptr;
   void *d_states = nullptr, *d_pool = nullptr;
-  double *d_part = nullptr, *d_epart = nullptr;
+  double *d_part = nullptr, *d_epart = nullptr, *d_norms = nullptr;
 };
 
 namespace {
@@ -359,6 +376,7 @@ struct Tables {
     std::vector<char> general[2];
     std::vector<cd> vals[2];
     int rows;
+    int unitary;
   };
   std::vector<Host> host;
 
@@ -425,6 +443,7 @@ bool add_circuit(Tables& T, const qsv_circuit* c) {
     MCirc C{};
     Tables::Host H{};
     H.c = c;
+    H.unitary = circuit_unitary(c) ? 1 : 0;
     std::vector<DynVal> dv;
     plan_symbolic(p, H.vals[0], dv);
     T.append(0, C, H, p->h_pass, p->h_ops, p->sb, {}, dv);
@@ -527,6 +546,7 @@ int batch_tiles_build(const std::vector<BatchTileItem>& all, BatchTiles** out, s
     for (const Group& g : gs) groups.push_back({g.flip, g.begin + int(terms.size()), g.count});
     terms.insert(terms.end(), ts.begin(), ts.end());
     I.index = it.index;
+    I.unitary = H.unitary;
     I.chunk0 = chunks;
     I.nchunk = int(dim(I.n) / kLamAmps);
     chunks += I.nchunk;
@@ -602,8 +622,9 @@ int batch_tiles_build(const std::vector<BatchTileItem>& all, BatchTiles** out, s
   }
   t->d_vals = static_cast<cx<double>*>(const_cast<void*>(vals_p));
   const size_t b_states = al(2 * psi_total * sizeof(cx<R>)), b_pool = al(pool_total * sizeof(cx<R>)),
-               b_part = al((part_total + 1) * sizeof(double)), b_epart = al(size_t(chunks) * sizeof(double));
-  const size_t bytes = b_states + b_pool + b_part + b_epart;
+               b_part = al((part_total + 1) * sizeof(double)), b_epart = al(2 * size_t(chunks) * sizeof(double)),
+               b_norms = al(its.size() * sizeof(double));
+  const size_t bytes = b_states + b_pool + b_part + b_epart + b_norms;
   if (hipMalloc(&t->d_data, bytes) != hipSuccess) {
     (void)hipGetLastError();
     t->d_data = nullptr;
@@ -615,6 +636,7 @@ int batch_tiles_build(const std::vector<BatchTileItem>& all, BatchTiles** out, s
   t->d_pool = d + b_states;
   t->d_part = reinterpret_cast<double*>(d + b_states + b_pool);
   t->d_epart = reinterpret_cast<double*>(d + b_states + b_pool + b_part);
+  t->d_norms = reinterpret_cast<double*>(d + b_states + b_pool + b_part + b_epart);
   *out = t;
   return QSV_OK;
 }
@@ -647,7 +669,8 @@ int batch_tiles_launch(const BatchTiles* t, const double* theta, double* energie
       hipLaunchKernelGGL((k_item_tile<R, 2>), g, dim3(nt), lds_f, st, t->args, w, l.round, states, pool);
     else if (l.dir == 2) {
       hipLaunchKernelGGL((k_item_lam<R>), g, dim3(kLamThreads), 0, st, t->args, w, states, t->d_epart);
-      hipLaunchKernelGGL(k_item_energy, dim3(ni), dim3(64), 0, st, t->args, t->d_epart, energies);
+      hipLaunchKernelGGL(k_item_energy, dim3(ni), dim3(64), 0, st, t->args, t->d_epart, energies,
+                         t->d_norms);
     } else if (!l.general)
       hipLaunchKernelGGL((k_item_adj<R, 0>), g, dim3(nt), lds_r, st, t->args, w, l.round, states, pool, t->d_part,
                          energies);
@@ -657,7 +680,7 @@ int batch_tiles_launch(const BatchTiles* t, const double* theta, double* energie
   }
   if (t->nparams)
     hipLaunchKernelGGL(k_item_grads, dim3(unsigned(t->nparams + 3) / 4), dim3(256), 0, st, t->args, t->nparams, t->d_part,
-                       grads);
+                       t->d_norms, grads);
   QSV_HIP_CHECK(hipGetLastError());
   return QSV_OK;
 }

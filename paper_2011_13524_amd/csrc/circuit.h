@@ -7,6 +7,8 @@
 
 #include "qsv_internal.h"
 
+struct qsv_circuit;
+
 namespace qsv {
 
 struct Gate {
@@ -36,6 +38,9 @@ int adjoint_pauli_step(qsv_state* psi, qsv_state* lam, const Gate& g, double t, 
 
 // Gate matrix of a gate for the given parameters (row-major, 2^k x 2^k).
 void gate_matrix(const Gate& g, const double* theta, std::vector<cd>& out);
+
+// Whether every gate is unitary (matrices: to 1e-12).
+bool circuit_unitary(const qsv_circuit* c);
 
 // Rotation matrix exp(+i t P / 2) for Pauli id p (table of named gates).
 void rotation_matrix(int pauli, double t, cd* m);

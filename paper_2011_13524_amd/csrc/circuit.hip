@@ -18,6 +18,24 @@ void rotation_matrix(int pauli, double t, cd* m) {
   }
 }
 
+bool circuit_unitary(const qsv_circuit* c) {
+  for (const Gate& g : c->gates) {
+    if (g.kind != Gate::MATRIX) continue;
+    const size_t D = size_t(1) << g.targets.size();
+    for (size_t a = 0; a < D; ++a)
+      for (size_t b = 0; b <= a; ++b) {
+        cd s{a == b ? -1.0 : 0.0, 0.0};
+        for (size_t r = 0; r < D; ++r) {
+          const cd x = g.mat[r * D + a], y = g.mat[r * D + b];
+          s.re += x.re * y.re + x.im * y.im;
+          s.im += x.re * y.im - x.im * y.re;
+        }
+        if (!(std::fabs(s.re) <= 1e-12 && std::fabs(s.im) <= 1e-12)) return false;
+      }
+  }
+  return true;
+}
+
 void gate_matrix(const Gate& g, const double* theta, std::vector<cd>& out) {
   if (g.kind == Gate::ROTATION) {
     out.resize(4);

@@ -98,7 +98,8 @@ __global__ void __launch_bounds__(kRedThreads)
   if (threadIdx.x == 0) partial[blockIdx.x] = r;
 }
 
-template <typename R>
+// Two sums: Re <a|b>, and Im <a|b> or (NORM) <a|a>.
+template <typename R, bool NORM>
 __global__ void __launch_bounds__(kRedThreads)
     k_inner(const R* __restrict__ a, const R* __restrict__ b, uint64_t N, double* __restrict__ partial) {
   __shared__ double sh[kRedThreads / 64];
@@ -107,7 +108,8 @@ __global__ void __launch_bounds__(kRedThreads)
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < N; i += stride) {
     const cx<double> u = ld(a, i), v = ld(b, i);
     re += u.re * v.re + u.im * v.im;
-    im += u.re * v.im - u.im * v.re;
+    if (NORM) im += u.re * u.re + u.im * u.im;
+    else im += u.re * v.im - u.im * v.re;
   }
   double r = block_reduce_sum(re, sh);
   __syncthreads();
@@ -220,7 +222,7 @@ int expectation_t(qsv_state* s, const qsv_observable* o, double* out) {
   return QSV_OK;
 }
 
-template <typename R>
+template <typename R, bool NORM>
 int inner_t(const qsv_state* bra, const qsv_state* ket, qsv_state* scratch_owner, double* re,
             double* im) {
   const uint64_t N = dim(bra->n);
@@ -229,7 +231,7 @@ int inner_t(const qsv_state* bra, const qsv_state* ket, qsv_state* scratch_owner
   if (rc) return rc;
   double* partial = scratch_owner->red;
   hipStream_t st = scratch_owner->stream;
-  hipLaunchKernelGGL((k_inner<R>), dim3(nb), dim3(kRedThreads), 0, st,
+  hipLaunchKernelGGL((k_inner<R, NORM>), dim3(nb), dim3(kRedThreads), 0, st,
                      static_cast<const R*>(bra->ptr), static_cast<const R*>(ket->ptr), N, partial);
   QSV_HIP_CHECK(hipGetLastError());
   hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kRedThreads), 0, st, partial, nb, 2,
@@ -266,6 +268,12 @@ int marginal_t(qsv_state* s, const InsertPos& ins, uint64_t vals, double* out) {
 }
 
 }  // namespace
+
+// Re <psi|lam> and <psi|psi> in one pass (states of one stream).
+int inner_and_norm(const qsv_state* psi, qsv_state* lam, double* re, double* norm2) {
+  return psi->dtype == QSV_C64 ? inner_t<float, true>(psi, lam, lam, re, norm2)
+                               : inner_t<double, true>(psi, lam, lam, re, norm2);
+}
 
 int expectation_impl(qsv_state* s, const qsv_observable* o, double* out) {
   return s->dtype == QSV_C64 ? expectation_t<float>(s, o, out) : expectation_t<double>(s, o, out);
@@ -317,8 +325,8 @@ int qsv_inner(const qsv_state* bra, const qsv_state* ket, double* re, double* im
   if (bra->dtype != ket->dtype) return fail(QSV_EDTYPE, "dtypes differ");
   if (bra->stream != ket->stream) QSV_HIP_CHECK(hipStreamSynchronize(bra->stream));
   qsv_state* owner = const_cast<qsv_state*>(ket);
-  return bra->dtype == QSV_C64 ? inner_t<float>(bra, ket, owner, re, im)
-                               : inner_t<double>(bra, ket, owner, re, im);
+  return bra->dtype == QSV_C64 ? inner_t<float, false>(bra, ket, owner, re, im)
+                               : inner_t<double, false>(bra, ket, owner, re, im);
 }
 
 int qsv_observable_create(int n, qsv_observable** out) {
