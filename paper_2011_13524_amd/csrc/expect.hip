@@ -103,6 +103,10 @@ constexpr int kExpSplitTerms = 8;
 // QSV_EXPECT_GRID overrides
 constexpr int kExpGrid = 2048;
 
+// Workgroups that an expectation's launch aims at where the state has few tiles
+// (a pass's groups are split until there are this many).
+constexpr uint64_t kExpSplitGrid = 1024;
+
 // Persistent grid of the expectation and lambda passes: kExpGrid, or the
 // QSV_EXPECT_GRID override (tuning, and tests that give every workgroup a
 // ragged range of several tiles at small sizes).
@@ -381,6 +385,8 @@ __device__ __forceinline__ double exp_pairs(const cx<R>* tx, const cx<R>* ty, co
 // guards); 1: the tile has at least two amplitudes per thread, so every loop
 // below has a workgroup-uniform trip count; 2: the tile has exp_tile_bits<R>()
 // qubits (trip counts known at compile time).
+// gridDim.y passes run in one launch, each split over gridDim.z ranges of its
+// groups (workgroup b = x + gridDim.x (y + gridDim.y z) writes partial[b]).
 template <typename R, int MODE>
 __global__ void __launch_bounds__(kExpThreadsE)
     k_expect_tile(const R* __restrict__ psi, const ExpPassDev* __restrict__ passes, int pass_idx,
@@ -394,7 +400,9 @@ __global__ void __launch_bounds__(kExpThreadsE)
   __shared__ double red[NT / 64];
   __shared__ ExpTermLds et[kExpLdsTerms];
   cx<R>* t = reinterpret_cast<cx<R>*>(smem);
-  const ExpPassDev& P = passes[pass_idx];
+  const ExpPassDev& P = passes[pass_idx + int(blockIdx.y)];
+  const int grp0 = int(uint32_t(P.grp_count) * blockIdx.z / gridDim.z);
+  const int grps = int(uint32_t(P.grp_count) * (blockIdx.z + 1) / gridDim.z) - grp0;
   const uint32_t TS = LT > 0 ? (1u << LT) : (1u << P.L);
   const uint32_t tid = threadIdx.x;
   ExpTileStream<R, NT, LT> io(P);
@@ -409,10 +417,10 @@ __global__ void __launch_bounds__(kExpThreadsE)
       tr.base = tr.next_base();
       io.fetch(psi, tr.base);
     }
-    const ExpGroupDev* gd = groups + P.grp_begin;
+    const ExpGroupDev* gd = groups + P.grp_begin + grp0;
     ExpGroupHead head(gd[0]);
     __syncthreads();  // tile (and, first time, the group table) in LDS
-    for (int left = P.grp_count; left > 0; --left, ++gd) {
+    for (int left = grps; left > 0; --left, ++gd) {
       const ExpGroup G = head.fold(base, gd);
       const uint32_t kind = head.kind;
       head = ExpGroupHead(gd[1]);  // (after a pass's last record: the next pass's first, or the spare)
@@ -493,7 +501,8 @@ __global__ void __launch_bounds__(kExpThreadsE)
   if (tid == 0) {
     double r = 0.0;
     for (int w = 0; w < NT / 64; ++w) r += red[w];
-    partial[blockIdx.x] = accumulate ? partial[blockIdx.x] + r : r;
+    double* p = partial + blockIdx.x + size_t(gridDim.x) * (blockIdx.y + gridDim.y * blockIdx.z);
+    *p = accumulate ? *p + r : r;
   }
 }
 
@@ -981,6 +990,78 @@ int upload_exp_plan(ExpPlan* p, int device) {
   return QSV_OK;
 }
 
+constexpr size_t kNoAllocBytes = size_t(1) << 20;
+
+size_t al256(size_t x) { return (x + 255) / 256 * 256; }
+
+// Launch shape of an expectation: all passes in one launch (merged), each split
+// over nz ranges of its groups where the passes' tiles leave the chip idle
+// (every range reads its tiles again). The value depends on the shape in its
+// last bits, so the no-allocation variant takes the same one: merged only while
+// the partials fit its scratch beside the tables (else one launch per pass,
+// adding to one partial per workgroup).
+// Measured, 250 strings, one launch per pass against merged: complex64 12 qubits
+// 175 and 42 us, 16 qubits 171 and 68, 20 qubits 192 and 106, 24 qubits 937 and
+// 879, 30 qubits 33.7 and 32.0 ms; complex128 19 qubits 169 and 80 us.
+struct ExpShape {
+  uint64_t tiles, grid, parts;
+  unsigned np, nz;
+  bool merged;
+};
+
+size_t exp_table_bytes(const ExpPlan* pl) {
+  return al256(pl->passes.size() * sizeof(ExpPassDev)) + al256(pl->groups.size() * sizeof(ExpGroupDev)) +
+         al256(pl->terms.size() * sizeof(ExpTermDev)) + al256(pl->wide_terms.size() * sizeof(ExpTermDev));
+}
+
+ExpShape exp_shape(const ExpPlan* pl, int n) {
+  ExpShape h{};
+  h.tiles = dim(n - pl->L);
+  h.grid = std::min<uint64_t>(h.tiles, exp_grid_max());
+  h.np = unsigned(pl->passes.size());
+  h.nz = 1;
+  h.parts = h.grid;
+  if (h.np == 0) return h;
+  int most = 1;
+  for (const ExpPassDev& P : pl->passes) most = std::max(most, P.grp_count);
+  h.nz = unsigned(std::min<uint64_t>(uint64_t(most), std::max<uint64_t>(1, kExpSplitGrid / (h.grid * h.np))));
+  const uint64_t parts = h.grid * h.np * h.nz;
+  h.merged = al256((size_t(parts) + 1) * sizeof(double)) + exp_table_bytes(pl) <= kNoAllocBytes;
+  if (h.merged) h.parts = parts;
+  else h.nz = 1;
+  return h;
+}
+
+// Enqueues the passes, the wide groups and the sum (into part[h.parts]).
+template <typename R>
+int exp_launch(const ExpPlan* pl, const ExpShape& h, int n, const R* psi, const ExpPassDev* pd, const ExpGroupDev* gd,
+               const ExpTermDev* td, const ExpTermDev* wt, double* part, hipStream_t st) {
+  const size_t lds = (size_t(1) << pl->L) * sizeof(cx<R>);
+  // kernel variant: tile of the default size (compile-time trip counts), at
+  // least two amplitudes per thread, or any size
+  const int mode = pl->L == exp_tile_bits<R>() ? 2 : ((size_t(1) << pl->L) >= size_t(2 * kExpThreadsE) ? 1 : 0);
+  const auto kfn = mode == 2 ? &k_expect_tile<R, 2> : (mode == 1 ? &k_expect_tile<R, 1> : &k_expect_tile<R, 0>);
+  QSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    int(lds)));
+  const unsigned launches = h.merged ? 1u : h.np;
+  for (unsigned pi = 0; pi < launches; ++pi) {
+    ProfScope ps("expect", double(sizeof(cx<R>)) * double(dim(n)) * (h.merged ? h.np : 1u), st);
+    hipLaunchKernelGGL(kfn, dim3(unsigned(h.grid), h.merged ? h.np : 1u, h.nz), dim3(kExpThreadsE), lds, st, psi, pd,
+                       int(pi), gd, td, part, pi > 0 ? 1 : 0, h.tiles);
+    QSV_HIP_CHECK(hipGetLastError());
+  }
+  for (size_t wi = 0; wi < pl->wide.size(); ++wi) {
+    ProfScope ps("expect_wide", double(sizeof(cx<R>)) * double(dim(n)), st);
+    const ExpWide& w = pl->wide[wi];
+    hipLaunchKernelGGL((k_expect_wide<R>), dim3(unsigned(h.grid)), dim3(kExpThreadsE), 0, st, psi, w.flip, w.hbit,
+                       wt + w.term_begin, w.term_count, dim(n - 1), part, pl->passes.empty() && wi == 0 ? 0 : 1);
+    QSV_HIP_CHECK(hipGetLastError());
+  }
+  hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(kExpThreads), 0, st, part, h.parts, part + h.parts);
+  QSV_HIP_CHECK(hipGetLastError());
+  return QSV_OK;
+}
+
 template <typename R>
 int expect_tiled_t(qsv_state* s, qsv_observable* o, double* out) {
   ExpPlan*& pl = o->exp_plan[s->dtype];
@@ -991,48 +1072,15 @@ int expect_tiled_t(qsv_state* s, qsv_observable* o, double* out) {
   }
   int rc = upload_exp_plan(pl, s->device);
   if (rc) return rc;
-  const uint64_t tiles = dim(s->n - pl->L);
-  const uint64_t grid = std::min<uint64_t>(tiles, exp_grid_max());
-  if ((rc = ensure_reduce_scratch(s, size_t(grid) + 1))) return rc;
-  const size_t lds = (size_t(1) << pl->L) * sizeof(cx<R>);
-  // kernel variant: tile of the default size (compile-time trip counts), at
-  // least two amplitudes per thread, or any size
-  const int mode = pl->L == exp_tile_bits<R>() ? 2 : ((size_t(1) << pl->L) >= size_t(2 * kExpThreadsE) ? 1 : 0);
-  const void* kfn = mode == 2   ? reinterpret_cast<const void*>(&k_expect_tile<R, 2>)
-                    : mode == 1 ? reinterpret_cast<const void*>(&k_expect_tile<R, 1>)
-                                : reinterpret_cast<const void*>(&k_expect_tile<R, 0>);
-  QSV_HIP_CHECK(hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+  const ExpShape h = exp_shape(pl, s->n);
+  if ((rc = ensure_reduce_scratch(s, size_t(h.parts) + 1))) return rc;
   char* d = static_cast<char*>(pl->dev);
-  for (size_t pi = 0; pi < pl->passes.size(); ++pi) {
-    ProfScope ps("expect", double(sizeof(cx<R>)) * double(dim(s->n)), s->stream);
-    const auto* pd = reinterpret_cast<const ExpPassDev*>(d);
-    const auto* gd = reinterpret_cast<const ExpGroupDev*>(d + pl->off_groups);
-    const auto* td = reinterpret_cast<const ExpTermDev*>(d + pl->off_terms);
-    const R* psi = static_cast<const R*>(s->ptr);
-    if (mode == 2)
-      hipLaunchKernelGGL((k_expect_tile<R, 2>), dim3(unsigned(grid)), dim3(kExpThreadsE), lds, s->stream, psi,
-                         pd, int(pi), gd, td, s->red, pi > 0 ? 1 : 0, tiles);
-    else if (mode == 1)
-      hipLaunchKernelGGL((k_expect_tile<R, 1>), dim3(unsigned(grid)), dim3(kExpThreadsE), lds, s->stream, psi,
-                         pd, int(pi), gd, td, s->red, pi > 0 ? 1 : 0, tiles);
-    else
-      hipLaunchKernelGGL((k_expect_tile<R, 0>), dim3(unsigned(grid)), dim3(kExpThreadsE), lds, s->stream, psi,
-                         pd, int(pi), gd, td, s->red, pi > 0 ? 1 : 0, tiles);
-    QSV_HIP_CHECK(hipGetLastError());
-  }
-  const auto* wt = reinterpret_cast<const ExpTermDev*>(d + pl->off_wide);
-  for (size_t wi = 0; wi < pl->wide.size(); ++wi) {
-    ProfScope ps("expect_wide", double(sizeof(cx<R>)) * double(dim(s->n)), s->stream);
-    const ExpWide& w = pl->wide[wi];
-    hipLaunchKernelGGL((k_expect_wide<R>), dim3(unsigned(grid)), dim3(kExpThreadsE), 0, s->stream,
-                       static_cast<const R*>(s->ptr), w.flip, w.hbit, wt + w.term_begin, w.term_count,
-                       dim(s->n - 1), s->red, pl->passes.empty() && wi == 0 ? 0 : 1);
-    QSV_HIP_CHECK(hipGetLastError());
-  }
-  hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(kExpThreads), 0, s->stream, s->red, grid, s->red + grid);
-  QSV_HIP_CHECK(hipGetLastError());
-  QSV_HIP_CHECK(hipMemcpyAsync(s->red_host, s->red + grid, sizeof(double), hipMemcpyDeviceToHost,
-                               s->stream));
+  rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), reinterpret_cast<const ExpPassDev*>(d),
+                     reinterpret_cast<const ExpGroupDev*>(d + pl->off_groups),
+                     reinterpret_cast<const ExpTermDev*>(d + pl->off_terms),
+                     reinterpret_cast<const ExpTermDev*>(d + pl->off_wide), s->red, s->stream);
+  if (rc) return rc;
+  QSV_HIP_CHECK(hipMemcpyAsync(s->red_host, s->red + h.parts, sizeof(double), hipMemcpyDeviceToHost, s->stream));
   QSV_HIP_CHECK(hipStreamSynchronize(s->stream));
   *out = s->red_host[0];
   return QSV_OK;
@@ -1101,7 +1149,6 @@ int apply_obs_tiled_t(const qsv_state* in, qsv_observable* o, qsv_state* out) {
 // array; its address on a device is taken once (hipGetSymbolAddress, with
 // that device current) and only that address is used from the host. Calls on
 // one device share the array: calls that overlap on one device race.
-constexpr size_t kNoAllocBytes = size_t(1) << 20;
 static __device__ __align__(256) char scratch[kNoAllocBytes];
 
 constexpr int kNoAllocMaxDevices = 64;
@@ -1135,15 +1182,13 @@ int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
     *out = 0.0;
     return QSV_OK;
   }
-  const uint64_t tiles = dim(s->n - pl->L);
-  const uint64_t grid = std::min<uint64_t>(tiles, exp_grid_max());
-  // scratch layout: partials[grid + 1] | passes | groups | terms (256-byte aligned)
-  auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t o_pass = al((size_t(grid) + 1) * sizeof(double));
-  const size_t o_grp = o_pass + al(pl->passes.size() * sizeof(ExpPassDev));
-  const size_t o_term = o_grp + al(pl->groups.size() * sizeof(ExpGroupDev));
-  const size_t o_wide = o_term + al(pl->terms.size() * sizeof(ExpTermDev));
-  const size_t need = o_wide + al(pl->wide_terms.size() * sizeof(ExpTermDev));
+  const ExpShape h = exp_shape(pl, s->n);
+  // scratch layout: partials[parts + 1] | passes | groups | terms (256-byte aligned)
+  const size_t o_pass = al256((size_t(h.parts) + 1) * sizeof(double));
+  const size_t o_grp = o_pass + al256(pl->passes.size() * sizeof(ExpPassDev));
+  const size_t o_term = o_grp + al256(pl->groups.size() * sizeof(ExpGroupDev));
+  const size_t o_wide = o_term + al256(pl->terms.size() * sizeof(ExpTermDev));
+  const size_t need = o_pass + exp_table_bytes(pl);
   if (need > kNoAllocBytes)
     return fail(QSV_ERANGE, "observable needs %zu bytes of device scratch; the no-allocation limit is %zu",
                 need, kNoAllocBytes);
@@ -1164,42 +1209,14 @@ int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
     QSV_HIP_CHECK(hipMemcpyAsync(d + o_wide, pl->wide_terms.data(), pl->wide_terms.size() * sizeof(ExpTermDev),
                                  hipMemcpyHostToDevice, st));
   double* part = reinterpret_cast<double*>(d);
-  const auto* pd = reinterpret_cast<const ExpPassDev*>(d + o_pass);
-  const auto* gd = reinterpret_cast<const ExpGroupDev*>(d + o_grp);
-  const auto* td = reinterpret_cast<const ExpTermDev*>(d + o_term);
-  const size_t lds = (size_t(1) << pl->L) * sizeof(cx<R>);
-  const int mode = pl->L == exp_tile_bits<R>() ? 2 : ((size_t(1) << pl->L) >= size_t(2 * kExpThreadsE) ? 1 : 0);
-  const void* kfn = mode == 2   ? reinterpret_cast<const void*>(&k_expect_tile<R, 2>)
-                    : mode == 1 ? reinterpret_cast<const void*>(&k_expect_tile<R, 1>)
-                                : reinterpret_cast<const void*>(&k_expect_tile<R, 0>);
-  QSV_HIP_CHECK(hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-  const R* psi = static_cast<const R*>(s->ptr);
-  // the first pass writes every partial (accumulate = 0): nothing left from an
-  // earlier call is read
-  for (size_t pi = 0; pi < pl->passes.size(); ++pi) {
-    if (mode == 2)
-      hipLaunchKernelGGL((k_expect_tile<R, 2>), dim3(unsigned(grid)), dim3(kExpThreadsE), lds, st, psi, pd,
-                         int(pi), gd, td, part, pi > 0 ? 1 : 0, tiles);
-    else if (mode == 1)
-      hipLaunchKernelGGL((k_expect_tile<R, 1>), dim3(unsigned(grid)), dim3(kExpThreadsE), lds, st, psi, pd,
-                         int(pi), gd, td, part, pi > 0 ? 1 : 0, tiles);
-    else
-      hipLaunchKernelGGL((k_expect_tile<R, 0>), dim3(unsigned(grid)), dim3(kExpThreadsE), lds, st, psi, pd,
-                         int(pi), gd, td, part, pi > 0 ? 1 : 0, tiles);
-    QSV_HIP_CHECK(hipGetLastError());
-  }
-  const auto* wt = reinterpret_cast<const ExpTermDev*>(d + o_wide);
-  for (size_t wi = 0; wi < pl->wide.size(); ++wi) {
-    const ExpWide& w = pl->wide[wi];
-    hipLaunchKernelGGL((k_expect_wide<R>), dim3(unsigned(grid)), dim3(kExpThreadsE), 0, st, psi, w.flip, w.hbit,
-                       wt + w.term_begin, w.term_count, dim(s->n - 1), part,
-                       pl->passes.empty() && wi == 0 ? 0 : 1);
-    QSV_HIP_CHECK(hipGetLastError());
-  }
-  hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(kExpThreads), 0, st, part, grid, part + grid);
-  QSV_HIP_CHECK(hipGetLastError());
+  // (the first launch writes every partial that is summed: nothing left from an
+  // earlier call is read)
+  rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), reinterpret_cast<const ExpPassDev*>(d + o_pass),
+                     reinterpret_cast<const ExpGroupDev*>(d + o_grp), reinterpret_cast<const ExpTermDev*>(d + o_term),
+                     reinterpret_cast<const ExpTermDev*>(d + o_wide), part, st);
+  if (rc) return rc;
   double v = 0.0;
-  QSV_HIP_CHECK(hipMemcpyAsync(&v, part + grid, sizeof(double), hipMemcpyDeviceToHost, st));
+  QSV_HIP_CHECK(hipMemcpyAsync(&v, part + h.parts, sizeof(double), hipMemcpyDeviceToHost, st));
   QSV_HIP_CHECK(hipStreamSynchronize(st));
   *out = v;
   return QSV_OK;
