@@ -771,8 +771,17 @@ static TileRegFn<R> tile_reg_km(int km) {
                    : &k_tile_reg<R, RB, 5, TB>;
 }
 
+template <typename R, int TB>
+static TileRegFn<R> tile_reg_small(int km) {
+  return km == 0 ? &k_tile_reg<R, 3, 0, TB> : (km <= 3 ? &k_tile_reg<R, 3, 3, TB> : &k_tile_reg<R, 3, 5, TB>);
+}
 template <typename R>
 static TileRegFn<R> tile_reg_fn(int rb, int tb, int km) {
+  if (rb == 3) {  // states of one tile
+    if (tb == 6) return tile_reg_small<R, 6>(km);
+    if (tb == 7) return tile_reg_small<R, 7>(km);
+    return tile_reg_small<R, 8>(km);
+  }
   if constexpr (sizeof(R) == 4) {
     if (tb == 9) return tile_reg_km<R, 4, 9>(km);
     if (tb == 8 && rb == 5) return tile_reg_km<R, 5, 8>(km);
@@ -910,8 +919,15 @@ static int plan_create(const qsv_circuit* c, qsv_dtype dtype, int max_k, int til
   if ((dtype == QSV_C128 || max_k > 3) && TB == 9) TB = kRegThreadBits;
   // register bits: the rest of the tile; instantiated shapes (register bits,
   // thread bits): complex64 (4, 9), (4, 8), (5, 8), (4, 7); complex128 (4, 8), (4, 7)
+  // states of 9 to 11 qubits, one tile: three register bits, so that as many
+  // wavefronts as the tile allows share its chain of gates (the LDS kernel, which
+  // keeps 8 qubits and fewer, takes a barrier per block). Measured, 8-layer
+  // ansatz, LDS kernel against registers: complex128 9 qubits 102 and 45 us, 10
+  // qubits 149 and 53, 11 qubits 246 and 56; complex64 95 and 43, 139 and 49, 226
+  // and 57 us.
+  if (n < 12 && L == n && L >= 9 && TB == kRegThreadBits) TB = L - 3;
   const int RB = L - TB;
-  const bool rb_ok = RB == 4 || (dtype == QSV_C64 && RB == 5 && TB == 8);
+  const bool rb_ok = RB == 4 || (RB == 3 && L == n && TB >= 6) || (dtype == QSV_C64 && RB == 5 && TB == 8);
   p->thread_bits = TB;
   p->reg_bits = (rb_ok && n >= L) ? RB : 0;
   p->circ_copy = *c;

@@ -133,3 +133,23 @@ def test_gradients_around_the_smallest_full_tile(dt, n):
         slots = sorted({0, 1, npar // 2, npar - 1})
         ref = O.param_shift_grad(n, gates, theta, obs, slots=slots)
         assert np.max(np.abs(gr[slots] - ref)) <= RED_TOL[dt] * scale
+
+
+@pytest.mark.parametrize("dt", ["c128", "c64"])
+@pytest.mark.parametrize("n", [8, 9, 10, 11, 12])
+@pytest.mark.parametrize("max_k", [2, 3, 5])
+def test_states_of_one_tile(dt, n, max_k):
+    # three register bits below 12 qubits; blocks of up to max_k qubits too
+    g, _ = phase_circuit(n, 90, 40 + n)
+    rng = np.random.default_rng(n)
+    for k in (2, 3):
+        g.insert(30 * k, {"op": "dense", "q": [int(x) for x in rng.permutation(n)[:k]], "mat": W.haar_unitary(rng, 1 << k)})
+    v = rng.standard_normal(1 << n) + 1j * rng.standard_normal(1 << n)
+    v /= np.linalg.norm(v)
+    s = State(n, dt)
+    s.load(v)
+    ref = v.astype(np.complex64).astype(np.complex128) if dt == "c64" else v.copy()
+    apply_fused(s, Plan(Circuit.from_records(n, g), dt, max_k=max_k))
+    for rec in g:
+        O.apply_gate(ref, rec, None)
+    assert np.max(np.abs(s.store() - ref)) <= AMP_TOL[dt]
