@@ -165,7 +165,7 @@ int qsv_marginal_probability(const qsv_state* s, const int* values, double* out)
  * indices, out[i] = the smallest x with C(x) > u[i] * C(2^n - 1), C the
  * inclusive cumulative sum of |psi|^2 in FP64 (unnormalised states are
  * sampled from |psi|^2 / <psi|psi>). An index of probability zero is never
- * returned. The table takes 2^n FP64 entries (8 bytes per amplitude) plus
+ * returned. The table takes 2^(n-4) FP64 entries (half a byte per amplitude) plus
  * 2^(n-12) chunk totals and 16 bytes per sample, carved from the state's work
  * buffer: allocated on the first call (or grown), kept for later calls and
  * freed with the state. The call synchronises. count == 0 only builds the
