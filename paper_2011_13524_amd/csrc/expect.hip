@@ -43,6 +43,8 @@ constexpr int kExpMaxGlobal = 40;
 struct ExpPassDev {
   int L, b, nh, ng;
   int grp_begin, grp_count;
+  int single_count;            // the first records of the pass: those of one term
+  int span_begin, span_count;  // the same in spans (full tiles)
   int hq[kExpMaxHigh];
   int gpos[kExpMaxGlobal];
 };
@@ -70,6 +72,29 @@ struct ExpGroupDev {
   // the float +-1.0); for lf == 0 the step part of x is k * kExpThreadsE
   uint32_t sgn[kExpSteps];
 };
+
+// A span: the records whose flip masks lie in the linear span of `dim` basis
+// masks (2^dim amplitudes per thread of a full tile: 4 complex64, 3 complex128).
+// Every thread reads one coset into registers -- its representative XOR off[e],
+// byte offsets -- and evaluates all of the records there: a tile is read from LDS
+// once per span instead of once per record.
+struct ExpSpanDev {
+  uint32_t off[16];
+  int pv[4];  // pivot bits, ascending (representatives have them clear)
+  int rec_begin, rec_count;
+};
+
+// A record of a span.
+struct alignas(16) ExpRecDev {
+  uint32_t sgn[8];  // sign of the k-th pair's first element (flip mask 0: of element k), as in ExpGroupDev
+  uint32_t s8;      // flip mask 0: bit 31, sign of the elements from 8 on against those before
+  uint32_t zl;      // sign mask on local qubits
+  uint32_t code;    // flip mask as a combination of the basis; bit 4: imaginary
+  uint32_t pad;
+  double c;         // factor of the sum over pairs (flip mask: 2 re or -2 im; none: re)
+  uint64_t zg;      // sign mask on non-local qubits
+};
+constexpr int kSpanRecs = 512;  // records of a pass, at most (their factors for a tile sit in LDS)
 
 // Record kinds (set by the planner): one term with flip mask 0; several
 // terms with flip mask 0; one term with a flip mask and a real (REAL) or
@@ -129,11 +154,14 @@ struct ExpPlan {
   std::vector<ExpPassDev> passes;
   std::vector<ExpGroupDev> groups;
   std::vector<ExpTermDev> terms;
+  std::vector<ExpSpanDev> spans;  // (full tiles only)
+  std::vector<ExpRecDev> recs;
   std::vector<ExpWide> wide;
   std::vector<ExpTermDev> wide_terms;
-  void* dev = nullptr;  // passes | groups | terms | wide_terms
-  size_t off_groups = 0, off_terms = 0, off_wide = 0;
+  void* dev = nullptr;  // passes | groups | terms | wide_terms | spans | recs
+  size_t off_groups = 0, off_terms = 0, off_wide = 0, off_spans = 0, off_recs = 0;
   int device = -1;
+  bool spans_tried = false;
 };
 
 void free_exp_plan(ExpPlan* p) {
@@ -375,6 +403,53 @@ __device__ __forceinline__ double exp_pairs(const cx<R>* tx, const cx<R>* ty, co
   return xor_sign(sd, pt);  // the thread's part of the sign, common to every step
 }
 
+// A span's record of flip code F: its pairs (e, e ^ F), e with F's highest bit
+// clear, in registers; sums as in exp_pairs.
+template <typename R, int RB, int F, bool REAL>
+__device__ __forceinline__ double span_pairs(const cx<R>* v, const ExpRecDev& r) {
+  constexpr int H = F >= 8 ? 3 : (F >= 4 ? 2 : (F >= 2 ? 1 : 0));
+  R sw = R(0);
+#pragma unroll
+  for (int k = 0; k < (1 << (RB - 1)); ++k) {
+    const int e = ((k >> H) << (H + 1)) | (k & ((1 << H) - 1));
+    const R p = pair_product<R, REAL>(v[e], v[e ^ F]);
+    if constexpr (sizeof(R) == 4) sw = fmaf(__uint_as_float(r.sgn[k]), p, sw);
+    else sw += xor_sign(p, r.sgn[k]);
+  }
+  return double(sw);
+}
+
+template <typename R, int RB>
+__device__ __forceinline__ double span_record(const cx<R>* v, const ExpRecDev& r) {
+#define QSV_SPAN(F)                                             \
+  case F: return span_pairs<R, RB, F, true>(v, r);              \
+  case F + 16: return span_pairs<R, RB, F, false>(v, r);
+#define QSV_SPAN_HI(F)                                          \
+  case F:                                                       \
+    if constexpr (RB == 4) return span_pairs<R, RB, F, true>(v, r); \
+    break;                                                      \
+  case F + 16:                                                  \
+    if constexpr (RB == 4) return span_pairs<R, RB, F, false>(v, r); \
+    break;
+  switch (r.code) {
+    QSV_SPAN(1) QSV_SPAN(2) QSV_SPAN(3) QSV_SPAN(4) QSV_SPAN(5) QSV_SPAN(6) QSV_SPAN(7)
+    QSV_SPAN_HI(8) QSV_SPAN_HI(9) QSV_SPAN_HI(10) QSV_SPAN_HI(11)
+    QSV_SPAN_HI(12) QSV_SPAN_HI(13) QSV_SPAN_HI(14) QSV_SPAN_HI(15)
+    default: break;
+  }
+#undef QSV_SPAN
+#undef QSV_SPAN_HI
+  // flip mask 0: +-|psi_x|^2, summed in FP64
+  double lo = 0.0, hi = 0.0;
+#pragma unroll
+  for (int e = 0; e < (1 << RB); ++e) {
+    const double w = double(pair_product<R, true>(v[e], v[e]));
+    if (e < 8) lo += xor_sign(w, r.sgn[e & 7] & 0x80000000u);
+    else hi += xor_sign(w, r.sgn[e & 7] & 0x80000000u);
+  }
+  return lo + xor_sign(hi, r.s8);
+}
+
 // <psi|O|psi> over the tiles of one pass. Sums over threads and tiles are
 // FP64; single-term groups form their products in the amplitude precision,
 // and a flip group also sums each thread's 8 pairs per tile in it
@@ -385,24 +460,46 @@ __device__ __forceinline__ double exp_pairs(const cx<R>* tx, const cx<R>* ty, co
 // guards); 1: the tile has at least two amplitudes per thread, so every loop
 // below has a workgroup-uniform trip count; 2: the tile has exp_tile_bits<R>()
 // qubits (trip counts known at compile time).
+// 3: as 2, with the single-term records evaluated in spans. Bound by instruction
+// issue (200 strings of weight 4 at 30 qubits complex64: 45 vector and 34 scalar
+// instructions per record and wavefront, vector units 55% busy, four wavefronts
+// per SIMD): 32.0 ms reading LDS for each record, 27.5 ms in spans; complex128, 250
+// strings, 26 qubits 4.38 and 3.91 ms. The records' factors with the tile's
+// signs come from LDS (formed by one lane each; on the scalar unit 31.3 ms), and
+// records are read where they are used (two at a time 28.2 ms).
 // gridDim.y passes run in one launch, each split over gridDim.z ranges of its
 // groups (workgroup b = x + gridDim.x (y + gridDim.y z) writes partial[b]).
 template <typename R, int MODE>
 __global__ void __launch_bounds__(kExpThreadsE)
     k_expect_tile(const R* __restrict__ psi, const ExpPassDev* __restrict__ passes, int pass_idx,
                   const ExpGroupDev* __restrict__ groups, const ExpTermDev* __restrict__ terms,
+                  const ExpSpanDev* __restrict__ spans, const ExpRecDev* __restrict__ recs,
                   double* __restrict__ partial, int accumulate, uint64_t ntiles) {
   constexpr int NT = kExpThreadsE;
   constexpr int NA = kExpTileMax / NT;  // amplitudes per thread, at most
   constexpr bool FULL = MODE >= 1;
-  constexpr int LT = MODE == 2 ? exp_tile_bits<R>() : 0;
+  constexpr int LT = MODE >= 2 ? exp_tile_bits<R>() : 0;
+  constexpr bool SPANS = MODE == 3;
   extern __shared__ __align__(16) char smem[];
   __shared__ double red[NT / 64];
   __shared__ ExpTermLds et[kExpLdsTerms];
   cx<R>* t = reinterpret_cast<cx<R>*>(smem);
   const ExpPassDev& P = passes[pass_idx + int(blockIdx.y)];
-  const int grp0 = int(uint32_t(P.grp_count) * blockIdx.z / gridDim.z);
-  const int grps = int(uint32_t(P.grp_count) * (blockIdx.z + 1) / gridDim.z) - grp0;
+  // this workgroup's records: a range of the pass's groups, or of its spans and
+  // then the groups that are in none
+  const uint32_t items = uint32_t(SPANS ? P.span_count + P.grp_count - P.single_count : P.grp_count);
+  int grp0 = int(items * blockIdx.z / gridDim.z), grp1 = int(items * (blockIdx.z + 1) / gridDim.z);
+  int span0 = 0, span1 = 0;
+  if (SPANS) {
+    span0 = P.span_begin + min(grp0, P.span_count);
+    span1 = P.span_begin + min(grp1, P.span_count);
+    grp0 = max(grp0 - P.span_count, 0) + P.single_count;
+    grp1 = max(grp1 - P.span_count, 0) + P.single_count;
+  }
+  const int grps = grp1 - grp0;
+  __shared__ double cs[SPANS ? kSpanRecs : 1];  // the records' factors with the tile's signs
+  const int rec0 = SPANS && span0 < span1 ? spans[span0].rec_begin : 0;
+  const int nrec = SPANS && span0 < span1 ? spans[span1 - 1].rec_begin + spans[span1 - 1].rec_count - rec0 : 0;
   const uint32_t TS = LT > 0 ? (1u << LT) : (1u << P.L);
   const uint32_t tid = threadIdx.x;
   ExpTileStream<R, NT, LT> io(P);
@@ -413,6 +510,10 @@ __global__ void __launch_bounds__(kExpThreadsE)
     const uint64_t base = tr.base;
     __syncthreads();  // previous tile consumed
     io.to_lds(t);
+    if (SPANS && int(tid) < nrec) {
+      const ExpRecDev& r = recs[rec0 + int(tid)];
+      cs[tid] = xor_sign(r.c, uint32_t(__popcll(base & r.zg) & 1) << 31);
+    }
     if (tr.g + 1 < tr.end) {
       tr.base = tr.next_base();
       io.fetch(psi, tr.base);
@@ -420,12 +521,35 @@ __global__ void __launch_bounds__(kExpThreadsE)
     const ExpGroupDev* gd = groups + P.grp_begin + grp0;
     ExpGroupHead head(gd[0]);
     __syncthreads();  // tile (and, first time, the group table) in LDS
+    if constexpr (SPANS) {
+      constexpr int RB = exp_tile_bits<R>() - 9;  // 512 threads
+      for (int si = span0; si < span1; ++si) {
+        const ExpSpanDev& S = spans[si];
+        uint32_t rep = tid;
+#pragma unroll
+        for (int j = 0; j < RB; ++j) rep = ins0(rep, S.pv[j]);
+        cx<R> v[1 << RB];
+#pragma unroll
+        for (int e = 0; e < (1 << RB); ++e)
+          v[e] = *reinterpret_cast<const cx<R>*>(smem + ((rep * uint32_t(sizeof(cx<R>))) ^ S.off[e]));
+        for (int ri = S.rec_begin; ri < S.rec_begin + S.rec_count; ++ri) {
+          const ExpRecDev& r = recs[ri];
+          const double c = cs[ri - rec0];
+          // (the products of all codes are loop-invariant: formed ahead of the
+          // loop they would take far more registers than there are)
+#pragma unroll
+          for (int e = 0; e < (1 << RB); ++e) asm volatile("" : "+v"(v[e].re), "+v"(v[e].im));
+          const uint32_t pt = uint32_t(__popc(rep & r.zl)) << 31;
+          acc += c * xor_sign(span_record<R, RB>(v, r), pt);
+        }
+      }
+    }
     for (int left = grps; left > 0; --left, ++gd) {
       const ExpGroup G = head.fold(base, gd);
       const uint32_t kind = head.kind;
       head = ExpGroupHead(gd[1]);  // (after a pass's last record: the next pass's first, or the spare)
       const int nt = G.term_count;
-      if (kind == kExpFlipRe || kind == kExpFlipIm) {
+      if (!SPANS && (kind == kExpFlipRe || kind == kExpFlipIm)) {
         // one term (the common case for random strings). A Hermitian term's
         // coefficient alpha i^nY is real (nY even) or imaginary (nY odd):
         // only Re or Im of w = conj(psi[y]) psi[x] counts
@@ -444,7 +568,7 @@ __global__ void __launch_bounds__(kExpThreadsE)
         exp_stage_terms(terms, G, base, et);
         __syncthreads();
       }
-      if (kind == kExpZ1) {
+      if (!SPANS && kind == kExpZ1) {
         // sum of +-|psi_x|^2: thread part of the sign once, uniform part per step
         uint32_t pt = uint32_t(__popc(tid & G.zl) & 1) << 31;
         double sum = 0.0;
@@ -836,6 +960,107 @@ void rebalance_passes(const std::vector<Group>& groups, const std::vector<uint64
   }
 }
 
+// The single-term records of a pass in spans of `dim` basis masks: each span is
+// grown from a seed mask by the mask after which most records lie inside, and the
+// best of kSpanSeeds seeds is kept. With all masks reduced by the basis so far,
+// the records that a new basis mask c brings in are those reduced to c.
+constexpr size_t kSpanSeeds = 4;
+
+struct SpanBasis {
+  int dim = 0;
+  uint32_t b[4];  // reduced: each has its highest bit (its pivot) alone
+  uint32_t reduce(uint32_t m) const {
+    for (int j = 0; j < dim; ++j)
+      if (m >> (31 - __builtin_clz(b[j])) & 1) m ^= b[j];
+    return m;
+  }
+  void add(uint32_t m) {  // m reduced, not 0
+    const int p = 31 - __builtin_clz(m);
+    for (int j = 0; j < dim; ++j)
+      if (b[j] >> p & 1) b[j] ^= m;
+    b[dim++] = m;
+  }
+};
+
+void build_spans(ExpPlan* p, ExpPassDev& d, int dim, bool c64) {
+  const ExpGroupDev* g = p->groups.data() + d.grp_begin;
+  const size_t S = c64 ? 8 : 16;  // bytes per amplitude
+  std::vector<int> left;
+  for (int i = 0; i < d.single_count; ++i) left.push_back(i);
+  d.span_begin = int(p->spans.size());
+  while (!left.empty()) {
+    SpanBasis best;
+    int best_w = -1;
+    std::vector<uint32_t> red, run;
+    size_t seeds = 0;
+    for (size_t a = 0; a < left.size() && seeds < kSpanSeeds; ++a) {
+      uint32_t add = g[left[a]].lf;
+      if (add == 0) continue;
+      ++seeds;
+      SpanBasis B;
+      red.clear();
+      for (int i : left) red.push_back(g[i].lf);
+      for (;;) {
+        B.add(add);
+        const int pv = 31 - __builtin_clz(add);
+        for (uint32_t& m : red)
+          if (m >> pv & 1) m ^= add;
+        if (B.dim == dim) break;
+        run = red;
+        std::sort(run.begin(), run.end());
+        int most = 0;
+        for (size_t i = 0, j = 0; i < run.size(); i = j) {
+          while (j < run.size() && run[j] == run[i]) ++j;
+          if (run[i] && int(j - i) > most) {
+            most = int(j - i);
+            add = run[i];
+          }
+        }
+        if (most == 0) break;
+      }
+      const int w = int(std::count(red.begin(), red.end(), 0u));
+      if (w > best_w) {
+        best_w = w;
+        best = B;
+      }
+    }
+    for (int q = d.L - 1; best.dim < dim; --q)  // (few masks: any other directions)
+      if (const uint32_t m = best.reduce(1u << q)) best.add(m);
+    std::sort(best.b, best.b + dim);  // pivots ascending
+    ExpSpanDev s{};
+    for (int e = 0; e < (1 << dim); ++e)
+      for (int j = 0; j < dim; ++j)
+        if (e >> j & 1) s.off[e] ^= best.b[j] * uint32_t(S);
+    for (int j = 0; j < dim; ++j) s.pv[j] = 31 - __builtin_clz(best.b[j]);
+    s.rec_begin = int(p->recs.size());
+    std::vector<int> rest;
+    for (int i : left) {
+      const ExpGroupDev& G = g[i];
+      if (best.reduce(G.lf)) {
+        rest.push_back(i);
+        continue;
+      }
+      ExpRecDev r{};
+      r.zg = G.zg;
+      r.zl = G.zl;
+      for (int j = 0; j < dim; ++j) r.code |= (G.lf >> s.pv[j] & 1) << j;
+      const int top = r.code ? 31 - __builtin_clz(r.code) : 0;
+      r.c = !r.code ? G.re : (G.kind == kExpFlipRe ? 2.0 * G.re : -2.0 * G.im);
+      for (int k = 0; k < 8; ++k) {
+        const int e = (r.code ? ((k >> top) << (top + 1)) | (k & ((1 << top) - 1)) : k) & ((1 << dim) - 1);
+        r.sgn[k] = uint32_t(__builtin_popcount(s.off[e] / uint32_t(S) & G.zl) & 1) << 31 | (c64 ? 0x3f800000u : 0u);
+      }
+      if (dim == 4) r.s8 = uint32_t(__builtin_popcount(best.b[3] & G.zl) & 1) << 31;
+      if (G.kind == kExpFlipIm) r.code |= 16;
+      p->recs.push_back(r);
+    }
+    s.rec_count = int(p->recs.size()) - s.rec_begin;
+    p->spans.push_back(s);
+    left.swap(rest);
+  }
+  d.span_count = int(p->spans.size()) - d.span_begin;
+}
+
 ExpPlan* build_exp_plan(const qsv_observable* o, qsv_dtype dt) {
   std::vector<Group> groups;
   std::vector<GTerm> terms;
@@ -958,12 +1183,27 @@ ExpPlan* build_exp_plan(const qsv_observable* o, qsv_dtype dt) {
       }
     }
     d.grp_count = int(p->groups.size()) - d.grp_begin;
+    d.single_count = int(std::stable_partition(p->groups.begin() + d.grp_begin, p->groups.end(),
+                                               [](const ExpGroupDev& g) { return g.term_count == 1; }) -
+                         (p->groups.begin() + d.grp_begin));
     p->passes.push_back(d);
   }
   // the kernels read each record's successor ahead of use: one spare record
   // after the last pass keeps that read inside the table
   if (!p->passes.empty()) p->groups.push_back(ExpGroupDev{});
   return p;
+}
+
+// The spans of a plan of full tiles (built for the first expectation; lambda
+// passes have no use for them).
+void ensure_spans(ExpPlan* p, bool c64) {
+  if (p->spans_tried) return;
+  p->spans_tried = true;
+  if (p->L != (c64 ? exp_tile_bits<float>() : exp_tile_bits<double>())) return;
+  for (const ExpPassDev& d : p->passes)
+    if (d.single_count > kSpanRecs) return;
+  for (ExpPassDev& d : p->passes) build_spans(p, d, p->L - 9, c64);
+  p->device = -1;  // (tables already uploaded are uploaded again, with them)
 }
 
 int upload_exp_plan(ExpPlan* p, int device) {
@@ -975,7 +1215,9 @@ int upload_exp_plan(ExpPlan* p, int device) {
   const size_t bsz = p->groups.size() * sizeof(ExpGroupDev);
   p->off_terms = (p->off_groups + bsz + 255) / 256 * 256;
   p->off_wide = (p->off_terms + p->terms.size() * sizeof(ExpTermDev) + 255) / 256 * 256;
-  const size_t total = p->off_wide + std::max<size_t>(1, p->wide_terms.size()) * sizeof(ExpTermDev);
+  p->off_spans = (p->off_wide + std::max<size_t>(1, p->wide_terms.size()) * sizeof(ExpTermDev) + 255) / 256 * 256;
+  p->off_recs = (p->off_spans + p->spans.size() * sizeof(ExpSpanDev) + 255) / 256 * 256;
+  const size_t total = p->off_recs + p->recs.size() * sizeof(ExpRecDev);
   if (hipMalloc(&p->dev, total) != hipSuccess) return fail(QSV_ENOMEM, "observable plan allocation failed");
   char* d = static_cast<char*>(p->dev);
   if (a) QSV_HIP_CHECK(hipMemcpy(d, p->passes.data(), a, hipMemcpyHostToDevice));
@@ -986,6 +1228,10 @@ int upload_exp_plan(ExpPlan* p, int device) {
   if (!p->wide_terms.empty())
     QSV_HIP_CHECK(hipMemcpy(d + p->off_wide, p->wide_terms.data(), p->wide_terms.size() * sizeof(ExpTermDev),
                             hipMemcpyHostToDevice));
+  if (!p->spans.empty()) {
+    QSV_HIP_CHECK(hipMemcpy(d + p->off_spans, p->spans.data(), p->spans.size() * sizeof(ExpSpanDev), hipMemcpyHostToDevice));
+    QSV_HIP_CHECK(hipMemcpy(d + p->off_recs, p->recs.data(), p->recs.size() * sizeof(ExpRecDev), hipMemcpyHostToDevice));
+  }
   p->device = device;
   return QSV_OK;
 }
@@ -994,8 +1240,8 @@ constexpr size_t kNoAllocBytes = size_t(1) << 20;
 
 size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 
-// Launch shape of an expectation: all passes in one launch (merged), each split
-// over nz ranges of its groups where the passes' tiles leave the chip idle
+// Launch shape of an expectation: all passes in one launch (merged, full tiles in
+// spans), each split over nz ranges of its spans and groups where the passes' tiles leave the chip idle
 // (every range reads its tiles again). The value depends on the shape in its
 // last bits, so the no-allocation variant takes the same one: merged only while
 // the partials fit its scratch beside the tables (else one launch per pass,
@@ -1014,6 +1260,10 @@ size_t exp_table_bytes(const ExpPlan* pl) {
          al256(pl->terms.size() * sizeof(ExpTermDev)) + al256(pl->wide_terms.size() * sizeof(ExpTermDev));
 }
 
+size_t exp_span_bytes(const ExpPlan* pl) {
+  return al256(pl->spans.size() * sizeof(ExpSpanDev)) + al256(pl->recs.size() * sizeof(ExpRecDev));
+}
+
 ExpShape exp_shape(const ExpPlan* pl, int n) {
   ExpShape h{};
   h.tiles = dim(n - pl->L);
@@ -1023,10 +1273,12 @@ ExpShape exp_shape(const ExpPlan* pl, int n) {
   h.parts = h.grid;
   if (h.np == 0) return h;
   int most = 1;
-  for (const ExpPassDev& P : pl->passes) most = std::max(most, P.grp_count);
+  const bool spans = !pl->spans.empty();
+  for (const ExpPassDev& P : pl->passes)
+    most = std::max(most, spans ? P.span_count + P.grp_count - P.single_count : P.grp_count);
   h.nz = unsigned(std::min<uint64_t>(uint64_t(most), std::max<uint64_t>(1, kExpSplitGrid / (h.grid * h.np))));
   const uint64_t parts = h.grid * h.np * h.nz;
-  h.merged = al256((size_t(parts) + 1) * sizeof(double)) + exp_table_bytes(pl) <= kNoAllocBytes;
+  h.merged = al256((size_t(parts) + 1) * sizeof(double)) + exp_table_bytes(pl) + exp_span_bytes(pl) <= kNoAllocBytes;
   if (h.merged) h.parts = parts;
   else h.nz = 1;
   return h;
@@ -1035,19 +1287,22 @@ ExpShape exp_shape(const ExpPlan* pl, int n) {
 // Enqueues the passes, the wide groups and the sum (into part[h.parts]).
 template <typename R>
 int exp_launch(const ExpPlan* pl, const ExpShape& h, int n, const R* psi, const ExpPassDev* pd, const ExpGroupDev* gd,
-               const ExpTermDev* td, const ExpTermDev* wt, double* part, hipStream_t st) {
+               const ExpTermDev* td, const ExpTermDev* wt, const ExpSpanDev* sd, const ExpRecDev* rd, double* part,
+               hipStream_t st) {
   const size_t lds = (size_t(1) << pl->L) * sizeof(cx<R>);
   // kernel variant: tile of the default size (compile-time trip counts), at
   // least two amplitudes per thread, or any size
   const int mode = pl->L == exp_tile_bits<R>() ? 2 : ((size_t(1) << pl->L) >= size_t(2 * kExpThreadsE) ? 1 : 0);
-  const auto kfn = mode == 2 ? &k_expect_tile<R, 2> : (mode == 1 ? &k_expect_tile<R, 1> : &k_expect_tile<R, 0>);
+  const auto kfn = h.merged && !pl->spans.empty() ? &k_expect_tile<R, 3>
+                   : mode == 2                    ? &k_expect_tile<R, 2>
+                                                  : (mode == 1 ? &k_expect_tile<R, 1> : &k_expect_tile<R, 0>);
   QSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     int(lds)));
   const unsigned launches = h.merged ? 1u : h.np;
   for (unsigned pi = 0; pi < launches; ++pi) {
     ProfScope ps("expect", double(sizeof(cx<R>)) * double(dim(n)) * (h.merged ? h.np : 1u), st);
     hipLaunchKernelGGL(kfn, dim3(unsigned(h.grid), h.merged ? h.np : 1u, h.nz), dim3(kExpThreadsE), lds, st, psi, pd,
-                       int(pi), gd, td, part, pi > 0 ? 1 : 0, h.tiles);
+                       int(pi), gd, td, sd, rd, part, pi > 0 ? 1 : 0, h.tiles);
     QSV_HIP_CHECK(hipGetLastError());
   }
   for (size_t wi = 0; wi < pl->wide.size(); ++wi) {
@@ -1070,6 +1325,7 @@ int expect_tiled_t(qsv_state* s, qsv_observable* o, double* out) {
     *out = 0.0;
     return QSV_OK;
   }
+  ensure_spans(pl, sizeof(R) == 4);
   int rc = upload_exp_plan(pl, s->device);
   if (rc) return rc;
   const ExpShape h = exp_shape(pl, s->n);
@@ -1078,7 +1334,9 @@ int expect_tiled_t(qsv_state* s, qsv_observable* o, double* out) {
   rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), reinterpret_cast<const ExpPassDev*>(d),
                      reinterpret_cast<const ExpGroupDev*>(d + pl->off_groups),
                      reinterpret_cast<const ExpTermDev*>(d + pl->off_terms),
-                     reinterpret_cast<const ExpTermDev*>(d + pl->off_wide), s->red, s->stream);
+                     reinterpret_cast<const ExpTermDev*>(d + pl->off_wide),
+                     reinterpret_cast<const ExpSpanDev*>(d + pl->off_spans),
+                     reinterpret_cast<const ExpRecDev*>(d + pl->off_recs), s->red, s->stream);
   if (rc) return rc;
   QSV_HIP_CHECK(hipMemcpyAsync(s->red_host, s->red + h.parts, sizeof(double), hipMemcpyDeviceToHost, s->stream));
   QSV_HIP_CHECK(hipStreamSynchronize(s->stream));
@@ -1182,13 +1440,16 @@ int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
     *out = 0.0;
     return QSV_OK;
   }
+  ensure_spans(pl, sizeof(R) == 4);
   const ExpShape h = exp_shape(pl, s->n);
   // scratch layout: partials[parts + 1] | passes | groups | terms (256-byte aligned)
   const size_t o_pass = al256((size_t(h.parts) + 1) * sizeof(double));
   const size_t o_grp = o_pass + al256(pl->passes.size() * sizeof(ExpPassDev));
   const size_t o_term = o_grp + al256(pl->groups.size() * sizeof(ExpGroupDev));
   const size_t o_wide = o_term + al256(pl->terms.size() * sizeof(ExpTermDev));
-  const size_t need = o_pass + exp_table_bytes(pl);
+  const size_t o_span = o_pass + exp_table_bytes(pl);
+  const size_t o_rec = o_span + al256(pl->spans.size() * sizeof(ExpSpanDev));
+  const size_t need = h.merged ? o_span + exp_span_bytes(pl) : o_span;
   if (need > kNoAllocBytes)
     return fail(QSV_ERANGE, "observable needs %zu bytes of device scratch; the no-allocation limit is %zu",
                 need, kNoAllocBytes);
@@ -1208,12 +1469,19 @@ int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
   if (!pl->wide_terms.empty())
     QSV_HIP_CHECK(hipMemcpyAsync(d + o_wide, pl->wide_terms.data(), pl->wide_terms.size() * sizeof(ExpTermDev),
                                  hipMemcpyHostToDevice, st));
+  if (h.merged && !pl->spans.empty()) {
+    QSV_HIP_CHECK(hipMemcpyAsync(d + o_span, pl->spans.data(), pl->spans.size() * sizeof(ExpSpanDev),
+                                 hipMemcpyHostToDevice, st));
+    QSV_HIP_CHECK(hipMemcpyAsync(d + o_rec, pl->recs.data(), pl->recs.size() * sizeof(ExpRecDev),
+                                 hipMemcpyHostToDevice, st));
+  }
   double* part = reinterpret_cast<double*>(d);
   // (the first launch writes every partial that is summed: nothing left from an
   // earlier call is read)
   rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), reinterpret_cast<const ExpPassDev*>(d + o_pass),
                      reinterpret_cast<const ExpGroupDev*>(d + o_grp), reinterpret_cast<const ExpTermDev*>(d + o_term),
-                     reinterpret_cast<const ExpTermDev*>(d + o_wide), part, st);
+                     reinterpret_cast<const ExpTermDev*>(d + o_wide), reinterpret_cast<const ExpSpanDev*>(d + o_span),
+                     reinterpret_cast<const ExpRecDev*>(d + o_rec), part, st);
   if (rc) return rc;
   double v = 0.0;
   QSV_HIP_CHECK(hipMemcpyAsync(&v, part + h.parts, sizeof(double), hipMemcpyDeviceToHost, st));

@@ -19,7 +19,7 @@ TOL = {"c128": 1e-13, "c64": 6e-7}
 
 @pytest.mark.parametrize("grid", [None, "3"])
 @pytest.mark.parametrize("dt", ["c64", "c128"])
-@pytest.mark.parametrize("n,terms", [(2, 3), (7, 60), (11, 1), (12, 300), (13, 300), (15, 40), (16, 300)])
+@pytest.mark.parametrize("n,terms", [(2, 3), (7, 60), (11, 1), (12, 300), (13, 300), (13, 700), (15, 40), (16, 300)])
 def test_split_passes_vs_oracle(dt, n, terms, grid, monkeypatch):
     if grid:
         monkeypatch.setenv("QSV_EXPECT_GRID", grid)
