@@ -45,6 +45,8 @@ struct ExpPassDev {
   int grp_begin, grp_count;
   int single_count;            // the first records of the pass: those of one term
   int span_begin, span_count;  // the same in spans (full tiles)
+  int obs_begin, obs_real;     // the same for lambda: real coefficients first
+  int obs_last;                // flip bits above the thread's of the last record
   int hq[kExpMaxHigh];
   int gpos[kExpMaxGlobal];
 };
@@ -96,6 +98,22 @@ struct alignas(16) ExpRecDev {
 };
 constexpr int kSpanRecs = 512;  // records of a pass, at most (their factors for a tile sit in LDS)
 
+// A single-term record of a lambda pass over a full tile. A thread's outputs y =
+// thread + k x threads gather the amplitudes thread ^ lf + j x threads, j = k ^ (the
+// flip bits above the thread's): the accumulators are kept in the order of j,
+// exchanged where those bits change from one record to the next.
+struct alignas(32) ObsRecDev {
+  uint32_t lfb;    // flip bits inside the thread part, as a byte offset
+  uint32_t zt;     // sign mask on the thread part
+  uint32_t swap;   // bits b: exchange the accumulators j and j ^ (1 << b) first
+  uint32_t s[3];   // bit 31: sign of the amplitudes with bit b of j set
+  uint32_t pad[2];
+};
+struct ObsCoefDev {
+  double c;     // alpha i^nY (its real or imaginary part) with the record's constant signs
+  uint64_t zg;  // sign mask on non-local qubits
+};
+
 // Record kinds (set by the planner): one term with flip mask 0; several
 // terms with flip mask 0; one term with a flip mask and a real (REAL) or
 // imaginary (IMAG) coefficient alpha i^nY; several terms with a flip mask.
@@ -140,6 +158,16 @@ uint64_t exp_grid_max() {
   return kExpGrid;
 }
 
+// Persistent grid of the lambda passes: one workgroup per compute unit (all that
+// its registers and LDS let in), so that each has several tiles and reads the
+// next one while it computes. Measured, one lambda of 500 strings at 24 qubits
+// complex64: 2048 workgroups (a tile each) 4.89 ms, 1024 4.17, 512 3.88, 256 3.75.
+constexpr int kObsGrid = 256;
+uint64_t obs_grid_max() {
+  if (std::getenv("QSV_EXPECT_GRID")) return exp_grid_max();
+  return kObsGrid;
+}
+
 // A group whose flip mask has more qubits than a tile holds (with the low
 // ones): its terms are wide_terms[term_begin, term_begin + term_count), with
 // zg the whole sign mask.
@@ -156,12 +184,14 @@ struct ExpPlan {
   std::vector<ExpTermDev> terms;
   std::vector<ExpSpanDev> spans;  // (full tiles only)
   std::vector<ExpRecDev> recs;
+  std::vector<ObsRecDev> orecs;  // (full tiles only)
+  std::vector<ObsCoefDev> ocoef;
   std::vector<ExpWide> wide;
   std::vector<ExpTermDev> wide_terms;
   void* dev = nullptr;  // passes | groups | terms | wide_terms | spans | recs
-  size_t off_groups = 0, off_terms = 0, off_wide = 0, off_spans = 0, off_recs = 0;
+  size_t off_groups = 0, off_terms = 0, off_wide = 0, off_spans = 0, off_recs = 0, off_orecs = 0, off_ocoef = 0;
   int device = -1;
-  bool spans_tried = false;
+  bool spans_tried = false, orecs_tried = false;
 };
 
 void free_exp_plan(ExpPlan* p) {
@@ -403,6 +433,16 @@ __device__ __forceinline__ double exp_pairs(const cx<R>* tx, const cx<R>* ty, co
   return xor_sign(sd, pt);  // the thread's part of the sign, common to every step
 }
 
+// An amplitude of a tile, by byte address (one aligned read).
+__device__ __forceinline__ cx<float> lds_amp(const char* p, float) {
+  const float2 t = *reinterpret_cast<const float2*>(p);
+  return {t.x, t.y};
+}
+__device__ __forceinline__ cx<double> lds_amp(const char* p, double) {
+  const double2 t = *reinterpret_cast<const double2*>(p);
+  return {t.x, t.y};
+}
+
 // A span's record of flip code F: its pairs (e, e ^ F), e with F's highest bit
 // clear, in registers; sums as in exp_pairs.
 template <typename R, int RB, int F, bool REAL>
@@ -531,7 +571,7 @@ __global__ void __launch_bounds__(kExpThreadsE)
         cx<R> v[1 << RB];
 #pragma unroll
         for (int e = 0; e < (1 << RB); ++e)
-          v[e] = *reinterpret_cast<const cx<R>*>(smem + ((rep * uint32_t(sizeof(cx<R>))) ^ S.off[e]));
+          v[e] = lds_amp(smem + ((rep * uint32_t(sizeof(cx<R>))) ^ S.off[e]), R(0));
         for (int ri = S.rec_begin; ri < S.rec_begin + S.rec_count; ++ri) {
           const ExpRecDev& r = recs[ri];
           const double c = cs[ri - rec0];
@@ -667,15 +707,73 @@ __device__ __forceinline__ void obs_single(const cx<R>* t, uint32_t tid, uint32_
   }
 }
 
+__device__ __forceinline__ void swap_regs(float& a, float& b) { asm volatile("v_swap_b32 %0, %1" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void swap_regs(double& a, double& b) {
+  const double t = a;
+  a = b;
+  b = t;
+}
+
+// Exchanges accumulators j and j ^ (1 << b) for the bits b of m.
+template <int KO, typename R>
+__device__ __forceinline__ void obs_swap(uint32_t m, R* ar, R* ai) {
+#pragma unroll
+  for (int b = 1; b < KO; b <<= 1)
+    if (m & uint32_t(b)) {
+#pragma unroll
+      for (int j = 0; j < KO; ++j)
+        if (!(j & b)) {
+          swap_regs(ar[j], ar[j | b]);
+          swap_regs(ai[j], ai[j | b]);
+        }
+    }
+}
+
+// One record: acc_j += c_j psi (REAL) or i c_j psi, psi the thread's j-th gathered
+// amplitude (one address, fixed offsets), c_j = +-c.
+template <typename R, bool REAL, int NT>
+__device__ __forceinline__ void obs_record(const char* smem, uint32_t tid, const ObsRecDev& r, R c, R* ar, R* ai) {
+  constexpr int KO = obs_out<R>();
+  const char* p = smem + ((tid * uint32_t(sizeof(cx<R>))) ^ r.lfb);
+  cx<R> v[KO];
+#pragma unroll
+  for (int j = 0; j < KO; ++j) v[j] = lds_amp(p + j * NT * int(sizeof(cx<R>)), R(0));
+  R cj[KO];
+  cj[0] = xor_sign(c, uint32_t(__popc(tid & r.zt)) << 31);
+#pragma unroll
+  for (int j = 1; j < KO; ++j) {
+    const int b = j >= 4 ? 2 : (j >= 2 ? 1 : 0);
+    cj[j] = xor_sign(cj[j & ~(1 << b)], r.s[b]);
+  }
+#pragma unroll
+  for (int j = 0; j < KO; ++j) {
+    if constexpr (REAL) {
+      ar[j] = fma(cj[j], v[j].re, ar[j]);
+      ai[j] = fma(cj[j], v[j].im, ai[j]);
+    } else {
+      ar[j] = fma(-cj[j], v[j].im, ar[j]);
+      ai[j] = fma(cj[j], v[j].re, ai[j]);
+    }
+  }
+}
+
+// RECS: the single-term records come as ObsRecDev: 28 vector instructions and
+// four LDS reads of 16 bytes per record and thread (complex64), where forming
+// each output's address and sign took about twice as many. One lambda, with the
+// grid above: 500 strings at 24 qubits complex64 4.89 -> 2.98 ms (both grids
+// alike: 3.75 -> 2.98), 200 strings at 28 qubits 31.4 -> 26.3; complex128, 250
+// strings, 24 qubits 4.12 -> 3.26 ms.
 // FIXED: the tile has obs_tile_bits<R>() qubits and every thread's outputs
 // exist (complex64: 2^13 = 8 x 1024, complex128: 2^12 = 4 x 1024). Tiles of
 // at most obs_out<R>() x NT amplitudes.
-template <typename R, bool FIXED, int NT>
+template <typename R, bool FIXED, int NT, bool RECS>
 __global__ void __launch_bounds__(NT)
     k_apply_obs_tile(const R* __restrict__ psi, R* __restrict__ lam, const ExpPassDev* __restrict__ passes,
                      int pass_idx, const ExpGroupDev* __restrict__ groups,
-                     const ExpTermDev* __restrict__ terms, int accumulate, uint64_t ntiles) {
+                     const ExpTermDev* __restrict__ terms, const ObsRecDev* __restrict__ orecs,
+                     const ObsCoefDev* __restrict__ ocoef, int accumulate, uint64_t ntiles) {
   constexpr int KO = obs_out<R>();
+  __shared__ R cs[RECS ? kSpanRecs : 1];  // the records' coefficients with the tile's signs
   extern __shared__ __align__(16) char smem[];
   __shared__ ExpTermLds et[kExpLdsTerms];
   cx<R>* t = reinterpret_cast<cx<R>*>(smem);
@@ -703,15 +801,33 @@ __global__ void __launch_bounds__(NT)
     R ar[KO], ai[KO];
 #pragma unroll
     for (int k = 0; k < KO; ++k) ar[k] = ai[k] = R(0);
-    const ExpGroupDev* gd = groups + P.grp_begin;
+    if (RECS && int(tid) < P.single_count) {
+      const ObsCoefDev& r = ocoef[P.obs_begin + int(tid)];
+      cs[tid] = R(xor_sign(r.c, uint32_t(__popcll(base & r.zg) & 1) << 31));
+    }
+    const ExpGroupDev* gd = groups + P.grp_begin + (RECS ? P.single_count : 0);
     ExpGroupHead head(gd[0]);
     __syncthreads();  // tile (and, first time, the group table) in LDS
-    for (int left = P.grp_count; left > 0; --left, ++gd) {
+    if constexpr (RECS) {
+      int i = 0;
+      for (; i < P.obs_real; ++i) {
+        const ObsRecDev& r = orecs[P.obs_begin + i];
+        if (r.swap) obs_swap<KO>(r.swap, ar, ai);
+        obs_record<R, true, NT>(smem, tid, r, cs[i], ar, ai);
+      }
+      for (; i < P.single_count; ++i) {
+        const ObsRecDev& r = orecs[P.obs_begin + i];
+        if (r.swap) obs_swap<KO>(r.swap, ar, ai);
+        obs_record<R, false, NT>(smem, tid, r, cs[i], ar, ai);
+      }
+      obs_swap<KO>(uint32_t(P.obs_last), ar, ai);
+    }
+    for (int left = RECS ? P.grp_count - P.single_count : P.grp_count; left > 0; --left, ++gd) {
       const ExpGroup G = head.fold(base, gd);
       const uint32_t kind = head.kind;
       head = ExpGroupHead(gd[1]);  // (see k_expect_tile)
       const uint32_t lf = G.lf;
-      if (kind == kExpZ1 || kind == kExpFlipRe || kind == kExpFlipIm) {
+      if (!RECS && (kind == kExpZ1 || kind == kExpFlipRe || kind == kExpFlipIm)) {
         // alpha i^nY is real or imaginary (a Z-only string's is real):
         // lambda += c psi or i c psi
         const uint32_t pt = (__popc((tid ^ lf) & G.zl) & 1);
@@ -1194,6 +1310,53 @@ ExpPlan* build_exp_plan(const qsv_observable* o, qsv_dtype dt) {
   return p;
 }
 
+// The lambda records of a plan of full tiles (built for the first lambda pass).
+void ensure_obs_recs(ExpPlan* p, bool c64) {
+  if (p->orecs_tried) return;
+  p->orecs_tried = true;
+  if (p->L != (c64 ? obs_tile_bits<float>() : obs_tile_bits<double>())) return;
+  for (const ExpPassDev& d : p->passes)
+    if (d.single_count > kSpanRecs) return;
+  constexpr int tb = 10;  // 1024 threads
+  static_assert(obs_threads<float>() == 1 << tb && obs_threads<double>() == 1 << tb, "thread part of an index");
+  for (ExpPassDev& d : p->passes) {
+    const ExpGroupDev* g = p->groups.data() + d.grp_begin;
+    std::vector<int> order;
+    for (int i = 0; i < d.single_count; ++i) order.push_back(i);
+    auto gray = [&](int i) {  // neighbours differ in one bit
+      uint32_t h = g[i].lf >> tb, k = h;
+      for (h >>= 1; h; h >>= 1) k ^= h;
+      return k;
+    };
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+      const bool ia = g[a].kind == kExpFlipIm, ib = g[b].kind == kExpFlipIm;
+      return ia != ib ? !ia : gray(a) < gray(b);
+    });
+    d.obs_begin = int(p->orecs.size());
+    d.obs_real = 0;
+    uint32_t cur = 0;
+    for (int i : order) {
+      const ExpGroupDev& G = g[i];
+      const bool im = G.kind == kExpFlipIm;
+      d.obs_real += im ? 0 : 1;
+      const uint32_t hi = G.lf >> tb, zh = G.zl >> tb;
+      ObsRecDev r{};
+      r.lfb = (G.lf & ((1u << tb) - 1)) * (c64 ? 8u : 16u);
+      r.zt = G.zl & ((1u << tb) - 1);
+      r.swap = hi ^ cur;
+      cur = hi;
+      for (int b = 0; b < 3; ++b) r.s[b] = (zh >> b & 1) << 31;
+      p->orecs.push_back(r);
+      // the sign is that of x = y ^ lf: thread part tid ^ lf (constant lf & zl),
+      // upper part j itself
+      const double c = im ? G.im : G.re;
+      p->ocoef.push_back({__builtin_popcount(G.lf & r.zt) & 1 ? -c : c, G.zg});
+    }
+    d.obs_last = int(cur);
+  }
+  p->device = -1;  // (tables already uploaded are uploaded again, with them)
+}
+
 // The spans of a plan of full tiles (built for the first expectation; lambda
 // passes have no use for them).
 void ensure_spans(ExpPlan* p, bool c64) {
@@ -1217,7 +1380,9 @@ int upload_exp_plan(ExpPlan* p, int device) {
   p->off_wide = (p->off_terms + p->terms.size() * sizeof(ExpTermDev) + 255) / 256 * 256;
   p->off_spans = (p->off_wide + std::max<size_t>(1, p->wide_terms.size()) * sizeof(ExpTermDev) + 255) / 256 * 256;
   p->off_recs = (p->off_spans + p->spans.size() * sizeof(ExpSpanDev) + 255) / 256 * 256;
-  const size_t total = p->off_recs + p->recs.size() * sizeof(ExpRecDev);
+  p->off_orecs = (p->off_recs + p->recs.size() * sizeof(ExpRecDev) + 255) / 256 * 256;
+  p->off_ocoef = (p->off_orecs + p->orecs.size() * sizeof(ObsRecDev) + 255) / 256 * 256;
+  const size_t total = p->off_ocoef + p->ocoef.size() * sizeof(ObsCoefDev);
   if (hipMalloc(&p->dev, total) != hipSuccess) return fail(QSV_ENOMEM, "observable plan allocation failed");
   char* d = static_cast<char*>(p->dev);
   if (a) QSV_HIP_CHECK(hipMemcpy(d, p->passes.data(), a, hipMemcpyHostToDevice));
@@ -1231,6 +1396,10 @@ int upload_exp_plan(ExpPlan* p, int device) {
   if (!p->spans.empty()) {
     QSV_HIP_CHECK(hipMemcpy(d + p->off_spans, p->spans.data(), p->spans.size() * sizeof(ExpSpanDev), hipMemcpyHostToDevice));
     QSV_HIP_CHECK(hipMemcpy(d + p->off_recs, p->recs.data(), p->recs.size() * sizeof(ExpRecDev), hipMemcpyHostToDevice));
+  }
+  if (!p->orecs.empty()) {
+    QSV_HIP_CHECK(hipMemcpy(d + p->off_orecs, p->orecs.data(), p->orecs.size() * sizeof(ObsRecDev), hipMemcpyHostToDevice));
+    QSV_HIP_CHECK(hipMemcpy(d + p->off_ocoef, p->ocoef.data(), p->ocoef.size() * sizeof(ObsCoefDev), hipMemcpyHostToDevice));
   }
   p->device = device;
   return QSV_OK;
@@ -1356,6 +1525,7 @@ int apply_obs_tiled_t(const qsv_state* in, qsv_observable* o, qsv_state* out) {
     QSV_HIP_CHECK(hipGetLastError());
     return QSV_OK;
   }
+  ensure_obs_recs(pl, sizeof(R) == 4);
   int rc = upload_exp_plan(pl, in->device);
   if (rc) return rc;
   const uint64_t tiles = dim(in->n - pl->L);
@@ -1363,24 +1533,21 @@ int apply_obs_tiled_t(const qsv_state* in, qsv_observable* o, qsv_state* out) {
   // compile-time output count when every thread has obs_out<R>() outputs
   constexpr int NTo = obs_threads<R>();
   const bool fixed = pl->L == obs_tile_bits<R>() && (size_t(1) << pl->L) == size_t(obs_out<R>()) * NTo;
-  QSV_HIP_CHECK(hipFuncSetAttribute(fixed ? reinterpret_cast<const void*>(&k_apply_obs_tile<R, true, NTo>)
-                                          : reinterpret_cast<const void*>(&k_apply_obs_tile<R, false, NTo>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+  const auto kfn = fixed && !pl->orecs.empty() ? &k_apply_obs_tile<R, true, NTo, true>
+                   : fixed                     ? &k_apply_obs_tile<R, true, NTo, false>
+                                               : &k_apply_obs_tile<R, false, NTo, false>;
+  QSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    int(lds)));
   char* d = static_cast<char*>(pl->dev);
   for (size_t pi = 0; pi < pl->passes.size(); ++pi) {
     ProfScope ps("apply_obs", double(sizeof(cx<R>)) * double(N) * (pi > 0 ? 3.0 : 2.0), in->stream);
-    const dim3 grid(unsigned(std::min<uint64_t>(tiles, exp_grid_max())));
-    const auto* pd = reinterpret_cast<const ExpPassDev*>(d);
-    const auto* gd = reinterpret_cast<const ExpGroupDev*>(d + pl->off_groups);
-    const auto* td = reinterpret_cast<const ExpTermDev*>(d + pl->off_terms);
-    if (fixed)
-      hipLaunchKernelGGL((k_apply_obs_tile<R, true, NTo>), grid, dim3(NTo), lds, in->stream,
-                         static_cast<const R*>(in->ptr), static_cast<R*>(out->ptr), pd, int(pi), gd, td,
-                         pi > 0 ? 1 : 0, tiles);
-    else
-      hipLaunchKernelGGL((k_apply_obs_tile<R, false, NTo>), grid, dim3(NTo), lds, in->stream,
-                         static_cast<const R*>(in->ptr), static_cast<R*>(out->ptr), pd, int(pi), gd, td,
-                         pi > 0 ? 1 : 0, tiles);
+    hipLaunchKernelGGL(kfn, dim3(unsigned(std::min<uint64_t>(tiles, obs_grid_max()))), dim3(NTo), lds, in->stream,
+                       static_cast<const R*>(in->ptr), static_cast<R*>(out->ptr),
+                       reinterpret_cast<const ExpPassDev*>(d), int(pi),
+                       reinterpret_cast<const ExpGroupDev*>(d + pl->off_groups),
+                       reinterpret_cast<const ExpTermDev*>(d + pl->off_terms),
+                       reinterpret_cast<const ObsRecDev*>(d + pl->off_orecs),
+                       reinterpret_cast<const ObsCoefDev*>(d + pl->off_ocoef), pi > 0 ? 1 : 0, tiles);
     QSV_HIP_CHECK(hipGetLastError());
   }
   const auto* wt = reinterpret_cast<const ExpTermDev*>(d + pl->off_wide);
