@@ -548,32 +548,93 @@ int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T) {
 template int adjoint_tables<float>(const qsv_circuit*, const double*, AdjTables&);
 template int adjoint_tables<double>(const qsv_circuit*, const double*, AdjTables&);
 
-// Reverse sweep by tile passes. On entry psi = psi_L, lam = H psi_L and energy =
-// <psi|lam>; on
-// return both are uncomputed and rows[r] holds the gradient term of the r-th
-// parametric rotation counted from the end (T.row_slot maps rows to slots).
+// The tables of a sweep that do not depend on theta, one after the other.
+struct AdjLayout {
+  size_t pass, ops, segs, rops, ents, heads, prow, bytes;
+};
+
+static AdjLayout adj_pack(const AdjTables& T, std::vector<char>* out) {
+  const std::vector<RegHeadDev> heads = op_heads(T.sb);
+  AdjLayout o{};
+  size_t at = 0;
+  auto put = [&](size_t& off, const void* p, size_t bytes) {
+    off = at;
+    at += (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
+    if (!out) return;
+    out->resize(at);
+    if (bytes) std::copy_n(static_cast<const char*>(p), bytes, out->data() + off);
+  };
+  put(o.pass, T.hp.data(), T.hp.size() * sizeof(TilePassDev));
+  put(o.ops, T.ho.data(), T.ho.size() * sizeof(TileOpDev));
+  put(o.segs, T.sb.segs.data(), T.sb.segs.size() * sizeof(RegSegDev));
+  put(o.rops, T.sb.rops.data(), T.sb.rops.size() * sizeof(RegOpDev));
+  put(o.ents, T.sb.ents.data(), T.sb.ents.size() * sizeof(PhaseEntDev));
+  put(o.heads, heads.data(), heads.size() * sizeof(RegHeadDev));
+  put(o.prow, T.prow.data(), T.prow.size() * sizeof(int));
+  o.bytes = at;
+  return o;
+}
+
+void adjoint_values(const AdjTables& T, const double* theta, std::vector<cd>& vals) {
+  vals = T.vals;
+  for (const DynVal& d : T.dyn) {
+    const double t = d.sgn * theta[d.slot];
+    cd* v = &vals[size_t(d.voff)];
+    if (d.type == 0) {
+      rotation_shears(t, v);
+    } else if (d.type == 1) {
+      cd m[4];
+      rotation_matrix(3, t, m);
+      v[0] = m[0];
+      v[1] = m[3];
+    } else {
+      v[0] = {std::cos(t / 2), std::sin(t / 2)};
+    }
+  }
+}
+
 template <typename R>
-int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, qsv_state* lam,
-                           std::vector<double>& rows) {
+AdjCache* adjoint_cache(qsv_plan* plan, const qsv_circuit* c) {
+  if (!same_circuit(*c, plan->circ_copy)) return nullptr;
+  if (!plan->adj) {
+    plan->adj = new AdjCache();
+    for (const Gate& g : c->gates)
+      if (g.kind == Gate::PAULI && g.slot >= 0 &&
+          (g.targets.size() < 2 || std::any_of(g.paulis.begin(), g.paulis.end(), [](int p) { return p != 3; })))
+        return nullptr;
+    if (adjoint_tables<R>(c, nullptr, plan->adj->T) != QSV_OK) clear_error();
+    else plan->adj->usable = plan->adj->T.reg;
+  }
+  return plan->adj->usable ? plan->adj : nullptr;
+}
+template AdjCache* adjoint_cache<float>(qsv_plan*, const qsv_circuit*);
+template AdjCache* adjoint_cache<double>(qsv_plan*, const qsv_circuit*);
+
+void adjoint_cache_free(AdjCache* a) {
+  if (!a) return;
+  if (a->dev) (void)hipFree(a->dev);
+  delete a;
+}
+
+// Reverse sweep by tile passes. On entry psi = psi_L, lam = H psi_L and energy =
+// <psi|lam>; on return both are uncomputed and rows[r] holds the gradient term of the r-th
+// parametric rotation counted from the end (T.row_slot maps rows to slots). vals:
+// the host values; cache: T's, if it is kept with a plan (else null).
+template <typename R>
+int adjoint_backward_tiled(const AdjTables& T, std::vector<cd>& vals, AdjCache* cache, int n, double energy,
+                           qsv_state* psi, qsv_state* lam, std::vector<double>& rows) {
   const std::vector<int>& row_slot = T.row_slot;
   const int L = T.L, kmax = T.kmax;
   const bool reg = T.reg;
   const std::vector<TilePassDev>& hp = T.hp;
-  const std::vector<TileOpDev>& ho = T.ho;
-  const std::vector<int>& prow = T.prow;
-  const SegBuild& sb = T.sb;
   std::vector<cx<R>> pool;
   {
     std::vector<cd> pv;
-    if (reg) assemble_pool(sb, T.vals, pv);
-    else pv.swap(T.vals);
+    if (reg) assemble_pool(T.sb, vals, pv);
+    else pv.swap(vals);
     pool.resize(pv.size());
     for (size_t i = 0; i < pv.size(); ++i) pool[i] = {R(pv[i].re), R(pv[i].im)};
   }
-  const std::vector<RegSegDev>& segs = sb.segs;
-  const std::vector<RegOpDev>& rops = sb.rops;
-  const std::vector<PhaseEntDev>& ents = sb.ents;
-  const std::vector<RegHeadDev> heads = op_heads(sb);
   const int nrows = int(row_slot.size());
   const uint64_t tiles = dim(n - L);
   // register-resident passes: tile + gradient slots in LDS
@@ -603,45 +664,42 @@ int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, q
   }
   if (const char* e = std::getenv("QSV_ADJOINT_GRID")) gmax = uint64_t(std::max(1, std::atoi(e)));
   const int G = int(std::min<uint64_t>(tiles, gmax));
-  // one device allocation: passes | ops | pool | segs | rops | ents | heads | prow | partial[nrows x G] | rows[nrows]
+  // psi's work buffer (kept for the next gradient; the sweep synchronises before
+  // returning): pool | partial[nrows x G] | rows[nrows], and the tables unless they
+  // are kept with a plan, each uploaded in one copy
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t o_ops = al(hp.size() * sizeof(TilePassDev));
-  const size_t o_pool = o_ops + al(std::max<size_t>(1, ho.size()) * sizeof(TileOpDev));
-  const size_t o_segs = o_pool + al(std::max<size_t>(1, pool.size()) * sizeof(cx<R>));
-  const size_t o_rops = o_segs + al(std::max<size_t>(1, segs.size()) * sizeof(RegSegDev));
-  const size_t o_ents = o_rops + al(std::max<size_t>(1, rops.size()) * sizeof(RegOpDev));
-  const size_t o_heads = o_ents + al(std::max<size_t>(1, ents.size()) * sizeof(PhaseEntDev));
-  const size_t o_prow = o_heads + al(heads.size() * sizeof(RegHeadDev));
-  const size_t o_part = o_prow + al(std::max<size_t>(1, prow.size()) * sizeof(int));
+  std::vector<char> stage;
+  const bool kept = cache && cache->dev && cache->device == psi->device;
+  const AdjLayout lo = adj_pack(T, kept ? nullptr : &stage);
+  const size_t o_part = al(std::max<size_t>(1, pool.size()) * sizeof(cx<R>));
   const size_t o_rows = o_part + al(std::max<size_t>(1, size_t(nrows) * G) * sizeof(double));
-  const size_t total = o_rows + al(std::max(1, nrows) * sizeof(double));
-  // the tables live in psi's work buffer (kept for the next gradient; the
-  // sweep synchronises before returning)
+  const size_t o_tab = o_rows + al(std::max(1, nrows) * sizeof(double));
   void* wb = nullptr;
-  if (int e = state_work(psi, total, &wb)) return e;
+  if (int e = state_work(psi, cache ? o_tab : o_tab + lo.bytes, &wb)) return e;
   char* d = static_cast<char*>(wb);
+  char* tab = cache ? static_cast<char*>(cache->dev) : d + o_tab;
   hipStream_t st = psi->stream;
   int rc = QSV_OK;
   auto fin = [&](int r) {
     (void)hipStreamSynchronize(st);
     return r;
   };
-  if (hipMemcpyAsync(d, hp.data(), hp.size() * sizeof(TilePassDev), hipMemcpyHostToDevice, st) != hipSuccess ||
-      (!ho.empty() && hipMemcpyAsync(d + o_ops, ho.data(), ho.size() * sizeof(TileOpDev),
-                                     hipMemcpyHostToDevice, st) != hipSuccess) ||
-      (!pool.empty() && hipMemcpyAsync(d + o_pool, pool.data(), pool.size() * sizeof(cx<R>),
-                                       hipMemcpyHostToDevice, st) != hipSuccess) ||
-      (!segs.empty() && hipMemcpyAsync(d + o_segs, segs.data(), segs.size() * sizeof(RegSegDev),
-                                       hipMemcpyHostToDevice, st) != hipSuccess) ||
-      (!rops.empty() && hipMemcpyAsync(d + o_rops, rops.data(), rops.size() * sizeof(RegOpDev),
-                                       hipMemcpyHostToDevice, st) != hipSuccess) ||
-      (!ents.empty() && hipMemcpyAsync(d + o_ents, ents.data(), ents.size() * sizeof(PhaseEntDev),
-                                       hipMemcpyHostToDevice, st) != hipSuccess) ||
-      hipMemcpyAsync(d + o_heads, heads.data(), heads.size() * sizeof(RegHeadDev), hipMemcpyHostToDevice, st) !=
-          hipSuccess ||
-      (!prow.empty() && hipMemcpyAsync(d + o_prow, prow.data(), prow.size() * sizeof(int),
-                                       hipMemcpyHostToDevice, st) != hipSuccess))
+  if (cache && !kept) {
+    if (cache->dev) (void)hipFree(cache->dev);
+    cache->dev = nullptr;
+    if (hipMalloc(&cache->dev, lo.bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      cache->dev = nullptr;
+      return fail(QSV_ENOMEM, "sweep table allocation failed");
+    }
+    cache->device = -1;  // (until they are uploaded)
+    tab = static_cast<char*>(cache->dev);
+  }
+  if ((!kept && hipMemcpyAsync(tab, stage.data(), lo.bytes, hipMemcpyHostToDevice, st) != hipSuccess) ||
+      (!pool.empty() &&
+       hipMemcpyAsync(d, pool.data(), pool.size() * sizeof(cx<R>), hipMemcpyHostToDevice, st) != hipSuccess))
     return fin(fail(QSV_EHIP, "tiled sweep table upload failed"));
+  if (cache && !kept) cache->device = psi->device;
   double* part = reinterpret_cast<double*>(d + o_part);
   hipLaunchKernelGGL(k_zero_doubles, dim3(256), dim3(256), 0, st, part, uint64_t(nrows) * G);
   {
@@ -652,14 +710,14 @@ int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, q
 #define QSV_ADJR_LAUNCH(KM)                                                                      \
     hipLaunchKernelGGL((k_adj_reg<R, sizeof(R) == 4 ? 4 : 3, KM, 8>), dim3(G), dim3(256), lds, st, \
                        static_cast<R*>(psi->ptr), static_cast<R*>(lam->ptr),                      \
-                       reinterpret_cast<const TilePassDev*>(d), int(pi),                          \
-                       reinterpret_cast<const RegSegDev*>(d + o_segs),                            \
-                       reinterpret_cast<const RegHeadDev*>(d + o_heads),                          \
-                       reinterpret_cast<const RegOpDev*>(d + o_rops),                             \
-                       reinterpret_cast<const TileOpDev*>(d + o_ops),                             \
-                       reinterpret_cast<const PhaseEntDev*>(d + o_ents),                          \
-                       reinterpret_cast<const cx<R>*>(d + o_pool),                                \
-                       reinterpret_cast<const int*>(d + o_prow), part, tiles,                     \
+                       reinterpret_cast<const TilePassDev*>(tab + lo.pass), int(pi),                          \
+                       reinterpret_cast<const RegSegDev*>(tab + lo.segs),                            \
+                       reinterpret_cast<const RegHeadDev*>(tab + lo.heads),                          \
+                       reinterpret_cast<const RegOpDev*>(tab + lo.rops),                             \
+                       reinterpret_cast<const TileOpDev*>(tab + lo.ops),                             \
+                       reinterpret_cast<const PhaseEntDev*>(tab + lo.ents),                          \
+                       reinterpret_cast<const cx<R>*>(d),                                \
+                       reinterpret_cast<const int*>(tab + lo.prow), part, tiles,                     \
                        R(pi == 0 ? energy : 0.0), R(pi + 1 == hp.size() ? energy : 0.0))
         if (!hp[pi].general) QSV_ADJR_LAUNCH(0);
         else if (kmax <= 2) QSV_ADJR_LAUNCH(2);
@@ -682,9 +740,9 @@ int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, q
 #define QSV_ADJ_LAUNCH(KM)                                                                       \
     hipLaunchKernelGGL((k_tile_adj<R, KM>), dim3(G), dim3(kAdjTileThreads), lds, st,               \
                        static_cast<R*>(psi->ptr), static_cast<R*>(lam->ptr),                      \
-                       reinterpret_cast<const TilePassDev*>(d), int(pi),                          \
-                       reinterpret_cast<const TileOpDev*>(d + o_ops),                             \
-                       reinterpret_cast<const cx<R>*>(d + o_pool), part, tiles)
+                       reinterpret_cast<const TilePassDev*>(tab + lo.pass), int(pi),                          \
+                       reinterpret_cast<const TileOpDev*>(tab + lo.ops),                             \
+                       reinterpret_cast<const cx<R>*>(d), part, tiles)
       if (kmax <= 2) QSV_ADJ_LAUNCH(2);
       else if (kmax <= 3) QSV_ADJ_LAUNCH(3);
       else QSV_ADJ_LAUNCH(5);
@@ -703,7 +761,9 @@ int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, q
   return fin(rc);
 }
 
-template int adjoint_backward_tiled<float>(AdjTables&, int, double, qsv_state*, qsv_state*, std::vector<double>&);
-template int adjoint_backward_tiled<double>(AdjTables&, int, double, qsv_state*, qsv_state*, std::vector<double>&);
+template int adjoint_backward_tiled<float>(const AdjTables&, std::vector<cd>&, AdjCache*, int, double, qsv_state*,
+                                           qsv_state*, std::vector<double>&);
+template int adjoint_backward_tiled<double>(const AdjTables&, std::vector<cd>&, AdjCache*, int, double, qsv_state*,
+                                            qsv_state*, std::vector<double>&);
 
 }  // namespace qsv

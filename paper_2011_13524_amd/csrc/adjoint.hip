@@ -78,6 +78,16 @@ __global__ void __launch_bounds__(kAdjThreads)
   if (threadIdx.x == 0) partial[blockIdx.x] = r;
 }
 
+// lam += a psi.
+template <typename R>
+__global__ void __launch_bounds__(kAdjThreads) k_axpy(R* __restrict__ lam, const R* __restrict__ psi, uint64_t N, R a) {
+  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
+  for (uint64_t x = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < N; x += stride) {
+    const cx<R> p = load1(psi, x), l = load1(lam, x);
+    store1(lam, x, cx<R>{fma(a, p.re, l.re), fma(a, p.im, l.im)});
+  }
+}
+
 // out[row] = sum of `cols` partials of row `row` (fixed order).
 __global__ void __launch_bounds__(kAdjThreads)
     k_sum_rows(const double* __restrict__ partial, int cols, double* __restrict__ out) {
@@ -94,8 +104,8 @@ int expectation_impl(qsv_state* s, const qsv_observable* o, double* out);
 int apply_observable_tiled(const qsv_state* in, const qsv_observable* o, qsv_state* out);
 int circuit_apply_unfused(qsv_state* s, const qsv_circuit* c, const double* theta);
 template <typename R>
-int adjoint_backward_tiled(AdjTables& T, int n, double energy, qsv_state* psi, qsv_state* lam,
-                           std::vector<double>& rows);
+int adjoint_backward_tiled(const AdjTables& T, std::vector<cd>& vals, AdjCache* cache, int n, double energy,
+                           qsv_state* psi, qsv_state* lam, std::vector<double>& rows);
 
 namespace {
 
@@ -148,32 +158,40 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
   int tiled_min = sizeof(R) == 4 ? 12 : 11;
   int tiled_must = tiled_min + 8;  // no per-gate sweep from here on
   if (const char* e = std::getenv("QSV_ADJOINT_TILED_MIN")) tiled_min = tiled_must = std::atoi(e);  // testing
-  AdjTables T;
+  AdjTables own;
+  std::vector<cd> vals;
   bool tiled = n >= tiled_min && !wide;
-  if (tiled && (rc = adjoint_tables<R>(c, theta, T))) {
+  AdjCache* cache = tiled && plan ? adjoint_cache<R>(plan, c) : nullptr;
+  const AdjTables& T = cache ? cache->T : own;
+  if (cache) {
+    adjoint_values(T, theta, vals);
+  } else if (tiled && (rc = adjoint_tables<R>(c, theta, own))) {
     // (a gate with more local controls than the passes take)
     if (n >= tiled_must) return rc;
     clear_error();
     tiled = false;
+  } else if (tiled) {
+    vals.swap(own.vals);
   }
   // E = Re <psi|lambda>
-  double re = 0.0, im = 0.0;
+  // the norm that rounding left is divided out where the circuit keeps it
+  // exactly: it made up nearly all of the energy's error (24 qubits, 960
+  // parameters, complex64: 0.6e-6 to 1.7e-6 with it, 0.4e-7 to 3e-7 without)
+  double re = 0.0, norm2 = 1.0;
+  if ((rc = inner_and_norm(psi, lam, &re, &norm2))) return rc;
+  if (!(circuit_unitary(c) && norm2 > 0.0 && std::isfinite(norm2))) norm2 = 1.0;
+  *energy = re / norm2;
   if (tiled) {
-    // the norm that rounding left is divided out where the circuit keeps it
-    // exactly: it made up nearly all of the energy's error (24 qubits, 960
-    // parameters, complex64: 0.6e-6 to 1.7e-6 with it, 0.4e-7 to 3e-7 without)
-    double norm2 = 1.0;
-    if ((rc = inner_and_norm(psi, lam, &re, &norm2))) return rc;
-    if (!(circuit_unitary(c) && norm2 > 0.0 && std::isfinite(norm2))) norm2 = 1.0;
-    *energy = re / norm2;
     std::vector<double> rv;
-    if ((rc = adjoint_backward_tiled<R>(T, n, re / norm2, psi, lam, rv))) return rc;
+    if ((rc = adjoint_backward_tiled<R>(T, vals, cache, n, re / norm2, psi, lam, rv))) return rc;
     for (int i = 0; i < c->nparams; ++i) grad[i] = 0.0;
     for (size_t r = 0; r < rv.size(); ++r) grad[T.row_slot[r]] += rv[r] / norm2;
     return QSV_OK;
   }
-  if ((rc = qsv_inner(psi, lam, &re, &im))) return rc;
-  *energy = re;
+  // (on lambda - E psi, as in the tile passes; put back below)
+  const int AB = adj_blocks(N);
+  hipLaunchKernelGGL((k_axpy<R>), dim3(AB), dim3(kAdjThreads), 0, st, static_cast<R*>(lam->ptr),
+                     static_cast<const R*>(psi->ptr), N, R(-re / norm2));
   const int B = adj_blocks(N / 2);
   if ((rc = ensure_reduce_scratch(psi, size_t(nrot) * B + size_t(nrot) + 1))) return rc;
   double* partial = psi->red;
@@ -221,6 +239,9 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
                               g.ctrl_vals.data(), int(g.controls.size()))))
       return rc;
   }
+  hipLaunchKernelGGL((k_axpy<R>), dim3(AB), dim3(kAdjThreads), 0, st, static_cast<R*>(lam->ptr),
+                     static_cast<const R*>(psi->ptr), N, R(re / norm2));
+  QSV_HIP_CHECK(hipGetLastError());
   for (int i = 0; i < c->nparams; ++i) grad[i] = 0.0;
   if (nrot > 0) {
     hipLaunchKernelGGL(k_sum_rows, dim3(nrot), dim3(kAdjThreads), 0, st, partial, B, rows);
@@ -228,7 +249,7 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
     QSV_HIP_CHECK(hipStreamSynchronize(st));
     std::vector<double> hr(nrot);
     QSV_HIP_CHECK(hipMemcpy(hr.data(), rows, nrot * sizeof(double), hipMemcpyDeviceToHost));
-    for (int r = 0; r < nrot; ++r) grad[row_slot[r]] += hr[r];
+    for (int r = 0; r < nrot; ++r) grad[row_slot[r]] += hr[r] / norm2;
   } else {
     QSV_HIP_CHECK(hipStreamSynchronize(st));
   }

@@ -340,23 +340,6 @@ struct BatchTiles {
 
 namespace {
 
-bool same_gate(const Gate& a, const Gate& b) {
-  if (a.kind != b.kind || a.targets != b.targets || a.controls != b.controls || a.ctrl_vals != b.ctrl_vals ||
-      a.pauli != b.pauli || a.slot != b.slot || a.paulis != b.paulis || a.mat.size() != b.mat.size())
-    return false;
-  if (!(a.fixed_angle == b.fixed_angle)) return false;
-  for (size_t i = 0; i < a.mat.size(); ++i)
-    if (!(a.mat[i].re == b.mat[i].re && a.mat[i].im == b.mat[i].im)) return false;
-  return true;
-}
-
-bool same_circuit(const qsv_circuit& a, const qsv_circuit& b) {
-  if (a.n != b.n || a.nparams != b.nparams || a.gates.size() != b.gates.size()) return false;
-  for (size_t i = 0; i < a.gates.size(); ++i)
-    if (!same_gate(a.gates[i], b.gates[i])) return false;
-  return true;
-}
-
 // Host tables of all distinct circuits, one after the other.
 struct Tables {
   std::vector<MCirc> circs;

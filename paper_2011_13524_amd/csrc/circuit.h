@@ -39,6 +39,9 @@ int adjoint_pauli_step(qsv_state* psi, qsv_state* lam, const Gate& g, double t, 
 // Gate matrix of a gate for the given parameters (row-major, 2^k x 2^k).
 void gate_matrix(const Gate& g, const double* theta, std::vector<cd>& out);
 
+// Whether two circuits have the same gates in the same order.
+bool same_circuit(const qsv_circuit& a, const qsv_circuit& b);
+
 // Whether every gate is unitary (matrices: to 1e-12).
 bool circuit_unitary(const qsv_circuit* c);
 

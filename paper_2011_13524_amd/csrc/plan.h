@@ -7,6 +7,8 @@
 
 #include "circuit.h"
 
+struct qsv_plan;
+
 namespace qsv {
 
 constexpr int kTileMaxOps = 4096;
@@ -276,6 +278,24 @@ struct AdjTables {
 template <typename R>
 int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T);
 
+
+// Reverse-sweep tables kept with a forward plan: those that do not depend on
+// theta, on the host and on the device that first needed them.
+struct AdjCache {
+  AdjTables T;
+  bool usable = false;
+  void* dev = nullptr;
+  int device = -1;
+};
+// The tables of c's reverse sweep kept with `plan` (made on the first call), or
+// null where they cannot be: c is not the plan's circuit, or values other than
+// rotations' and Z strings' depend on theta.
+template <typename R>
+AdjCache* adjoint_cache(qsv_plan* plan, const qsv_circuit* c);
+void adjoint_cache_free(AdjCache* a);
+// T.vals with the values that depend on theta.
+void adjoint_values(const AdjTables& T, const double* theta, std::vector<cd>& vals);
+
 constexpr int kAdjMaxRows = 64;  // gradient rows per pass (LDS slots)
 
 // A fused block: gates (indices into the circuit) applied in order, acting on
@@ -353,6 +373,7 @@ struct qsv_plan {
   void* h_stage = nullptr;
   size_t stage_bytes = 0;
   hipEvent_t stage_ev = nullptr;
+  qsv::AdjCache* adj = nullptr;  // reverse-sweep tables (first gradient with this plan)
   bool stage_used = false;
 };
 

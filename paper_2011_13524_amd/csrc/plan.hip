@@ -875,6 +875,7 @@ static int apply_fused_t(qsv_state* s, qsv_plan* p, const double* theta) {
 // Releases a plan and its device tables (keeps the error message).
 static void plan_release(qsv_plan* p) {
   if (!p) return;
+  adjoint_cache_free(p->adj);
   if (p->stage_used) (void)hipEventSynchronize(p->stage_ev);
   if (p->stage_ev) (void)hipEventDestroy(p->stage_ev);
   if (p->h_stage) (void)hipHostFree(p->h_stage);

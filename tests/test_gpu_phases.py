@@ -153,3 +153,26 @@ def test_states_of_one_tile(dt, n, max_k):
     for rec in g:
         O.apply_gate(ref, rec, None)
     assert np.max(np.abs(s.store() - ref)) <= AMP_TOL[dt]
+
+
+@pytest.mark.parametrize("dt", ["c128", "c64"])
+@pytest.mark.parametrize("strings", ["z", "xy"])
+def test_sweep_tables_kept_with_a_plan(dt, strings):
+    # one plan, several parameter vectors and states: with the tables kept from
+    # the first gradient (Z strings only) and without (strings with X and Y)
+    n = 13
+    g, npar = phase_circuit(n, 60, 77, parametric=True)
+    g = g + [{"op": "pauli_rot", "q": [1, 5, 12], "paulis": [3, 3, 3] if strings == "z" else [1, 2, 3], "slot": npar}]
+    npar += 1
+    obs = W.random_pauli_observable(n, 12, (1, 4), seed_key=(n, 9)) + [(0.4, [])]
+    scale = sum(abs(c) for c, _ in obs)
+    circ, o = Circuit.from_records(n, g), Observable(n, obs)
+    plan = Plan(circ, dt)
+    slots = [0, npar // 3, npar - 2, npar - 1]
+    for k in range(3):
+        theta = np.random.default_rng(k).uniform(-7.0, 7.0, npar)
+        psi, lam = State(n, dt), State(n, dt)
+        e, gr = adjoint_gradient(circ, theta, o, psi, lam, plan)
+        assert abs(e - O.energy(n, g, theta, obs)) <= RED_TOL[dt] * scale
+        ref = O.param_shift_grad(n, g, theta, obs, slots=slots)
+        assert np.max(np.abs(gr[slots] - ref)) <= RED_TOL[dt] * scale
