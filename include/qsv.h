@@ -386,11 +386,12 @@ int qsv_apply_observable(const qsv_state* in, const qsv_observable* o, qsv_state
  * forward pass (NULL = one launch per gate). grad: circuit nparams doubles,
  * overwritten; a slot used by several gates receives the sum of their
  * contributions. Gradients accumulate in double. Parametric multi-qubit Pauli
- * rotations (qsv_circuit_add_pauli_rotation) are differentiated too. From 12
- * (complex64) / 11 (complex128) qubits the reverse sweep runs in tile passes
- * whose tables live in psi's work buffer (allocated on first use, kept,
- * freed with the state); Pauli strings on more than 5 qubits keep the
- * per-gate sweep. Synchronises the stream. */
+ * rotations (qsv_circuit_add_pauli_rotation) are differentiated too. From 3
+ * qubits the reverse sweep runs in tile passes (register-resident from 9);
+ * its tables stay with the forward plan, or live in psi's work buffer
+ * (allocated on first use, kept, freed with the state). Pauli strings on more
+ * than 5 qubits keep the per-gate sweep. Where every gate is unitary, energy and
+ * gradient are divided by the norm that rounding left. Synchronises the stream. */
 int qsv_adjoint_gradient(const qsv_circuit* c, qsv_plan* forward_plan, const double* theta,
                          const qsv_observable* o, qsv_state* psi, qsv_state* lam,
                          double* energy, double* grad);

@@ -23,10 +23,6 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CFLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-fPIC", "-std=c++17",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # matrix-core results stay in ordinary VGPRs (the register tiles feed them
-    # straight back to vector code; accumulation registers would cost copies
-    # and occupancy)
-    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wno-unused-result", "-I" + os.path.join(HERE, "..", "include"),
 ]
 

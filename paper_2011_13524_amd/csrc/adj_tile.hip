@@ -270,11 +270,14 @@ template <typename R>
 int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T) {
   const int n = c->n;
   // complex64 states of at least one 2^12 tile (complex128: 2^11) run
-  // register-resident: 256 threads x 16 (8) amplitudes per state
+  // register-resident: 256 threads x 16 (8) amplitudes per state; smaller ones
+  // down to 9 qubits are one tile of 8 amplitudes per thread
   const int Lc = sizeof(R) == 4 ? 12 : 11;
   const int L = T.L = std::min(n, Lc);
-  const bool reg = T.reg = n >= Lc;
-  const SegCfg cfg{sizeof(R) == 4 ? 4 : 3, 8, sizeof(R) == 4};
+  const bool reg = T.reg = n >= 9;
+  const int RB = n >= Lc && sizeof(R) == 4 ? 4 : 3;
+  T.thread_bits = L - RB;
+  const SegCfg cfg{RB, T.thread_bits, sizeof(R) == 4};
   const int b = std::min(L, sizeof(R) == 4 ? 4 : 3);  // 128-byte contiguous runs
   const double utol = sizeof(R) == 4 ? 1e-9 : 2e-15;
   // reversed, daggered op list with gradient terms
@@ -616,6 +619,29 @@ void adjoint_cache_free(AdjCache* a) {
   delete a;
 }
 
+template <typename R>
+using AdjRegFn = void (*)(R*, R*, const TilePassDev*, int, const RegSegDev*, const RegHeadDev*, const RegOpDev*,
+                          const TileOpDev*, const PhaseEntDev*, const cx<R>*, const int*, double*, uint64_t, R, R);
+
+template <typename R, int TB>
+static AdjRegFn<R> adj_reg_small(int km) {
+  return km == 0 ? &k_adj_reg<R, 3, 0, TB> : (km <= 3 ? &k_adj_reg<R, 3, 3, TB> : &k_adj_reg<R, 3, 5, TB>);
+}
+
+// The sweep's kernel for register bits rb, thread bits tb and the widest dense op
+// (0: no general products).
+template <typename R>
+static AdjRegFn<R> adj_reg_fn(int rb, int tb, int km) {
+  constexpr int RBs = sizeof(R) == 4 ? 4 : 3;
+  if (tb == 6) return adj_reg_small<R, 6>(km);
+  if (tb == 7) return adj_reg_small<R, 7>(km);
+  if (rb < RBs) return adj_reg_small<R, 8>(km);
+  return km == 0   ? &k_adj_reg<R, RBs, 0, 8>
+         : km <= 2 ? &k_adj_reg<R, RBs, 2, 8>
+         : km <= 3 ? &k_adj_reg<R, RBs, 3, 8>
+                   : &k_adj_reg<R, RBs, 5, 8>;
+}
+
 // Reverse sweep by tile passes. On entry psi = psi_L, lam = H psi_L and energy =
 // <psi|lam>; on return both are uncomputed and rows[r] holds the gradient term of the r-th
 // parametric rotation counted from the end (T.row_slot maps rows to slots). vals:
@@ -638,14 +664,10 @@ int adjoint_backward_tiled(const AdjTables& T, std::vector<cd>& vals, AdjCache* 
   const int nrows = int(row_slot.size());
   const uint64_t tiles = dim(n - L);
   // register-resident passes: tile + gradient slots in LDS
-  const size_t reg_lds = (size_t(1) << L) * sizeof(cx<R>) + size_t(kAdjMaxRows) * (256 / 64) * sizeof(double);
-  constexpr int RBs = sizeof(R) == 4 ? 4 : 3;
+  const int nt = 1 << T.thread_bits;
+  const size_t reg_lds = (size_t(1) << L) * sizeof(cx<R>) + size_t(kAdjMaxRows) * (nt / 64) * sizeof(double);
   bool general = false;
   for (const TilePassDev& p : hp) general |= p.general != 0;
-  const void* reg_fn = !general    ? reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 0, 8>)
-                       : kmax <= 2   ? reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 2, 8>)
-                       : kmax <= 3 ? reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 3, 8>)
-                                   : reinterpret_cast<const void*>(&k_adj_reg<R, RBs, 5, 8>);
   // persistent grid: for the register sweep, eight rounds of the workgroups
   // the device holds at once (the variant's occupancy times the compute
   // units), so no round runs part-full and the last one is short (measured:
@@ -656,7 +678,8 @@ int adjoint_backward_tiled(const AdjTables& T, std::vector<cd>& vals, AdjCache* 
   uint64_t gmax = kAdjTileGrid;
   if (reg) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reg_fn, 256, reg_lds) != hipSuccess || per_cu < 1)
+    const AdjRegFn<R> fn = adj_reg_fn<R>(L - T.thread_bits, T.thread_bits, general ? kmax : 0);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, nt, reg_lds) != hipSuccess || per_cu < 1)
       per_cu = 1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, psi->device) != hipSuccess || cus < 1)
       cus = 256;
@@ -704,26 +727,18 @@ int adjoint_backward_tiled(const AdjTables& T, std::vector<cd>& vals, AdjCache* 
   hipLaunchKernelGGL(k_zero_doubles, dim3(256), dim3(256), 0, st, part, uint64_t(nrows) * G);
   {
     if (reg) {
-      const size_t lds = reg_lds;
       for (size_t pi = 0; pi < hp.size(); ++pi) {
         ProfScope ps("adjoint", 4.0 * sizeof(cx<R>) * double(dim(n)), st);
-#define QSV_ADJR_LAUNCH(KM)                                                                      \
-    hipLaunchKernelGGL((k_adj_reg<R, sizeof(R) == 4 ? 4 : 3, KM, 8>), dim3(G), dim3(256), lds, st, \
-                       static_cast<R*>(psi->ptr), static_cast<R*>(lam->ptr),                      \
-                       reinterpret_cast<const TilePassDev*>(tab + lo.pass), int(pi),                          \
-                       reinterpret_cast<const RegSegDev*>(tab + lo.segs),                            \
-                       reinterpret_cast<const RegHeadDev*>(tab + lo.heads),                          \
-                       reinterpret_cast<const RegOpDev*>(tab + lo.rops),                             \
-                       reinterpret_cast<const TileOpDev*>(tab + lo.ops),                             \
-                       reinterpret_cast<const PhaseEntDev*>(tab + lo.ents),                          \
-                       reinterpret_cast<const cx<R>*>(d),                                \
-                       reinterpret_cast<const int*>(tab + lo.prow), part, tiles,                     \
-                       R(pi == 0 ? energy : 0.0), R(pi + 1 == hp.size() ? energy : 0.0))
-        if (!hp[pi].general) QSV_ADJR_LAUNCH(0);
-        else if (kmax <= 2) QSV_ADJR_LAUNCH(2);
-        else if (kmax <= 3) QSV_ADJR_LAUNCH(3);
-        else QSV_ADJR_LAUNCH(5);
-#undef QSV_ADJR_LAUNCH
+        hipLaunchKernelGGL((adj_reg_fn<R>(L - T.thread_bits, T.thread_bits, hp[pi].general ? kmax : 0)), dim3(G),
+                           dim3(nt), reg_lds, st, static_cast<R*>(psi->ptr), static_cast<R*>(lam->ptr),
+                           reinterpret_cast<const TilePassDev*>(tab + lo.pass), int(pi),
+                           reinterpret_cast<const RegSegDev*>(tab + lo.segs),
+                           reinterpret_cast<const RegHeadDev*>(tab + lo.heads),
+                           reinterpret_cast<const RegOpDev*>(tab + lo.rops),
+                           reinterpret_cast<const TileOpDev*>(tab + lo.ops),
+                           reinterpret_cast<const PhaseEntDev*>(tab + lo.ents), reinterpret_cast<const cx<R>*>(d),
+                           reinterpret_cast<const int*>(tab + lo.prow), part, tiles, R(pi == 0 ? energy : 0.0),
+                           R(pi + 1 == hp.size() ? energy : 0.0));
         if (hipGetLastError() != hipSuccess) return fin(fail(QSV_EHIP, "register sweep launch failed"));
       }
     }

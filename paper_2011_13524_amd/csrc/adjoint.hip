@@ -149,14 +149,14 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
     if ((g.kind == Gate::ROTATION || g.kind == Gate::PAULI) && g.slot >= 0) ++nrot;
     if (g.kind == Gate::PAULI && g.targets.size() > 5) wide = true;
   }
-  // reverse sweep by register tile passes (both states streamed once per pass)
-  // wherever there is a full tile; smaller states take one launch per gate.
-  // Measured, 8-layer ansatz, per gate against passes: complex64 12 qubits 1.19
-  // and 0.48 ms, 16 qubits 1.77 and 0.84, 20 qubits 3.03 and 1.28; complex128 11
-  // qubits 1.27 and 0.63 ms, 20 qubits 5.08 and 1.32. At 11 qubits complex64,
-  // through the LDS sweep, both take 1.30 ms.
-  int tiled_min = sizeof(R) == 4 ? 12 : 11;
-  int tiled_must = tiled_min + 8;  // no per-gate sweep from here on
+  // reverse sweep by tile passes (both states streamed once per pass): in
+  // registers from 9 qubits, in LDS below; the smallest states keep one launch
+  // per gate. Measured, 8-layer ansatz, per gate against passes: complex64 3
+  // qubits 0.45 and 0.25 ms, 8 qubits 0.93 and 0.48, 9 qubits 0.95 and 0.20, 12
+  // qubits 1.27 and 0.30, 20 qubits 3.03 and 1.28; complex128 9 qubits 1.00 and
+  // 0.21 ms, 20 qubits 5.08 and 1.32.
+  int tiled_min = 3;
+  int tiled_must = sizeof(R) == 4 ? 20 : 19;  // no per-gate sweep from here on
   if (const char* e = std::getenv("QSV_ADJOINT_TILED_MIN")) tiled_min = tiled_must = std::atoi(e);  // testing
   AdjTables own;
   std::vector<cd> vals;
@@ -173,25 +173,31 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
   } else if (tiled) {
     vals.swap(own.vals);
   }
-  // E = Re <psi|lambda>
-  // the norm that rounding left is divided out where the circuit keeps it
+  // E = Re <psi|lambda>; the norm that rounding left is divided out where the circuit keeps it
   // exactly: it made up nearly all of the energy's error (24 qubits, 960
   // parameters, complex64: 0.6e-6 to 1.7e-6 with it, 0.4e-7 to 3e-7 without)
   double re = 0.0, norm2 = 1.0;
   if ((rc = inner_and_norm(psi, lam, &re, &norm2))) return rc;
   if (!(circuit_unitary(c) && norm2 > 0.0 && std::isfinite(norm2))) norm2 = 1.0;
   *energy = re / norm2;
+  // the register passes sweep lambda - E psi; the others are given it, and it is
+  // put back after them
+  const int AB = adj_blocks(N);
+  auto shift = [&](double e) {
+    hipLaunchKernelGGL((k_axpy<R>), dim3(AB), dim3(kAdjThreads), 0, st, static_cast<R*>(lam->ptr),
+                       static_cast<const R*>(psi->ptr), N, R(e));
+    return hipGetLastError() == hipSuccess ? QSV_OK : fail(QSV_EHIP, "lambda shift launch failed");
+  };
+  const bool in_pass = tiled && T.reg;
+  if (!in_pass && (rc = shift(-re / norm2))) return rc;
   if (tiled) {
     std::vector<double> rv;
     if ((rc = adjoint_backward_tiled<R>(T, vals, cache, n, re / norm2, psi, lam, rv))) return rc;
+    if (!in_pass && (rc = shift(re / norm2))) return rc;
     for (int i = 0; i < c->nparams; ++i) grad[i] = 0.0;
     for (size_t r = 0; r < rv.size(); ++r) grad[T.row_slot[r]] += rv[r] / norm2;
     return QSV_OK;
   }
-  // (on lambda - E psi, as in the tile passes; put back below)
-  const int AB = adj_blocks(N);
-  hipLaunchKernelGGL((k_axpy<R>), dim3(AB), dim3(kAdjThreads), 0, st, static_cast<R*>(lam->ptr),
-                     static_cast<const R*>(psi->ptr), N, R(-re / norm2));
   const int B = adj_blocks(N / 2);
   if ((rc = ensure_reduce_scratch(psi, size_t(nrot) * B + size_t(nrot) + 1))) return rc;
   double* partial = psi->red;
@@ -239,9 +245,7 @@ int adjoint_t(const qsv_circuit* c, qsv_plan* plan, const double* theta, const q
                               g.ctrl_vals.data(), int(g.controls.size()))))
       return rc;
   }
-  hipLaunchKernelGGL((k_axpy<R>), dim3(AB), dim3(kAdjThreads), 0, st, static_cast<R*>(lam->ptr),
-                     static_cast<const R*>(psi->ptr), N, R(re / norm2));
-  QSV_HIP_CHECK(hipGetLastError());
+  if ((rc = shift(re / norm2))) return rc;
   for (int i = 0; i < c->nparams; ++i) grad[i] = 0.0;
   if (nrot > 0) {
     hipLaunchKernelGGL(k_sum_rows, dim3(nrot), dim3(kAdjThreads), 0, st, partial, B, rows);

@@ -420,7 +420,7 @@ bool add_circuit(Tables& T, const qsv_circuit* c) {
     clear_error();
     ok = false;
   }
-  ok = ok && A.reg && A.kmax <= 2;
+  ok = ok && A.reg && A.thread_bits == kRegThreadBits && A.kmax <= 2;
   for (const TilePassDev& d : A.hp) ok = ok && d.seg_count > 0;
   if (ok) {
     MCirc C{};

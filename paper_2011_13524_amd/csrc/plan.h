@@ -267,6 +267,7 @@ struct DynVal {
 struct AdjTables {
   int L = 0, kmax = 1;
   bool reg = false;
+  int thread_bits = 8;  // register-resident passes
   std::vector<TilePassDev> hp;
   std::vector<TileOpDev> ho;
   SegBuild sb;

@@ -115,9 +115,10 @@ def test_parametric_phases_follow_theta_and_differentiate(dt, monkeypatch):
     assert abs(psi.store()[0] - 1.0) <= 10 * AMP_TOL[dt]
 
 
-@pytest.mark.parametrize("dt,n", [("c64", 11), ("c64", 12), ("c64", 13), ("c128", 10), ("c128", 11), ("c128", 12)])
+@pytest.mark.parametrize("dt,n", [("c64", 5), ("c64", 8), ("c64", 9), ("c64", 10), ("c64", 11), ("c64", 12), ("c64", 13),
+                                  ("c128", 6), ("c128", 8), ("c128", 9), ("c128", 10), ("c128", 11), ("c128", 12)])
 def test_gradients_around_the_smallest_full_tile(dt, n):
-    # one tile, two tiles, and the size below (one launch per gate); then with a
+    # every register shape, one tile and two, and the LDS sweep below; then with a
     # gate of more local controls than the passes take (the per-gate sweep does)
     rng = np.random.default_rng(n)
     g, npar = phase_circuit(n, 50, 5 + n, parametric=True)
