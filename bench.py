@@ -18,8 +18,8 @@ Extra legs (same JSON line):
                 500-term observable: adjoint gradient vs central finite
                 differences on the same kernels (FD timed on a sample of
                 parameters; both reported as gradient components per second)
-  batch_vqe     512 hardware-efficient-ansatz items of 12..18 qubits: one
-                persistent launch (graph replay, launch shape autotuned
+  batch_vqe     512 hardware-efficient-ansatz items of 12..18 qubits: tile
+                passes over all items (graph replay, launch shape autotuned
                 beforehand) vs one adjoint call per item
   random_26q    26-qubit Haar-1q + random-CZ circuit, fused vs unfused, and
                 the plan the autotuner picks (fusion width, tile shape)

@@ -399,14 +399,18 @@ int qsv_adjoint_gradient(const qsv_circuit* c, qsv_plan* forward_plan, const dou
 /* ---------------------------------------------------------------- batches */
 
 /* A batch of independent items (circuit, observable, parameters) whose
- * energies and adjoint gradients are computed by ONE persistent kernel launch:
- * each workgroup takes items from a device work queue (largest first) and runs
+ * energies and adjoint gradients are computed together. Items of 12 qubits and
+ * more run as register-resident tile passes over all items at once: one launch
+ * per round runs the next pass of every item, a workgroup per tile (distinct
+ * circuits are planned once, on the first run). The others -- fewer qubits, or
+ * Pauli rotations with X or Y factors -- share ONE persistent launch: each
+ * workgroup takes items from a device work queue (largest first) and runs
  * forward pass, lambda = O psi, energy and reverse sweep for its item with the
  * item's states in LDS when psi and lambda fit in 64 KiB, else in device
- * memory streamed through LDS tiles in passes (several gates per pass, as in
- * qsv_plan_fused). The launch is captured once as a HIP graph and replayed
- * by later runs (qsv_batch_set_graph). This serves the regime the paper motivates -- small circuits
- * evaluated many times, where per-call overhead dominates (section 5.1) --
+ * memory streamed through LDS tiles in passes. The launches are captured once
+ * as a HIP graph and replayed by later runs (qsv_batch_set_graph). This serves
+ * the regime the paper motivates -- small circuits evaluated many times, where
+ * per-call overhead dominates (section 5.1) --
  * with a design of this library's own. Items take 2..24 qubits; their gates
  * must be one-qubit gates, rotations, CZ or CNOT (other gates: QSV_EINVAL at
  * run). The batch copies circuits, observables and parameters when added. */
@@ -428,18 +432,18 @@ int qsv_batch_info(const qsv_batch* b, int* items, int* total_params);
 int qsv_batch_run(qsv_batch* b, qsv_dtype dtype, void* stream, double* energies, double* grads);
 
 /* Launch-shape autotuner for the batch: times `reps` (1..100) runs of the
- * batch on `stream` for each candidate -- LDS for psi + lambda per workgroup
- * of 64 KiB (complex64 items up to 12 qubits held in LDS, 2^12-amplitude
- * tiles otherwise) or 32 KiB (2^11 tiles, more workgroups per CU) times 512 or
- * 256 threads per workgroup -- after one untimed run each, and keeps the
+ * batch on `stream` for each candidate shape of the persistent launch (tile
+ * passes have one shape) -- LDS for psi + lambda per workgroup of 64 KiB (items
+ * in LDS up to 12 qubits in complex64, 2^12-amplitude tiles otherwise) or 32 KiB
+ * (2^11 tiles, more workgroups per CU) times 512 or 256 threads -- after one untimed run each, and keeps the
  * fastest for later runs. choice (may be NULL) receives int[2]: LDS KiB and
  * threads. Results do not depend on the shape beyond rounding order. Errors:
  * QSV_EINVAL (null or empty batch, reps out of range), QSV_EDTYPE, and those of
  * qsv_batch_run. */
 int qsv_batch_autotune(qsv_batch* b, qsv_dtype dtype, void* stream, int reps, int* choice);
 
-/* enable != 0 (the default): qsv_batch_run captures its launch (work-queue
- * reset kernel + persistent kernel) into a HIP graph on its first run for a
+/* enable != 0 (the default): qsv_batch_run captures its launches (those of
+ * the tile passes, and the work-queue reset + persistent kernel) into a HIP graph on its first run for a
  * dtype and replays that graph afterwards; 0: plain launches every run (and
  * the captured graph is released). Parameter uploads and result copies stay
  * outside the graph. Results are identical either way. */

@@ -445,7 +445,7 @@ def adjoint_gradient(circ: Circuit, theta, obs: Observable, psi: State, lam: Sta
 
 
 class Batch:
-    """Batched energies + adjoint gradients in one persistent launch (qsv_batch)."""
+    """Batched energies + adjoint gradients, all items together (qsv_batch)."""
 
     def __init__(self):
         h = _vp()
