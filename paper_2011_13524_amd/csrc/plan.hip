@@ -919,7 +919,8 @@ static int plan_create(const qsv_circuit* c, qsv_dtype dtype, int max_k, int til
   // 512-thread kernel would spill, and complex128 has no 512-thread shape)
   if ((dtype == QSV_C128 || max_k > 3) && TB == 9) TB = kRegThreadBits;
   // register bits: the rest of the tile; instantiated shapes (register bits,
-  // thread bits): complex64 (4, 9), (4, 8), (5, 8), (4, 7); complex128 (4, 8), (4, 7)
+  // thread bits): complex64 (4, 9), (4, 8), (5, 8), (4, 7); complex128 (4, 8), (4, 7);
+  // both, for states of one tile, (3, 6), (3, 7), (3, 8)
   // states of 9 to 11 qubits, one tile: three register bits, so that as many
   // wavefronts as the tile allows share its chain of gates (the LDS kernel, which
   // keeps 8 qubits and fewer, takes a barrier per block). Measured, 8-layer
@@ -928,7 +929,8 @@ static int plan_create(const qsv_circuit* c, qsv_dtype dtype, int max_k, int til
   // and 57 us.
   if (n < 12 && L == n && L >= 9 && TB == kRegThreadBits) TB = L - 3;
   const int RB = L - TB;
-  const bool rb_ok = RB == 4 || (RB == 3 && L == n && TB >= 6) || (dtype == QSV_C64 && RB == 5 && TB == 8);
+  const bool rb_ok = RB == 4 || (RB == 3 && L == n && TB >= 6 && TB <= kRegThreadBits) ||
+                     (dtype == QSV_C64 && RB == 5 && TB == 8);
   p->thread_bits = TB;
   p->reg_bits = (rb_ok && n >= L) ? RB : 0;
   p->circ_copy = *c;

@@ -177,3 +177,15 @@ def test_sweep_tables_kept_with_a_plan(dt, strings):
         assert abs(e - O.energy(n, g, theta, obs)) <= RED_TOL[dt] * scale
         ref = O.param_shift_grad(n, g, theta, obs, slots=slots)
         assert np.max(np.abs(gr[slots] - ref)) <= RED_TOL[dt] * scale
+
+
+@pytest.mark.parametrize("tb", ["7", "8", "9"])
+@pytest.mark.parametrize("n", [8, 9, 10, 11, 12])
+def test_one_tile_under_every_thread_bits_setting(n, tb, monkeypatch):
+    # shapes that are not compiled (9 thread bits at 12 qubits, 7 at 9) fall back
+    monkeypatch.setenv("QSV_TILE_THREAD_BITS", tb)
+    g, _ = phase_circuit(n, 40, 60 + n)
+    for dt in ("c64", "c128"):
+        s = State(n, dt)
+        apply_fused(s, Plan(Circuit.from_records(n, g), dt))
+        assert np.max(np.abs(s.store() - O.run_circuit(n, g))) <= AMP_TOL[dt]
