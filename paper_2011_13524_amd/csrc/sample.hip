@@ -40,9 +40,11 @@ struct ScanTree {
   int levels;
 };
 
+// |v|^2 with its rounding spelled out: the table's kernel and the draws have to
+// form the same value.
 template <typename R>
 __device__ __forceinline__ double scan_weight(cx<R> v) {
-  return double(v.re) * double(v.re) + double(v.im) * double(v.im);
+  return fma(double(v.re), double(v.re), double(v.im) * double(v.im));
 }
 
 // A chunk passes through LDS so that global reads and writes stay coalesced;
@@ -67,8 +69,9 @@ __device__ __forceinline__ double scan_chain(double* base) {
 }
 
 // Level 0, one workgroup per chunk (the last may be short): ends[t] = B_{t+1} of
-// its runs, sums[blockIdx.x] its total. Bound by the read of the state: 26 qubits complex64, 197 us with every value stored,
-// 116 us here (4.6 TB/s; 227 us with each thread reading its 16 entries itself).
+// its runs, sums[blockIdx.x] its total. Bound by the read of the state: 26 qubits
+// complex64, 197 us with every value stored, 116 us here (4.6 TB/s; 227 us with
+// each thread reading its 16 entries itself).
 template <typename R>
 __global__ void __launch_bounds__(kScanThreads)
     k_scan_amps(const R* __restrict__ psi, uint64_t count, double* __restrict__ ends, double* __restrict__ sums) {
