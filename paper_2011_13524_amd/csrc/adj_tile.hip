@@ -24,6 +24,7 @@ namespace qsv {
 
 constexpr int kAdjTileThreads = 256;
 constexpr int kAdjTileGrid = 2048;
+constexpr int kAdjRegMin = 9;  // qubits from which the passes are register-resident
 
 // TileOpDev with kind 2 = parametric rotation exp(i t P/2) seen by the reverse
 // sweep: k = Pauli id, lt[0] = local target or -1, gq[0] = global qubit (Z on
@@ -274,7 +275,7 @@ int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T) {
   // down to 9 qubits are one tile of 8 amplitudes per thread
   const int Lc = sizeof(R) == 4 ? 12 : 11;
   const int L = T.L = std::min(n, Lc);
-  const bool reg = T.reg = n >= 9;
+  const bool reg = T.reg = n >= kAdjRegMin;
   const int RB = n >= Lc && sizeof(R) == 4 ? 4 : 3;
   T.thread_bits = L - RB;
   const SegCfg cfg{RB, T.thread_bits, sizeof(R) == 4};
@@ -286,6 +287,11 @@ int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T) {
   std::vector<cd> m;
   for (int gi = int(c->gates.size()) - 1; gi >= 0; --gi) {
     const Gate& g = c->gates[gi];
+    // (without theta: only values that the parameters fill in later, as DynVals)
+    const bool zstr = reg && g.kind == Gate::PAULI && g.targets.size() > 1 &&
+                      std::all_of(g.paulis.begin(), g.paulis.end(), [](int p) { return p == 3; });
+    if (!theta && g.kind != Gate::MATRIX && g.slot >= 0 && !zstr && !(reg && g.kind == Gate::ROTATION))
+      return fail(QSV_EINVAL, "sweep tables of this circuit need its parameters");
     const double t = g.kind == Gate::MATRIX ? 0.0 : (g.slot >= 0 ? (theta ? theta[g.slot] : 0.0) : g.fixed_angle);
     if (g.kind == Gate::PAULI && g.slot >= 0) {
       // gradient term -Im<lambda|P|psi> of exp(i t P/2) (its own op), then the
@@ -326,8 +332,7 @@ int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T) {
       ops.push_back(gr);
       continue;
     }
-    if (reg && g.kind == Gate::PAULI && g.targets.size() > 1 &&
-        std::all_of(g.paulis.begin(), g.paulis.end(), [](int p) { return p == 3; })) {
+    if (zstr) {
       BOp z;
       z.kind = 5;
       z.sub = PH_ZSTR;
@@ -598,15 +603,11 @@ void adjoint_values(const AdjTables& T, const double* theta, std::vector<cd>& va
 
 template <typename R>
 AdjCache* adjoint_cache(qsv_plan* plan, const qsv_circuit* c) {
-  if (!same_circuit(*c, plan->circ_copy)) return nullptr;
+  if (c->n < kAdjRegMin || !same_circuit(*c, plan->circ_copy)) return nullptr;
   if (!plan->adj) {
     plan->adj = new AdjCache();
-    for (const Gate& g : c->gates)
-      if (g.kind == Gate::PAULI && g.slot >= 0 &&
-          (g.targets.size() < 2 || std::any_of(g.paulis.begin(), g.paulis.end(), [](int p) { return p != 3; })))
-        return nullptr;
     if (adjoint_tables<R>(c, nullptr, plan->adj->T) != QSV_OK) clear_error();
-    else plan->adj->usable = plan->adj->T.reg;
+    else plan->adj->usable = true;
   }
   return plan->adj->usable ? plan->adj : nullptr;
 }

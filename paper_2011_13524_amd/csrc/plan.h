@@ -263,7 +263,8 @@ struct DynVal {
 };
 
 // Tables of a reverse sweep (host side; the values for the theta given, or
-// with theta null the constant ones).
+// with theta null the constant ones: register-resident sweeps only, and refused
+// where a value other than those of DynVal depends on theta).
 struct AdjTables {
   int L = 0, kmax = 1;
   bool reg = false;
@@ -289,8 +290,9 @@ struct AdjCache {
   int device = -1;
 };
 // The tables of c's reverse sweep kept with `plan` (made on the first call), or
-// null where they cannot be: c is not the plan's circuit, or values other than
-// rotations' and Z strings' depend on theta.
+// null where they cannot be: c is not the plan's circuit, its sweep is not
+// register-resident, or values other than rotations' and Z strings' depend on
+// theta.
 template <typename R>
 AdjCache* adjoint_cache(qsv_plan* plan, const qsv_circuit* c);
 void adjoint_cache_free(AdjCache* a);
