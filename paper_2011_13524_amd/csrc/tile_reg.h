@@ -342,6 +342,13 @@ __device__ __forceinline__ void reg_apply(cx<R>* v, int key, const cx<R>* m, con
         : QSV_AB(c, 0), QSV_AB(c, 1), QSV_AB(c, 2), QSV_AB(c, 3), [m] "s"(rot)                             \
         : "scc");                                                                                          \
   }                                                                                                        \
+  /* bits 0 .. 2 of 8 elements */                                                                          \
+  __device__ __forceinline__ void rot8(cx<T>* v, const cx<T>* c, uint32_t rot) {                           \
+    asm(QSV_ROT8(F, N, 0, "1", "2") QSV_ROT8(F, N, 1, "3", "4") QSV_ROT8(F, N, 2, "5", "6")                \
+        : QSV_E8(v)                                                                                        \
+        : QSV_AB(c, 0), QSV_AB(c, 1), QSV_AB(c, 2), [m] "s"(rot)                                           \
+        : "scc");                                                                                          \
+  }                                                                                                        \
   /* one bit of a 16- or 8-element array (the reverse sweep evaluates gradients between them) */           \
   template <int P>                                                                                         \
   __device__ __forceinline__ void rot16_bit(cx<T>* v, cx<T> f, uint32_t rot) {                             \
@@ -634,12 +641,17 @@ __device__ __forceinline__ void rot_layer(cx<R>* v, uint32_t rot, const cx<R>* _
   cx<R> c[RB];
 #pragma unroll
   for (int p = 0; p < RB; ++p) c[p] = coef[p];
-  rot16(v, c, rot);
-  if constexpr (RB == 5) {
-    rot16(v + 16, c, rot);
-    const uint32_t r4 = (rot >> 1) & 0x808u;  // bit 4 in the place of bit 3
-    rot_pairs8(v, v + 16, c[4], r4);
-    rot_pairs8(v + 8, v + 24, c[4], r4);
+  static_assert(RB >= 3 && RB <= 5, "8, 16 or 32 elements");
+  if constexpr (RB == 3) {
+    rot8(v, c, rot);
+  } else {
+    rot16(v, c, rot);
+    if constexpr (RB == 5) {
+      rot16(v + 16, c, rot);
+      const uint32_t r4 = (rot >> 1) & 0x808u;  // bit 4 in the place of bit 3
+      rot_pairs8(v, v + 16, c[4], r4);
+      rot_pairs8(v + 8, v + 24, c[4], r4);
+    }
   }
 }
 
