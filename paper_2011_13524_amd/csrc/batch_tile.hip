@@ -97,17 +97,13 @@ __global__ void __launch_bounds__(256) k_item_vals(MArgs a, const double* __rest
   cx<double>* v = vals + I.val[dir] + d.voff;
   const double t = d.sgn * theta[I.theta + d.slot];
   if (d.type == 0) {
-    double h = remainder(0.5 * t, 2.0 * M_PI);
-    double sg = 1.0;
-    if (h > 0.5 * M_PI) {
-      h -= M_PI;
-      sg = -1.0;
-    } else if (h < -0.5 * M_PI) {
-      h += M_PI;
+    double s, c, sg = 1.0;
+    sincos(0.5 * t, &s, &c);
+    if (c < 0.0) {
+      s = -s;
+      c = -c;
       sg = -1.0;
     }
-    double s, c;
-    sincos(h, &s, &c);
     v[0] = {s / (1.0 + c), -s};
     v[1] = {sg, 0.0};
   } else {
