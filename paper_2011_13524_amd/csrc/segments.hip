@@ -25,7 +25,8 @@ void rotation_shears(double t, cd* out) {
 bool is_unitary2(const cd* u, double tol) {
   const double n0 = u[0].re * u[0].re + u[0].im * u[0].im + u[2].re * u[2].re + u[2].im * u[2].im;
   const double n1 = u[1].re * u[1].re + u[1].im * u[1].im + u[3].re * u[3].re + u[3].im * u[3].im;
-  if (!(n0 > 0.0) || !std::isfinite(n0) || !(std::fabs(n0 - n1) <= tol * n0)) return false;
+  // (where squares of the entries underflow the test says nothing)
+  if (!(n0 >= 1e-250) || !std::isfinite(n0) || !(std::fabs(n0 - n1) <= tol * n0)) return false;
   const double xr = u[0].re * u[1].re + u[0].im * u[1].im + u[2].re * u[3].re + u[2].im * u[3].im;
   const double xi = u[0].re * u[1].im - u[0].im * u[1].re + u[2].re * u[3].im - u[2].im * u[3].re;
   return std::fabs(xr) + std::fabs(xi) <= tol * n0;
