@@ -301,6 +301,17 @@ void adjoint_values(const AdjTables& T, const double* theta, std::vector<cd>& va
 
 constexpr int kAdjMaxRows = 64;  // gradient rows per pass (LDS slots)
 
+// Structure of one gate: targets/controls after control extraction and
+// whether the remaining target matrix is diagonal (value-independent for
+// rotations: Z rotations are diagonal for every angle).
+struct GateInfo {
+  std::vector<int> targets, controls, ctrl_vals;
+  std::vector<cd> mat;  // extracted matrix (MATRIX gates only)
+  bool diagonal = false;
+  bool exchange = false;  // extracted matrix is Pauli X on one target
+  uint64_t qubits = 0;
+};
+
 // A fused block: gates (indices into the circuit) applied in order, acting on
 // `qubits` (ascending). Single-gate blocks keep the gate's control structure.
 struct Block {
@@ -347,6 +358,7 @@ struct qsv_plan {
   int L = 12, b = 5;
   const qsv_circuit* circ = nullptr;  // borrowed structure snapshot below
   qsv_circuit circ_copy;
+  std::vector<qsv::GateInfo> info;  // of circ_copy's gates
   std::vector<qsv::Block> blocks;
   std::vector<qsv::Lop> lops;  // the blocks as elementary ops
   int nvals = 0;               // host values of the lops

@@ -101,21 +101,10 @@ uint64_t qmask(const std::vector<int>& qs) {
 
 std::vector<int> mask_list(uint64_t m) {
   std::vector<int> v;
-  for (int q = 0; q < 64; ++q)
-    if (m >> q & 1) v.push_back(q);
+  v.reserve(size_t(__builtin_popcountll(m)));
+  for (; m; m &= m - 1) v.push_back(__builtin_ctzll(m));
   return v;
 }
-
-// Structure of one gate: targets/controls after control extraction and
-// whether the remaining target matrix is diagonal (value-independent for
-// rotations: Z rotations are diagonal for every angle).
-struct GateInfo {
-  std::vector<int> targets, controls, ctrl_vals;
-  std::vector<cd> mat;  // extracted matrix (MATRIX gates only)
-  bool diagonal = false;
-  bool exchange = false;  // extracted matrix is Pauli X on one target
-  uint64_t qubits = 0;
-};
 
 GateInfo analyse(const Gate& g) {
   GateInfo gi;
@@ -259,7 +248,8 @@ std::vector<uint8_t> commute_masks(const Gate& g, const GateInfo& gi, int n) {
 static int build_plan(qsv_plan* p) {
   const qsv_circuit& C = p->circ_copy;
   const int n = C.n;
-  std::vector<GateInfo> info(C.gates.size());
+  std::vector<GateInfo>& info = p->info;
+  info.resize(C.gates.size());
   for (size_t i = 0; i < C.gates.size(); ++i) info[i] = analyse(C.gates[i]);
 
   // stage 2: merge
@@ -395,7 +385,7 @@ static void build_lops(qsv_plan* p) {
           else it->second.push_back(gi);
           continue;
         }
-        const GateInfo I = analyse(g);
+        const GateInfo& I = p->info[size_t(gi)];
         if (I.targets.size() == 1 && I.controls.empty()) {
           auto it = std::find_if(one.begin(), one.end(), [&](const auto& x) { return x.first == I.targets[0]; });
           if (it == one.end()) one.push_back({I.targets[0], {gi}});
@@ -450,7 +440,7 @@ static void build_lops(qsv_plan* p) {
       bool single = true, unitary = true;
       for (int gi : B.gates) {
         const Gate& g = C.gates[size_t(gi)];
-        const GateInfo I = analyse(g);
+        const GateInfo& I = p->info[size_t(gi)];
         if (I.targets.size() != 1 || !I.controls.empty()) single = unitary = false;
         if (g.kind == Gate::MATRIX && unitary && !is_unitary2(I.mat.data(), tol)) unitary = false;
         if (I.diagonal) {
@@ -629,17 +619,15 @@ static void plan_values(const qsv_plan* p, const double* theta, std::vector<cd>&
   // matrix of a block's targets (its controls, if any, are apart)
   auto block_matrix = [&](const Block& B) {
     if (B.gates.size() == 1) {
-      const Gate& g = C.gates[size_t(B.gates[0])];
-      extracted_matrix(g, analyse(g), theta, acc);
+      extracted_matrix(C.gates[size_t(B.gates[0])], p->info[size_t(B.gates[0])], theta, acc);
       return;
     }
     const int D = 1 << B.targets.size();
     acc.assign(size_t(D) * D, cd{0, 0});
     for (int i = 0; i < D; ++i) acc[size_t(i) * D + i] = {1, 0};
     for (int gidx : B.gates) {
-      const Gate& g = C.gates[size_t(gidx)];
-      const GateInfo gi = analyse(g);
-      extracted_matrix(g, gi, theta, gm);
+      const GateInfo& gi = p->info[size_t(gidx)];
+      extracted_matrix(C.gates[size_t(gidx)], gi, theta, gm);
       embed(gm, gi, B.targets, full);
       matmul(full, acc, D, tmp);  // later gate on the left
       acc.swap(tmp);
@@ -659,7 +647,7 @@ static void plan_values(const qsv_plan* p, const double* theta, std::vector<cd>&
         v[0] = v[1] = {1, 0};
         for (int gi : l.gates) {
           const Gate& g = C.gates[size_t(gi)];
-          if (g.kind == Gate::MATRIX) extracted_matrix(g, analyse(g), theta, gm);
+          if (g.kind == Gate::MATRIX) extracted_matrix(g, p->info[size_t(gi)], theta, gm);
           else gate_matrix(g, theta, gm);
           v[0] = cmul(gm[0], v[0]);
           v[1] = cmul(gm[3], v[1]);

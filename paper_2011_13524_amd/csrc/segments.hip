@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <functional>
 
 #include "plan.h"
 #include "tile_reg.h"
@@ -65,6 +66,38 @@ void unitary_to_rotation(const cd* u, cd* out) {
 
 namespace {
 
+// A set of places 0 .. n - 1, as bits.
+struct PlaceSet {
+  std::vector<uint64_t> w;
+  int count = 0;
+  void reset(size_t n) {
+    w.assign((n + 63) / 64, 0);
+    count = 0;
+  }
+  bool empty() const { return count == 0; }
+  void insert(int at) {
+    uint64_t& x = w[size_t(at) / 64];
+    count += int(~x >> (at & 63) & 1);
+    x |= uint64_t(1) << (at & 63);
+  }
+  void erase(int at) {
+    uint64_t& x = w[size_t(at) / 64];
+    count -= int(x >> (at & 63) & 1);
+    x &= ~(uint64_t(1) << (at & 63));
+  }
+  int first() const {  // (not empty)
+    size_t k = 0;
+    while (!w[k]) ++k;
+    return int(64 * k) + __builtin_ctzll(w[k]);
+  }
+  std::vector<int> list() const {
+    std::vector<int> v;
+    for (size_t k = 0; k < w.size(); ++k)
+      for (uint64_t m = w[k]; m; m &= m - 1) v.push_back(int(64 * k) + __builtin_ctzll(m));
+    return v;
+  }
+};
+
 // One pass of the scheduler below: the remaining ops that a pass can take, in
 // order. With `grow`, the local set takes the qubits of the ops in order while
 // it has room (at most L), else it is fixed.
@@ -73,15 +106,17 @@ struct PassTrial {
   int gain = 0;  // ops taken other than phases
 };
 
-// lists: also fill take / left (execution order, remaining ops).
+// lists: also fill take / left (execution order, remaining ops). free_diag: there
+// are diagonal ops other than phases, which any pass takes.
 PassTrial try_pass(const std::vector<PassOp>& ops, const std::vector<int>& rem, uint64_t local, bool grow, int L,
-                   uint64_t all, int max_rows, std::vector<int>* take, std::vector<int>* left) {
+                   uint64_t all, int max_rows, bool free_diag, std::vector<int>* take, std::vector<int>* left) {
   PassTrial t;
   uint64_t defer_nd = 0, defer_dg = 0;  // qubits of the deferred ops
   int rows = 0;
   std::vector<int> wait;  // phases that nothing taken needs yet
   const bool lists = take != nullptr, count = max_rows < (1 << 29);
-  for (size_t k = 0; k < rem.size(); ++k) {
+  size_t k = 0;
+  for (; k < rem.size(); ++k) {
     const int oi = rem[k];
     const PassOp& o = ops[size_t(oi)];
     bool ok = !((o.nd & (defer_nd | defer_dg)) | (o.dg & defer_nd));
@@ -114,29 +149,88 @@ PassTrial try_pass(const std::vector<PassOp>& ops, const std::vector<int>& rem, 
     if (lists) left->push_back(oi);
     defer_nd |= o.nd;
     defer_dg |= o.dg;
-    if (!lists && (defer_nd & all) == all) break;  // nothing later can run
+    // nothing later can run: every qubit is held back, or every local one is and
+    // ops that are not phases act on a local qubit (at the end of a list, phases
+    // run for their own sake only in a pass that takes nothing else)
+    const uint64_t held = free_diag ? defer_nd : (defer_nd | defer_dg);
+    if ((held & (free_diag || grow ? all : local)) == (free_diag || grow ? all : local) && (!lists || !take->empty())) {
+      ++k;
+      break;
+    }
   }
   t.local = local;
   if (lists) {
+    left->insert(left->end(), rem.begin() + long(k), rem.end());
     // phases that only later passes need wait for those; at the end of the
     // circuit, or when nothing else can run, they run here
     if (left->empty() || take->empty()) {
-      size_t k = 0;
+      size_t j = 0;
       for (int w : wait) {
         if (rows + ops[size_t(w)].rows <= max_rows) {
           rows += ops[size_t(w)].rows;
           take->push_back(w);
         } else {
-          wait[k++] = w;
+          wait[j++] = w;
         }
       }
-      wait.resize(k);
+      wait.resize(j);
     }
+    const long mid = long(left->size());
     left->insert(left->end(), wait.begin(), wait.end());
-    std::sort(left->begin(), left->end());
+    std::inplace_merge(left->begin(), left->begin() + mid, left->end());
   }
   return t;
 }
+
+// The gain of try_pass for a fixed local set, over the ops that bear on it: a phase
+// on one qubit without a gradient row holds back nothing that what it waits for does
+// not. Phases with rows are on one qubit (plain), so those that wait are counted
+// per qubit.
+struct GainOps {
+  std::vector<PassOp> ops;
+  bool plain = true;
+  void fill(const std::vector<PassOp>& from, const std::vector<int>& rem) {
+    ops.clear();
+    for (int oi : rem) {
+      const PassOp& o = from[size_t(oi)];
+      const bool one = (o.dg & (o.dg - 1)) == 0;
+      if (!o.lazy || !one || o.rows) ops.push_back(o);
+      plain = plain && (!o.lazy || one || !o.rows);
+    }
+  }
+  template <bool COUNT>
+  int gain(uint64_t local, uint64_t all, bool free_diag, int max_rows) const {
+    uint64_t defer_nd = 0, defer_dg = 0;
+    const uint64_t stop = free_diag ? all : local;
+    int g = 0, rows = 0;
+    int wait[64];
+    if (COUNT) std::fill(wait, wait + 64, 0);
+    for (const PassOp& o : ops) {
+      bool ok = !((o.nd & (defer_nd | defer_dg)) | (o.dg & defer_nd) | (o.local & ~local));
+      if (ok && o.lazy) {
+        if (COUNT && o.rows) wait[__builtin_ctzll(o.dg)] += o.rows;
+        continue;
+      }
+      if (COUNT && ok) {
+        int r = rows + o.rows;
+        for (uint64_t m = o.nd; m; m &= m - 1) r += wait[__builtin_ctzll(m)];
+        ok = r <= max_rows;
+        if (ok) {
+          rows = r;
+          for (uint64_t m = o.nd; m; m &= m - 1) wait[__builtin_ctzll(m)] = 0;
+        }
+      }
+      if (ok) {
+        g += o.weight;
+        continue;
+      }
+      defer_nd |= o.nd;
+      defer_dg |= o.dg;
+      if (((free_diag ? defer_nd : (defer_nd | defer_dg)) & stop) == stop) break;
+    }
+    return g;
+  }
+};
 
 }  // namespace
 
@@ -148,15 +242,25 @@ int schedule_passes(const std::vector<PassOp>& ops, int n, int L, int b, int max
   for (size_t i = 0; i < ops.size(); ++i) rem[i] = int(i);
   const uint64_t all = (n >= 64) ? ~0ull : ((uint64_t(1) << n) - 1);
   const uint64_t low = (b >= 64) ? ~0ull : ((uint64_t(1) << b) - 1);
-  const int budget = 100;  // trial exchanges per pass (each scans the ops in reach: about 2 us)
+  const int budget = 100;  // trial exchanges per pass (each scans the ops in reach: under 1 us)
+  const bool count = max_rows < (1 << 29);
+  bool free_diag = false;
+  for (const PassOp& o : ops) free_diag = free_diag || (!o.lazy && o.nd == 0);
+  GainOps reach;
   while (!rem.empty()) {
-    PassTrial best = try_pass(ops, rem, low, true, L, all, max_rows, nullptr, nullptr);
-    for (int q = 0; q < n && __builtin_popcountll(best.local) < L; ++q) best.local |= uint64_t(1) << q;
+    PassTrial best;
+    best.local = all;
     if (n > L) {
+      best = try_pass(ops, rem, low, true, L, all, max_rows, free_diag, nullptr, nullptr);
+      for (int q = 0; q < n && __builtin_popcountll(best.local) < L; ++q) best.local |= uint64_t(1) << q;
+      reach.fill(ops, rem);
       auto consider = [&](uint64_t local) {
-        const PassTrial t = try_pass(ops, rem, local, false, L, all, max_rows, nullptr, nullptr);
-        if (t.gain <= best.gain) return false;
-        best.gain = t.gain;
+        const int gain =
+            !count          ? reach.gain<false>(local, all, free_diag, max_rows)
+            : reach.plain   ? reach.gain<true>(local, all, free_diag, max_rows)
+                            : try_pass(ops, rem, local, false, L, all, max_rows, free_diag, nullptr, nullptr).gain;
+        if (gain <= best.gain) return false;
+        best.gain = gain;
         best.local = local;
         return true;
       };
@@ -184,7 +288,7 @@ int schedule_passes(const std::vector<PassOp>& ops, int n, int L, int b, int max
       }
     }
     std::vector<int> take, left;
-    try_pass(ops, rem, best.local, false, L, all, max_rows, &take, &left);
+    try_pass(ops, rem, best.local, false, L, all, max_rows, free_diag, &take, &left);
     if (take.empty()) return fail(QSV_EINVAL, "planner made no progress (tile too small)");
     pass_ops.push_back(std::move(take));
     pass_local.push_back(best.local);
@@ -273,18 +377,57 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
       need[i] = 0;
     }
   }
-  std::vector<std::vector<int>> preds(nops);
-  for (int j = 0; j < nops; ++j)
-    for (int i = 0; i < j; ++i)
-      if ((nd[i] & (nd[j] | dg[j])) | (dg[i] & nd[j])) preds[j].push_back(i);
+  // Direct predecessors: per local bit, a non-diagonal op follows the diagonal ops
+  // since the last non-diagonal one, and that one; a diagonal op follows the last
+  // non-diagonal one. Every other op that op i has to follow comes before one of
+  // these, and each state below (executed, folded, done) holds for an op only if
+  // it holds for all that the op follows: the direct ones tell.
+  // preds of op i: pred[pred_at[i] .. pred_at[i + 1]), and the other way round.
+  std::vector<int> pred, pred_at(nops + 1, 0), succ, succ_at(nops + 2, 0);
+  {
+    std::vector<int> last_nd(L, -1);
+    std::vector<std::vector<int>> since(L);
+    for (int i = 0; i < nops; ++i) {
+      const size_t p0 = pred.size();
+      for (uint32_t m = nd[i] | dg[i]; m; m &= m - 1) {
+        const int q = __builtin_ctz(m);
+        if (nd[i] >> q & 1) {
+          if (since[q].empty() && last_nd[q] >= 0) pred.push_back(last_nd[q]);
+          pred.insert(pred.end(), since[q].begin(), since[q].end());
+          since[q].clear();
+          last_nd[q] = i;
+        } else {
+          if (last_nd[q] >= 0) pred.push_back(last_nd[q]);
+          since[q].push_back(i);
+        }
+      }
+      std::sort(pred.begin() + long(p0), pred.end());
+      pred.erase(std::unique(pred.begin() + long(p0), pred.end()), pred.end());
+      pred_at[i + 1] = int(pred.size());
+    }
+    succ.resize(pred.size());
+    for (int q : pred) ++succ_at[q + 2];
+    for (int i = 0; i < nops; ++i) succ_at[i + 2] += succ_at[i + 1];
+    for (int i = 0; i < nops; ++i)
+      for (int k = pred_at[i]; k < pred_at[i + 1]; ++k) succ[size_t(succ_at[pred[size_t(k)] + 1]++)] = i;
+  }
+  struct Range {
+    const int *b, *e;
+    const int* begin() const { return b; }
+    const int* end() const { return e; }
+  };
+  auto succs = [&](int i) { return Range{succ.data() + succ_at[i], succ.data() + succ_at[i + 1]}; };
+  auto preds = [&](int i) { return Range{pred.data() + pred_at[i], pred.data() + pred_at[i + 1]}; };
+  auto npreds = [&](int i) { return pred_at[i + 1] - pred_at[i]; };
   std::vector<char> foldable(nops, 0);
   for (int i = 0; i < nops; ++i) {
     const TileOpDev& o = ho[d.op_begin + i];
     foldable[i] = o.kind == 0 && o.k == 1 && o.xswap && o.gcm == 0 && __builtin_popcount(o.lcm) <= 1;
   }
 
-  // list scheduling into segments; state 1: executed or folded into an
-  // earlier re-map, 2: folded into the re-map after the current segment
+  // list scheduling into segments: an op executes in a segment when all that it
+  // follows was executed, or folded into an earlier re-map; it folds into the
+  // re-map after the segment when all that was executed or folded
   struct Seg {
     uint32_t regs = 0;  // register positions the ops need (+ IO constraints)
     bool io = false;
@@ -294,7 +437,13 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
     bool xwave = false;
   };
   std::vector<Seg> segs;
-  std::vector<char> st(nops, 0);
+  // predecessors still to come (wait_fold) and those or only just folded (wait_exec)
+  std::vector<int> wait_exec(nops), wait_fold(nops);
+  std::vector<int> ready, later;  // ops that can be placed, in order
+  for (int i = 0; i < nops; ++i) {
+    wait_exec[i] = wait_fold[i] = npreds(i);
+    if (npreds(i) == 0) ready.push_back(i);
+  }
   int left = nops;
   do {
     Seg s;
@@ -302,31 +451,43 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
     s.io = first;
     s.regs = first ? io_reg : 0u;
     const uint32_t forbid = first ? io_lane : 0u;
-    for (bool progress = true; progress;) {
-      progress = false;
-      for (int i = 0; i < nops; ++i) {
-        if (st[i]) continue;
-        bool exec_ready = true, fold_ready = true;
-        for (int q : preds[i]) {
-          exec_ready = exec_ready && st[q] == 1;
-          fold_ready = fold_ready && st[q] != 0;
+    // (one sweep in order: an op that becomes ready comes after the one that made
+    // it so, and the registers in use only grow)
+    std::make_heap(ready.begin(), ready.end(), std::greater<int>());
+    auto next_ready = [&](int j) {
+      ready.push_back(j);
+      std::push_heap(ready.begin(), ready.end(), std::greater<int>());
+    };
+    later.clear();
+    while (!ready.empty()) {
+      std::pop_heap(ready.begin(), ready.end(), std::greater<int>());
+      const int i = ready.back();
+      ready.pop_back();
+      if (foldable[i]) {
+        s.fold.push_back(i);
+        for (int j : succs(i))
+          if (--wait_fold[j] == 0 && foldable[j]) next_ready(j);
+      } else {
+        const uint32_t u = s.regs | need[i];
+        if ((need[i] & forbid) || __builtin_popcount(u) > RB) {
+          later.push_back(i);
+          continue;
         }
-        if (foldable[i] && fold_ready) {
-          st[i] = 2;
-          s.fold.push_back(i);
-        } else {
-          const uint32_t u = s.regs | need[i];
-          if (!exec_ready || (need[i] & forbid) || __builtin_popcount(u) > RB) continue;
-          s.regs = u;
-          s.ops.push_back(i);
-          st[i] = 1;
+        s.regs = u;
+        s.ops.push_back(i);
+        for (int j : succs(i)) {
+          --wait_exec[j];
+          --wait_fold[j];
+          if ((foldable[j] ? wait_fold[j] : wait_exec[j]) == 0) next_ready(j);
         }
-        --left;
-        progress = true;
       }
+      --left;
     }
     if (s.ops.empty() && s.fold.empty() && !first) return fail(QSV_EINVAL, "internal: segment scheduling stalled");
-    for (int i : s.fold) st[i] = 1;
+    for (int i : s.fold)
+      for (int j : succs(i))
+        if (--wait_exec[j] == 0 && !foldable[j]) later.push_back(j);
+    ready.swap(later);
     segs.push_back(std::move(s));
   } while (left > 0);
   {
@@ -418,7 +579,34 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
     if (segs[k - 1].xwave) pre[k] = 1;
   }
 
+  // emission: an op's predecessors not done yet, and those that do not even wait
+  // (phases); the current segment's ops that can be emitted, by their place in it
   std::vector<char> done(nops, 0), waiting(nops, 0);
+  std::vector<int> undone(nops), unheld(nops), place_of(nops, -1);
+  for (int i = 0; i < nops; ++i) undone[i] = unheld[i] = npreds(i);
+  PlaceSet can_phase, can_rot, can_other, wanting;
+  auto sort_in = [&](int li) {
+    const int at = place_of[li], kind = ho[d.op_begin + li].kind;
+    if (undone[li] == 0) {
+      wanting.erase(at);
+      (kind == 5 ? can_phase : kind == 4 ? can_rot : can_other).insert(at);
+    } else if (unheld[li] == 0) {
+      wanting.insert(at);
+    }
+  };
+  auto set_waiting = [&](int li) {
+    waiting[li] = 1;
+    for (int j : succs(li))
+      if (--unheld[j] == 0 && place_of[j] >= 0) sort_in(j);
+  };
+  auto set_done = [&](int li) {
+    if (done[li]) return;
+    done[li] = 1;
+    for (int j : succs(li)) {
+      if (!waiting[li]) --unheld[j];
+      if ((--undone[j] == 0 || unheld[j] == 0) && place_of[j] >= 0) sort_in(j);
+    }
+  };
   d.general = 0;
   std::vector<int> pend;     // phases waiting for an op that needs them
   std::vector<int> rot_src;  // values of the pass's rotations (their signs)
@@ -605,7 +793,7 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
         out.ents.push_back(x.e);
       }
       if (r.flags) out_rops.push_back(r);
-      for (int li : list) done[li] = 1;
+      for (int li : list) set_done(li);
     };
     // Emission: phases wait (pend) until an op that does not commute with
     // them is due; then every waiting phase that touches a register bit goes
@@ -647,7 +835,7 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
           const uint32_t i = ((uint32_t(g) >> p) << (p + 1)) | (uint32_t(g) & ((1u << p) - 1));
           if ((i & cm) == cv) r.xch |= 256u << g;
         }
-        done[li] = 1;
+        set_done(li);
         return QSV_OK;
       }
       d.general = 1;
@@ -723,17 +911,8 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
         o.moff = r.moff;  // the LDS form reads the same pool
       }
       out_rops.push_back(r);
-      done[li] = 1;
+      set_done(li);
       return QSV_OK;
-    };
-    auto blocked_by = [&](int li) {  // 0 ready, 1 only waiting phases are missing, 2 not ready
-      int r = 0;
-      for (int q : preds[li])
-        if (!done[q]) {
-          if (!waiting[q]) return 2;
-          r = 1;
-        }
-      return r;
     };
     auto flush = [&](const std::vector<int>& for_ops, bool all) {
       uint32_t t = regmask;
@@ -743,26 +922,23 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
       pend.swap(keep);
       if (!list.empty()) emit_phase(list);
     };
-    std::vector<int> todo = s.ops;
-    while (!todo.empty()) {
-      std::vector<int> rots, other, wanting, rest;
-      bool moved = false;
-      for (int li : todo) {
-        const TileOpDev& o = ho[d.op_begin + li];
-        const int st_ = blocked_by(li);
-        if (st_ == 0 && o.kind == 5) {
-          pend.push_back(li);
-          waiting[li] = 1;
-          moved = true;
-          continue;
-        }
-        if (st_ == 0) (o.kind == 4 ? rots : other).push_back(li);
-        if (st_ == 1) wanting.push_back(li);
-        rest.push_back(li);
-      }
-      todo.swap(rest);
-      if (moved) continue;
-      if (!rots.empty()) {
+    for (size_t k = 0; k < s.ops.size(); ++k) place_of[s.ops[k]] = int(k);
+    for (PlaceSet* x : {&can_phase, &can_rot, &can_other, &wanting}) x->reset(s.ops.size());
+    for (int li : s.ops) sort_in(li);
+    size_t emitted = 0;  // (phases: once they wait)
+    auto take = [&](PlaceSet& from) {
+      const int li = s.ops[size_t(from.first())];
+      from.erase(from.first());
+      place_of[li] = -1;
+      ++emitted;
+      return li;
+    };
+    while (emitted < s.ops.size()) {
+      if (!can_phase.empty()) {
+        const int li = take(can_phase);
+        pend.push_back(li);
+        set_waiting(li);
+      } else if (!can_rot.empty()) {
         // one op per register bit
         if (!open_op(true)) {
           out_rops.push_back(RegOpDev{});
@@ -770,6 +946,8 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
         }
         RegOpDev& r = out_rops.back();
         r.roff = pool_take(RB);
+        std::vector<int> rots;
+        for (int at : can_rot.list()) rots.push_back(s.ops[size_t(at)]);
         for (int li : rots) {
           const TileOpDev& o = ho[d.op_begin + li];
           const int p = regidx[o.lt[0]];
@@ -782,28 +960,29 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
           }
           out.recs.push_back({0, r.roff + p, o.moff, 1, {}});
           rot_src.push_back(o.moff);
-          done[li] = 1;
+          can_rot.erase(place_of[li]);
+          place_of[li] = -1;
+          ++emitted;
+          set_done(li);
         }
-      } else if (!other.empty()) {
-        const int rc = emit_old(other[0]);
+      } else if (!can_other.empty()) {
+        const int rc = emit_old(take(can_other));
         if (rc) return rc;
       } else if (!wanting.empty()) {
-        flush(wanting, false);
-      } else if (!todo.empty()) {
+        std::vector<int> want;
+        for (int at : wanting.list()) want.push_back(s.ops[size_t(at)]);
+        flush(want, false);
+      } else {
         return fail(QSV_EINVAL, "internal: segment emission stalled");
       }
-      size_t k = 0;
-      for (int li : todo)
-        if (!done[li]) todo[k++] = li;
-      todo.resize(k);
     }
     {
       // ops folded into the next re-map: the phases before them are due here
       bool due = false;
       for (int li : s.fold)
-        for (int q : preds[li]) due |= waiting[q] && !done[q];
+        for (int q : preds(li)) due |= waiting[q] && !done[q];
       if (due) flush(s.fold, false);
-      for (int li : s.fold) done[li] = 1;
+      for (int li : s.fold) set_done(li);
     }
     if (&s == &segs.back()) flush({}, true);
     sd.op_count = int(out_rops.size()) - sd.op_begin;
