@@ -161,53 +161,61 @@ __device__ __forceinline__ void adj_super(const RegHeadDev& hd, const RegOpDev& 
 
 // and the others.
 template <typename R, int RB, int KMAX, int TB>
-__device__ __forceinline__ void adj_general(const RegOpDev& op, cx<R> (&v)[2][1 << RB], const RegSegDev& S,
+__device__ __forceinline__ void adj_general(const RegHeadDev& hd, const RegOpDev& op, cx<R> (&v)[2][1 << RB], const RegSegDev& S,
                                             const ThrMask<TB>& tm, uint32_t tau, uint64_t base, Swz<sizeof(R) == 4 ? 5 : 4> sw, char* smem,
                                             const TileOpDev* __restrict__ lops, const cx<R>* __restrict__ pool, int L,
                                             double* wslot) {
   constexpr int NR = 1 << RB;
-  const cx<R>* m = pool + op.moff;
-  if ((base & op.gcm) != op.gcv) return;  // non-local controls: uniform per tile
-  if (op.kind == 8) {
-    // Pauli-string gradient: psi staged in LDS in this segment's layout; the
-    // partner x ^ f of element i is at its address XOR pf_lds (the swizzle is
-    // linear over XOR and the tile starts at LDS address 0)
-    const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
-    __syncthreads();  // (a preceding cross-wave re-map's reads are done)
-#pragma unroll
-    for (int i = 0; i < NR; ++i) ms.put(smem, i, v[0][i]);
-    __syncthreads();
-    typedef R R2 __attribute__((ext_vector_type(2)));
-    typedef __attribute__((address_space(3))) R2 lds_r2;
-    const uint32_t tpar = uint32_t(__popc(tau & op.pz_thr) + __popcll(base & op.pz_glob)) & 1u;
-    double sr = 0.0, si = 0.0;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const R2 av = *reinterpret_cast<lds_r2*>(uintptr_t(reinterpret_cast<uintptr_t>(ms.at(smem, i)) ^ op.pf_lds));
-      const cx<R> c = v[1][i];
-      const double wr = double(c.re) * av.x + double(c.im) * av.y;
-      const double wi = double(c.re) * av.y - double(c.im) * av.x;
-      const bool neg = ((uint32_t(__popc(uint32_t(i) & op.pz_reg)) ^ tpar) & 1u) != 0;
-      sr += neg ? -wr : wr;
-      si += neg ? -wi : wi;
-    }
-    __syncthreads();  // every read done before the LDS tile is written again
-    add_row<TB>(neg_im_phase(sr, si, op.pph), wslot, op.aux[0], tau);
-    return;
-  }
-  if (op.kind == 3) {
-    const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
-    __syncthreads();  // (a preceding cross-wave re-map's reads are done)
-    adj_lds_op<R, RB, TB, KMAX>(v[0], ms, smem, lops[op.lop], pool, L, base, sw);
-    adj_lds_op<R, RB, TB, KMAX>(v[1], ms, smem, lops[op.lop], pool, L, base, sw);
-    return;
-  }
+  const cx<R>* m = pool + hd.moff;
+  int key = int(hd.xch);  // (dense products without controls need the head alone, see reg_general)
+  uint32_t cm = 0, cv = 0;
+  bool lane = true;
   cx<R> gtab[4];
-  int a = op.p1, bb = op.p2;
-  if (op.kind == 2) diag_table<R>(op, m, tau, base, gtab, a, bb);
-  const bool lane = (tau & op.ti_cm) == op.ti_cv;
-  reg_apply<R, NR>(v[0], op.key, m, gtab, op.ri_cm, op.ri_cv, lane);
-  reg_apply<R, NR>(v[1], op.key, m, gtab, op.ri_cm, op.ri_cv, lane);
+  if (!(hd.flags & 1u)) {
+    if ((base & op.gcm) != op.gcv) return;  // non-local controls: uniform per tile
+    if (op.kind == 8) {
+      // Pauli-string gradient: psi staged in LDS in this segment's layout; the
+      // partner x ^ f of element i is at its address XOR pf_lds (the swizzle is
+      // linear over XOR and the tile starts at LDS address 0)
+      const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
+      __syncthreads();  // (a preceding cross-wave re-map's reads are done)
+#pragma unroll
+      for (int i = 0; i < NR; ++i) ms.put(smem, i, v[0][i]);
+      __syncthreads();
+      typedef R R2 __attribute__((ext_vector_type(2)));
+      typedef __attribute__((address_space(3))) R2 lds_r2;
+      const uint32_t tpar = uint32_t(__popc(tau & op.pz_thr) + __popcll(base & op.pz_glob)) & 1u;
+      double sr = 0.0, si = 0.0;
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const R2 av = *reinterpret_cast<lds_r2*>(uintptr_t(reinterpret_cast<uintptr_t>(ms.at(smem, i)) ^ op.pf_lds));
+        const cx<R> c = v[1][i];
+        const double wr = double(c.re) * av.x + double(c.im) * av.y;
+        const double wi = double(c.re) * av.y - double(c.im) * av.x;
+        const bool neg = ((uint32_t(__popc(uint32_t(i) & op.pz_reg)) ^ tpar) & 1u) != 0;
+        sr += neg ? -wr : wr;
+        si += neg ? -wi : wi;
+      }
+      __syncthreads();  // every read done before the LDS tile is written again
+      add_row<TB>(neg_im_phase(sr, si, op.pph), wslot, op.aux[0], tau);
+      return;
+    }
+    if (op.kind == 3) {
+      const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
+      __syncthreads();  // (a preceding cross-wave re-map's reads are done)
+      adj_lds_op<R, RB, TB, KMAX>(v[0], ms, smem, lops[op.lop], pool, L, base, sw);
+      adj_lds_op<R, RB, TB, KMAX>(v[1], ms, smem, lops[op.lop], pool, L, base, sw);
+      return;
+    }
+    int a = op.p1, b = op.p2;
+    if (op.kind == 2) diag_table<R>(op, m, tau, base, gtab, a, b);
+    key = op.key;
+    cm = op.ri_cm;
+    cv = op.ri_cv;
+    lane = (tau & op.ti_cm) == op.ti_cv;
+  }
+  reg_apply<R, NR>(v[0], key, m, gtab, cm, cv, lane);
+  reg_apply<R, NR>(v[1], key, m, gtab, cm, cv, lane);
 }
 
 // One pass over the tiles [g0, gend) of one workgroup; its partial of row r goes
@@ -306,7 +314,7 @@ __device__ __forceinline__ void adj_pass(R* __restrict__ psi, R* __restrict__ la
         next = heads[++oi];
         if constexpr (KMAX > 0) {
           if ((hd.flags >> 24) != 11) {
-            adj_general<R, RB, KMAX, TB>(op, v, *S, tm, tau, base, sw, smem, lops, pool, L, &slot[0][wave]);
+            adj_general<R, RB, KMAX, TB>(hd, op, v, *S, tm, tau, base, sw, smem, lops, pool, L, &slot[0][wave]);
             continue;
           }
         }

@@ -148,8 +148,8 @@ struct RegOpDev {
 // What every op of a segment needs of its RegOpDev (same index), in one cache
 // line that the kernels read one op ahead. A spare record follows the last.
 struct alignas(64) RegHeadDev {
-  uint32_t flags;  // RegOpDev::flags; bits 24-31: the kind
-  uint32_t rot, xch;
+  uint32_t flags;  // RegOpDev::flags; bits 24-31: the kind (kinds 0, 1: flag 1 without controls)
+  uint32_t rot, xch;  // (kinds 0, 1 without controls: xch is the key)
   int moff, roff;
   int ent_begin, ent_count, row_begin, row_count;
   uint32_t h_rsg[kRegMaxH];

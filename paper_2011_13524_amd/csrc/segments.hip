@@ -1046,7 +1046,11 @@ std::vector<RegHeadDev> op_heads(const SegBuild& sb) {
     h.flags = r.flags | uint32_t(r.kind) << 24;
     h.rot = r.rot;
     h.xch = r.xch;
-    h.moff = r.kind == 11 ? r.moff : 0;
+    h.moff = r.moff;
+    if (r.kind <= 1 && r.gcm == 0 && r.ti_cm == 0 && r.ri_cm == 0) {
+      h.flags |= 1;
+      h.xch = uint32_t(r.key);
+    }
     h.roff = r.roff;
     h.ent_begin = r.ent_begin;
     h.ent_count = r.ent_count;

@@ -792,31 +792,41 @@ __device__ __forceinline__ void reg_super(const RegHeadDev& hd, const RegOpDev& 
 // nothing; ops on LDS (kind 3) go through the tile in LDS; controls on thread
 // bits are per lane.
 template <typename R, int RB, int KMAX, int TB>
-__device__ __forceinline__ void reg_general(const RegOpDev& op, cx<R> (&v)[1][1 << RB], const RegSegDev& S,
+__device__ __forceinline__ void reg_general(const RegHeadDev& hd, const RegOpDev& op, cx<R> (&v)[1][1 << RB], const RegSegDev& S,
                                             const ThrMask<TB>& tm, uint32_t tau, uint64_t base, Swz<sizeof(R) == 4 ? 5 : 4> sw,
                                             char* smem, const TileOpDev* __restrict__ lops,
                                             const cx<R>* __restrict__ pool, int L) {
   constexpr int NR = 1 << RB;
-  const cx<R>* m = pool + op.moff;
-  if ((base & op.gcm) != op.gcv) return;  // non-local controls: uniform per tile
-  if (op.kind == 3) {
-    const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
-    __syncthreads();  // (a preceding cross-wave re-map's reads are done)
-#pragma unroll
-    for (int i = 0; i < NR; ++i) ms.put(smem, i, v[0][i]);
-    __syncthreads();
-    lds_op<R, KMAX>(reinterpret_cast<cx<R>*>(smem), lops[op.lop], pool, L, base, sw);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NR; ++i) v[0][i] = ms.get(smem, i);
-    __syncthreads();
-    return;
-  }
+  // (dense products without controls need the head alone, which is there already:
+  // nothing waits for the record before the matrix is read)
+  const cx<R>* m = pool + hd.moff;
+  int key = int(hd.xch);
+  uint32_t cm = 0, cv = 0;
+  bool lane = true;
   cx<R> g[4];
-  int a = op.p1, bb = op.p2;
-  if (op.kind == 2) diag_table<R>(op, m, tau, base, g, a, bb);
-  const bool lane = (tau & op.ti_cm) == op.ti_cv;
-  reg_apply<R, NR>(v[0], op.key, m, g, op.ri_cm, op.ri_cv, lane);
+  if (!(hd.flags & 1u)) {
+    if ((base & op.gcm) != op.gcv) return;  // non-local controls: uniform per tile
+    if (op.kind == 3) {
+      const LdsMap<R, RB> ms(S.get_reg, tm.map(0u, S.tcol) >> 16);
+      __syncthreads();  // (a preceding cross-wave re-map's reads are done)
+#pragma unroll
+      for (int i = 0; i < NR; ++i) ms.put(smem, i, v[0][i]);
+      __syncthreads();
+      lds_op<R, KMAX>(reinterpret_cast<cx<R>*>(smem), lops[op.lop], pool, L, base, sw);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NR; ++i) v[0][i] = ms.get(smem, i);
+      __syncthreads();
+      return;
+    }
+    int a = op.p1, b = op.p2;
+    if (op.kind == 2) diag_table<R>(op, m, tau, base, g, a, b);
+    key = op.key;
+    cm = op.ri_cm;
+    cv = op.ri_cv;
+    lane = (tau & op.ti_cm) == op.ti_cv;
+  }
+  reg_apply<R, NR>(v[0], key, m, g, cm, cv, lane);
 }
 
 // Register budget (the launch bound's second argument: wavefronts per SIMD):
@@ -858,8 +868,13 @@ __device__ __forceinline__ uint64_t pass_base(const TilePassDev& P, uint32_t g) 
 }
 
 // KMAX 0: passes of kind-11 ops only. Workgroups are persistent: workgroup b
-// takes tiles b, b + grid, ... and issues the loads of its next tile before it
-// computes on the current one. LDS (32 KiB tiles in granules of 1280 bytes)
+// takes tiles b, b + grid, ... and (KMAX 0) issues the loads of its next tile before
+// it computes on the current one. General products need those registers: with
+// the read-ahead they spilled. Measured at 24 qubits complex64 with it and without:
+// six layers of dense two-qubit blocks 905 and 864 us, of controlled unitaries 881
+// and 804, of non-unitary one-qubit matrices 1150 and 918, two layers of dense
+// four-qubit blocks 1277 and 1108 (heads alone read for uncontrolled products
+// included: reg_general). LDS (32 KiB tiles in granules of 1280 bytes)
 // holds four workgroups on a compute unit, four wavefronts per SIMD, so a
 // wavefront has 128 registers: 32 amplitude words, 32 of the next tile. Bound
 // by vector issue: at 30 qubits complex64 (15 passes of the layered circuit,
@@ -888,15 +903,20 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
     th0 |= S0->gcol_t[k] & on;
     thL |= SL->gcol_t[k] & on;
   }
-  cx<R> v[1][NR], pf[NR];
+  constexpr bool AHEAD = KMAX == 0;
+  cx<R> v[1][NR], pf[AHEAD ? NR : 1];
   uint64_t base = pass_base(P, g);
-  tile_io<R, RB, false>(psi, pf, base | th0, *S0);
+  if constexpr (AHEAD) tile_io<R, RB, false>(psi, pf, base | th0, *S0);
   for (;;) {
-#pragma unroll
-    for (int i = 0; i < NR; ++i) v[0][i] = pf[i];
     const uint32_t gn = g + step;  // (ntiles <= 2^27: no overflow)
     const uint64_t nbase = gn < ntiles ? pass_base(P, gn) : 0;
-    if (gn < ntiles) tile_io<R, RB, false>(psi, pf, nbase | th0, *S0);
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) v[0][i] = pf[i];
+      if (gn < ntiles) tile_io<R, RB, false>(psi, pf, nbase | th0, *S0);
+    } else {
+      tile_io<R, RB, false>(psi, v[0], base | th0, *S0);
+    }
     const RegSegDev* S = S0;
     int oi = S->op_begin;
     RegHeadDev next = heads[oi];  // the next op's head, read one op ahead
@@ -933,7 +953,7 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
         next = heads[++oi];
         if constexpr (KMAX > 0) {
           if ((hd.flags >> 24) != 11) {
-            reg_general<R, RB, KMAX, TB>(op, v, *S, tm, tau, base, sw, smem, lops, pool, L);
+            reg_general<R, RB, KMAX, TB>(hd, op, v, *S, tm, tau, base, sw, smem, lops, pool, L);
             continue;
           }
         }
