@@ -89,7 +89,7 @@ __device__ __forceinline__ void grad_layer(cx<R> (&v)[2][1 << RB], uint32_t rot,
 // on a thread bit or a non-local qubit takes the plain sum with its sign.
 template <typename R, int RB, int TB>
 __device__ __forceinline__ void phase_rows(const cx<R> (&v)[2][1 << RB], const RegHeadDev& hd,
-                                           const PhaseEntDev* __restrict__ ents, double* wslot, uint32_t tau,
+                                           const RegOpDev& op, const PhaseEntDev* __restrict__ ents, double* wslot, uint32_t tau,
                                            uint64_t base) {
   constexpr int NR = 1 << RB;
   R w[NR], s[RB + 1];
@@ -105,7 +105,7 @@ __device__ __forceinline__ void phase_rows(const cx<R> (&v)[2][1 << RB], const R
     for (int r = 0; r < (1 << b); ++r) w[r] += w[r | (1 << b)];
   }
   s[RB] = w[0];
-  for (int e = hd.row_begin; e < hd.row_begin + hd.row_count; ++e) {
+  for (int e = op.row_begin; e < op.row_begin + hd.row_count; ++e) {
     const PhaseEntDev E = ents[e];
     R x = s[RB];
 #pragma unroll
@@ -151,7 +151,7 @@ template <typename R, int RB, int TB>
 __device__ __forceinline__ void adj_super(const RegHeadDev& hd, const RegOpDev& op, cx<R> (&v)[2][1 << RB],
                                           uint32_t tau, uint64_t base, const PhaseEntDev* __restrict__ ents,
                                           const cx<R>* __restrict__ pool, double* wslot) {
-  if (hd.flags & 8u) phase_rows<R, RB, TB>(v, hd, ents, wslot, tau, base);
+  if (hd.flags & 8u) phase_rows<R, RB, TB>(v, hd, op, ents, wslot, tau, base);
   phase_apply<R, RB, 2>(v, hd, op, ents, pool, tau, base);
   grad_layer<R, RB, TB>(v, su(hd.rot), op, pool + hd.roff, wslot, tau);
   const uint64_t xm = exchange_mask(hd.xch, op, tau, base);

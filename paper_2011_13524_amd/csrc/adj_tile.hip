@@ -563,6 +563,7 @@ struct AdjLayout {
 
 static AdjLayout adj_pack(const AdjTables& T, std::vector<char>* out) {
   const std::vector<RegHeadDev> heads = op_heads(T.sb);
+  const std::vector<PhaseEntDev> ents = op_entries(T.sb);
   AdjLayout o{};
   size_t at = 0;
   auto put = [&](size_t& off, const void* p, size_t bytes) {
@@ -576,7 +577,7 @@ static AdjLayout adj_pack(const AdjTables& T, std::vector<char>* out) {
   put(o.ops, T.ho.data(), T.ho.size() * sizeof(TileOpDev));
   put(o.segs, T.sb.segs.data(), T.sb.segs.size() * sizeof(RegSegDev));
   put(o.rops, T.sb.rops.data(), T.sb.rops.size() * sizeof(RegOpDev));
-  put(o.ents, T.sb.ents.data(), T.sb.ents.size() * sizeof(PhaseEntDev));
+  put(o.ents, ents.data(), ents.size() * sizeof(PhaseEntDev));
   put(o.heads, heads.data(), heads.size() * sizeof(RegHeadDev));
   put(o.prow, T.prow.data(), T.prow.size() * sizeof(int));
   o.bytes = at;

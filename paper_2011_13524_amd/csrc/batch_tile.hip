@@ -177,30 +177,36 @@ __global__ void __launch_bounds__(256) k_item_one(MArgs a, int nitems, cx<R>* __
   if (i < nitems) states[a.items[i].psi] = {R(1), R(0)};
 }
 
+// The tables come as pointers of their own that nothing else aliases, so that they
+// are read through the scalar cache.
+#define QSV_ITEM_TABLES                                                                                       \
+  const MItem *__restrict__ items, const MCirc *__restrict__ circs, const TilePassDev *__restrict__ passes,   \
+      const RegSegDev *__restrict__ segs, const RegHeadDev *__restrict__ heads, const RegOpDev *__restrict__ rops, \
+      const TileOpDev *__restrict__ ops, const PhaseEntDev *__restrict__ ents, const MWork *__restrict__ work, int round
 template <typename R, int KMAX>
 __global__ void __launch_bounds__(1 << kRegThreadBits, (tile_waves_per_simd<R, 4>()))
-    k_item_tile(MArgs a, const MWork* __restrict__ work, int round, cx<R>* __restrict__ states, const cx<R>* __restrict__ pool) {
+    k_item_tile(QSV_ITEM_TABLES, cx<R>* __restrict__ states, const cx<R>* __restrict__ pool) {
   extern __shared__ __align__(16) char smem[];
   const MWork w = work[blockIdx.x];
-  const MItem& I = a.items[w.item];
-  tile_pass<R, 4, KMAX, kRegThreadBits>(reinterpret_cast<R*>(states + I.psi), a.passes[a.circs[I.circ].pass[0] + round],
-                                        w.g, I.cols[0], I.ntiles[0], a.segs, a.heads, a.rops, a.ops, a.ents,
-                                        pool + I.pool[0], smem);
+  const MItem& I = items[w.item];
+  tile_pass<R, 4, KMAX, kRegThreadBits>(reinterpret_cast<R*>(states + I.psi), passes[circs[I.circ].pass[0] + round], w.g,
+                                        I.cols[0], I.ntiles[0], segs, heads, rops, ops, ents, pool + I.pool[0], smem);
 }
 
 template <typename R, int KMAX>
 __global__ void __launch_bounds__(1 << kRegThreadBits)
-    k_item_adj(MArgs a, const MWork* __restrict__ work, int round, cx<R>* __restrict__ states, const cx<R>* __restrict__ pool,
+    k_item_adj(QSV_ITEM_TABLES, cx<R>* __restrict__ states, const cx<R>* __restrict__ pool, const int* __restrict__ prow,
                double* __restrict__ part, const double* __restrict__ energies) {
   extern __shared__ __align__(16) char smem[];
   const MWork w = work[blockIdx.x];
-  const MItem& I = a.items[w.item];
+  const MItem& I = items[w.item];
   const uint64_t per = I.ntiles[1] / I.cols[1];  // (both powers of two)
   adj_pass<R, sizeof(R) == 4 ? 4 : 3, KMAX, kRegThreadBits>(
-      reinterpret_cast<R*>(states + I.psi), reinterpret_cast<R*>(states + I.lam),
-      a.passes[a.circs[I.circ].pass[1] + round], w.g * per, (w.g + 1) * per, a.segs, a.heads, a.rops, a.ops, a.ents,
-      pool + I.pool[1], a.prow, part + I.part, I.cols[1], w.g, round == 0 ? R(energies[I.index]) : R(0), R(0), smem);
+      reinterpret_cast<R*>(states + I.psi), reinterpret_cast<R*>(states + I.lam), passes[circs[I.circ].pass[1] + round],
+      w.g * per, (w.g + 1) * per, segs, heads, rops, ops, ents, pool + I.pool[1], prow, part + I.part, I.cols[1], w.g,
+      round == 0 ? R(energies[I.index]) : R(0), R(0), smem);
 }
+#undef QSV_ITEM_TABLES
 
 // lambda = H psi on kLamAmps amplitudes per workgroup, with the energy's
 // partial. Per group of equal flip mask, a term's sign is the parity of (x & z):
@@ -369,6 +375,8 @@ struct Tables {
       H.general[dir].push_back(char(p.general != 0));
       p.op_begin += op0;
       p.seg_begin += seg0;
+      p.rop_begin += rop0;
+      p.ent_begin += ent0;
       p.row_begin += row0;
       passes.push_back(p);
     }
@@ -553,6 +561,7 @@ int batch_tiles_build(const std::vector<BatchTileItem>& all, BatchTiles** out, s
     if (dir == 0) launch(2, 0, false);
   }
   const std::vector<RegHeadDev> heads = op_heads(T.sb);
+  const std::vector<PhaseEntDev> ents = op_entries(T.sb);
   t->nitems = int(items.size());
   t->nparams = int(param_item.size());
   t->psi_total = psi_total;
@@ -568,7 +577,7 @@ int batch_tiles_build(const std::vector<BatchTileItem>& all, BatchTiles** out, s
   const Part parts[] = {QSV_PART(items, a.items),         QSV_PART(T.circs, a.circs),
                         QSV_PART(T.passes, a.passes),     QSV_PART(T.ops, a.ops),
                         QSV_PART(T.sb.segs, a.segs),      QSV_PART(T.sb.rops, a.rops),
-                        QSV_PART(heads, a.heads),         QSV_PART(T.sb.ents, a.ents),
+                        QSV_PART(heads, a.heads),         QSV_PART(ents, a.ents),
                         QSV_PART(T.prow, a.prow),         QSV_PART(T.recs, a.recs),
                         QSV_PART(T.comps, a.comps),       QSV_PART(T.elem_rec, a.elem_rec),
                         QSV_PART(T.dyn, a.dyn),           QSV_PART(T.slot_begin, a.slot_begin),
@@ -639,23 +648,22 @@ int batch_tiles_launch(const BatchTiles* t, const double* theta, double* energie
   }
   hipLaunchKernelGGL((k_item_zero<R>), dim3(2048), dim3(256), 0, st, states, t->psi_total);
   hipLaunchKernelGGL((k_item_one<R>), dim3((ni + 255) / 256), dim3(256), 0, st, t->args, t->nitems, states);
+  const MArgs& a = t->args;
   for (const BatchTiles::Launch& l : t->launches) {
     const MWork* w = t->d_work + l.work;
     const dim3 g(l.count);
-    if (l.dir == 0 && !l.general)
-      hipLaunchKernelGGL((k_item_tile<R, 0>), g, dim3(nt), lds_f, st, t->args, w, l.round, states, pool);
-    else if (l.dir == 0)
-      hipLaunchKernelGGL((k_item_tile<R, 2>), g, dim3(nt), lds_f, st, t->args, w, l.round, states, pool);
-    else if (l.dir == 2) {
-      hipLaunchKernelGGL((k_item_lam<R>), g, dim3(kLamThreads), 0, st, t->args, w, states, t->d_epart);
-      hipLaunchKernelGGL(k_item_energy, dim3(ni), dim3(64), 0, st, t->args, t->d_epart, energies,
-                         t->d_norms);
-    } else if (!l.general)
-      hipLaunchKernelGGL((k_item_adj<R, 0>), g, dim3(nt), lds_r, st, t->args, w, l.round, states, pool, t->d_part,
-                         energies);
-    else
-      hipLaunchKernelGGL((k_item_adj<R, 2>), g, dim3(nt), lds_r, st, t->args, w, l.round, states, pool, t->d_part,
-                         energies);
+    if (l.dir == 2) {
+      hipLaunchKernelGGL((k_item_lam<R>), g, dim3(kLamThreads), 0, st, a, w, states, t->d_epart);
+      hipLaunchKernelGGL(k_item_energy, dim3(ni), dim3(64), 0, st, a, t->d_epart, energies, t->d_norms);
+    } else if (l.dir == 0) {
+      const auto fn = l.general ? &k_item_tile<R, 2> : &k_item_tile<R, 0>;
+      hipLaunchKernelGGL(fn, g, dim3(nt), lds_f, st, a.items, a.circs, a.passes, a.segs, a.heads, a.rops, a.ops, a.ents, w,
+                         l.round, states, pool);
+    } else {
+      const auto fn = l.general ? &k_item_adj<R, 2> : &k_item_adj<R, 0>;
+      hipLaunchKernelGGL(fn, g, dim3(nt), lds_r, st, a.items, a.circs, a.passes, a.segs, a.heads, a.rops, a.ops, a.ents, w,
+                         l.round, states, pool, a.prow, t->d_part, energies);
+    }
   }
   if (t->nparams)
     hipLaunchKernelGGL(k_item_grads, dim3(unsigned(t->nparams + 3) / 4), dim3(256), 0, st, t->args, t->nparams, t->d_part,

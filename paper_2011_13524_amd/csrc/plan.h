@@ -65,6 +65,8 @@ struct TilePassDev {
   // multiplied by when it is stored (the sign the pass's rotations left), -1: none
   int scale_off;
   int general;  // the pass holds ops other than kind 11 (selects the kernel)
+  // register-resident execution: the pass's ops, entries and pool values
+  int rop_begin, rop_count, ent_begin, ent_count, pool_begin, pool_count;
 };
 
 // Register-resident tiles: the 2^L tile is spread over 2^TB threads holding
@@ -119,9 +121,12 @@ struct RegOpDev {
                         // with a gradient (reverse sweep)
   uint32_t xch;         // kind 11: exchange of the pairs of one register bit (one-hot), bits 8-23: the
                         // pairs whose register bits match the controls
-  int ent_begin, ent_count;  // kind 11: entries of the thread's factor (PhaseEntDev kinds 0-2)
+  // kind 11: entries of the thread's factor: ent_count of PhaseEntDev kind 0, whose
+  // pairs of values follow each other from pool offset ent_moff, then ent_cz of kind 2
+  int ent_begin, ent_count, ent_cz, ent_moff;
   int row_begin, row_count;  // kind 11: gradient rows (kind 4)
-  int h_begin[kRegMaxH], h_count[kRegMaxH];  // kind 11: string factors (kind 3) of pattern h
+  // kind 11: string factors (kind 3) of pattern h, their values from h_moff
+  int h_begin[kRegMaxH], h_count[kRegMaxH], h_moff[kRegMaxH];
   uint32_t h_rsg[kRegMaxH];  // bit r: the sign of element r in pattern h
   // kind 11: elements with register bit a set change sign when the parity of
   // (thread index & tm[a]) and (tile base & gm[a]) is odd
@@ -151,23 +156,28 @@ struct alignas(64) RegHeadDev {
   uint32_t flags;  // RegOpDev::flags; bits 24-31: the kind (kinds 0, 1: flag 1 without controls)
   uint32_t rot, xch;  // (kinds 0, 1 without controls: xch is the key)
   int moff, roff;
-  int ent_begin, ent_count, row_begin, row_count;
+  int ent_begin, ent_moff;
+  uint32_t ent_counts;  // kind 0, << 16 kind 2
+  int row_count;
   uint32_t h_rsg[kRegMaxH];
   uint32_t tm01, tm23, tm4;  // tm[], 16 bits each
 };
 
 // A factor of a phase that depends on the thread or the tile. par(t, g) is the
 // parity of (thread index & t) and (tile base & g). Kinds in this order:
-//   0 every element times pool[moff + par(tm, gm)]
-//   1 every element times c + i s (-1)^par(tm, gm), (c, s) = pool[moff]
+//   0 every element times the par(tm, gm)-th of the entry's two values
 //   2 every element times (-1)^(par(tm, gm) par(tm2, gm2))
-//   3 a factor c + i s (-1)^par(tm, gm) of a string pattern: the product of its
-//     factors multiplies element r, conjugated where the pattern's bit r is set
+//   3 a factor c + i s (-1)^par(tm, gm) of a string pattern, (c, s) the entry's
+//     value: the product of its factors multiplies element r, conjugated where the
+//     pattern's bit r is set
 //   4 reverse sweep: gradient row (slot moff) of a rotation about Z, with the
 //     sign of par(tm, gm) and, where ra >= 0, of register bit ra
+// The kernels read the entries and values of kEntStep entries at once: the pool
+// offsets are the op's, and kEntStep - 1 spare records end the table.
+constexpr int kEntStep = 4;
 struct PhaseEntDev {
   int kind;
-  int moff;
+  int moff;  // kind 4: the slot
   uint32_t tm, tm2;
   uint64_t gm, gm2;
   int ra;
@@ -218,8 +228,9 @@ void pass_runs(TilePassDev& d);
 // rotations read theirs from offset 0).
 constexpr int kPoolSpare = 64;
 
-// The heads of a SegBuild's ops.
+// The heads of a SegBuild's ops, and its entries with the spare ones.
 std::vector<RegHeadDev> op_heads(const SegBuild& sb);
+std::vector<PhaseEntDev> op_entries(const SegBuild& sb);
 
 // The device pool of a SegBuild from the host values (FP64; the caller rounds).
 void assemble_pool(const SegBuild& sb, const std::vector<cd>& vals, std::vector<cd>& pool);

@@ -708,13 +708,14 @@ static int ensure_tables(qsv_plan* p, hipStream_t stream) {
     for (size_t i = 0; i < vals.size(); ++i) pool[i] = {R(vals[i].re), R(vals[i].im)};
   }
   const std::vector<RegHeadDev> heads = op_heads(p->sb);
+  const std::vector<PhaseEntDev> ents = op_entries(p->sb);
   void* buf[7] = {};
   const size_t bytes[7] = {p->h_pass.size() * sizeof(TilePassDev), p->h_ops.size() * sizeof(TileOpDev),
                            p->sb.segs.size() * sizeof(RegSegDev),  p->sb.rops.size() * sizeof(RegOpDev),
-                           p->sb.ents.size() * sizeof(PhaseEntDev), pool_n * sizeof(cx<R>),
+                           ents.size() * sizeof(PhaseEntDev), pool_n * sizeof(cx<R>),
                            heads.size() * sizeof(RegHeadDev)};
   const void* src[7] = {p->h_pass.data(), p->h_ops.data(), p->sb.segs.data(), p->sb.rops.data(),
-                        p->sb.ents.data(), pool.data(),    heads.data()};
+                        ents.data(),       pool.data(),    heads.data()};
   int rc = QSV_OK;
   for (int i = 0; i < 7 && !rc; ++i)
     if (hipMalloc(&buf[i], std::max<size_t>(bytes[i], 16)) != hipSuccess) {

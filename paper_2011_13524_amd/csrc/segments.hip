@@ -350,6 +350,10 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
     return at;
   };
 
+  d.rop_begin = int(out.rops.size());
+  d.ent_begin = int(out.ents.size());
+  d.pool_begin = out.pool_elems;
+
   // dependency order
   std::vector<uint32_t> need(nops), nd(nops), dg(nops);
   for (int i = 0; i < nops; ++i) {
@@ -740,9 +744,10 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
           if (e.tm == 0 && e.gm == 0) {
             tab.push_back(c);
           } else {
-            e.kind = rm ? 3 : 1;
+            e.kind = rm ? 3 : 0;
             TabComp c0 = c;
-            c0.rsg = 0;
+            c0.rsg = rm ? 0u : 2u;  // (no register bit: the second value is the conjugate)
+            if (!rm) e.rsg = 0;
             merge(e, &c0);
           }
         }
@@ -763,14 +768,24 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
       for (size_t k = 0; k < acc.size(); ++k) {
         Acc& x = acc[k];
         if (x.e.kind == 2 && !x.odd) continue;  // CZ twice
-        if (x.e.kind == 0 || x.e.kind == 1 || x.e.kind == 3) {
+        int moff = 0;
+        if (x.e.kind == 0 || x.e.kind == 3) {
           const int nv = x.e.kind == 0 ? 2 : 1;
-          x.e.moff = pool_take(nv);
-          out.recs.push_back({1, x.e.moff, 0, nv, x.comps});
+          moff = pool_take(nv);
+          out.recs.push_back({1, moff, 0, nv, x.comps});
         }
-        if (x.e.kind < 3) {
+        if (x.e.kind < 3 && (x.e.kind == 0 ? r.ent_count : r.ent_cz) == 0xffff) {  // (the head's fields)
+          out_rops.push_back(r);
+          r = RegOpDev{};
+          r.kind = 11;
+          r.ent_begin = int(out.ents.size());
+        }
+        if (x.e.kind == 0) {
           r.flags |= 2;
-          ++r.ent_count;
+          if (r.ent_count++ == 0) r.ent_moff = moff;
+        } else if (x.e.kind == 2) {
+          r.flags |= 2;
+          ++r.ent_cz;
         } else if (x.e.kind == 3) {
           if (h < 0 || r.h_rsg[h] != x.e.rsg) {
             if (h + 1 == kRegMaxH) {  // further patterns: another op
@@ -783,6 +798,7 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
             r.flags |= 16u << h;
             r.h_rsg[h] = x.e.rsg;
             r.h_begin[h] = int(out.ents.size());
+            r.h_moff[h] = moff;
           }
           ++r.h_count[h];
         } else {
@@ -1002,6 +1018,9 @@ int build_reg_segments(const SegCfg& cfg, std::vector<TileOpDev>& ho, TilePassDe
       out.recs.push_back({1, d.scale_off, 0, 1, sg});
     }
   }
+  d.rop_count = int(out.rops.size()) - d.rop_begin;
+  d.ent_count = int(out.ents.size()) - d.ent_begin;
+  d.pool_count = out.pool_elems - d.pool_begin;
   // LDS address tables of the pass's segments: the tile's LDS index is
   // swizzled by j ^ (j >> SB) ^ (j >> 2 SB) (low SB bits of each), linear over
   // XOR, so the byte offset splits into a per-thread part (XOR of per-bit
@@ -1053,8 +1072,8 @@ std::vector<RegHeadDev> op_heads(const SegBuild& sb) {
     }
     h.roff = r.roff;
     h.ent_begin = r.ent_begin;
-    h.ent_count = r.ent_count;
-    h.row_begin = r.row_begin;
+    h.ent_moff = r.ent_moff;
+    h.ent_counts = uint32_t(r.ent_count) | uint32_t(r.ent_cz) << 16;
     h.row_count = r.row_count;
     for (int k = 0; k < kRegMaxH; ++k) h.h_rsg[k] = r.h_rsg[k];
     h.tm01 = r.tm[0] | r.tm[1] << 16;
@@ -1064,6 +1083,12 @@ std::vector<RegHeadDev> op_heads(const SegBuild& sb) {
   }
   heads.push_back(RegHeadDev{});  // (read ahead past the last op)
   return heads;
+}
+
+std::vector<PhaseEntDev> op_entries(const SegBuild& sb) {
+  std::vector<PhaseEntDev> e = sb.ents;
+  e.resize(e.size() + kEntStep - 1);
+  return e;
 }
 
 void assemble_pool(const SegBuild& sb, const std::vector<cd>& vals, std::vector<cd>& pool) {

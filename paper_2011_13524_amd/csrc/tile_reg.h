@@ -265,7 +265,8 @@ __device__ __forceinline__ void reg_apply(cx<R>* v, int key, const cx<R>* m, con
 // parts in the source, or results in fresh registers, the compiler keeps the
 // array in two places and copies it at the joins (32 to 64 moves per op beside
 // the 48 FMAs of a rotation and the 64 products of a table). Few, large blocks:
-// a taken branch costs a wavefront more than the instructions it skips.
+// a taken branch costs a wavefront more than the instructions it skips; a block
+// first tests whether there is anything to do in it.
 // Uniform factors sit in scalar registers, one per instruction.
 //
 // Operands: the components of elements 0 .. 15 (or 0 .. 7) are %0 .. %31, the
@@ -295,6 +296,10 @@ __device__ __forceinline__ void reg_apply(cx<R>* v, int key, const cx<R>* m, con
 #define QSV_E16(v) QSV_E8(v), QSV_E8((v + 8))
 // skip to label L unless bit B of the uniform M is set
 #define QSV_UNLESS(M, B, L) "s_bitcmp0_b32 %[" M "], " B "\n\ts_cbranch_scc1 " L "f\n\t"
+
+// skip to label L if the uniform M is 0, or has none of the bits B (overwrites vcc_lo)
+#define QSV_NONE(M, L) "s_cmp_eq_u32 %[" M "], 0\n\ts_cbranch_scc1 " L "f\n\t"
+#define QSV_WITHOUT(M, B, L) "s_and_b32 vcc_lo, %[" M "], " B "\n\ts_cbranch_scc0 " L "f\n\t"
 
 // Rotation by t/2 of two real components (x, y) as three shears, x += al y,
 // y += be x, x += al y with al = tan(t/4), be = -sin(t/2) (|t/2| <= pi/2: both
@@ -336,15 +341,16 @@ __device__ __forceinline__ void reg_apply(cx<R>* v, int key, const cx<R>* m, con
 #define QSV_ROTS(T, F, N)                                                                                  \
   /* rotations on bits 0 .. 3 of 16 elements: bit P of rot about Y, 8 + P about X, shears c[P] */          \
   __device__ __forceinline__ void rot16(cx<T>* v, const cx<T>* c, uint32_t rot) {                          \
-    asm(QSV_ROT16(F, N, 0, "1", "2") QSV_ROT16(F, N, 1, "3", "4") QSV_ROT16(F, N, 2, "5", "6")              \
-            QSV_ROT16(F, N, 3, "7", "8")                                                                   \
+    asm(QSV_NONE("m", "9") QSV_ROT16(F, N, 0, "1", "2") QSV_ROT16(F, N, 1, "3", "4")                        \
+            QSV_ROT16(F, N, 2, "5", "6") QSV_ROT16(F, N, 3, "7", "8") "9:"                                 \
         : QSV_E16(v)                                                                                       \
         : QSV_AB(c, 0), QSV_AB(c, 1), QSV_AB(c, 2), QSV_AB(c, 3), [m] "s"(rot)                             \
         : "scc");                                                                                          \
   }                                                                                                        \
   /* bits 0 .. 2 of 8 elements */                                                                          \
   __device__ __forceinline__ void rot8(cx<T>* v, const cx<T>* c, uint32_t rot) {                           \
-    asm(QSV_ROT8(F, N, 0, "1", "2") QSV_ROT8(F, N, 1, "3", "4") QSV_ROT8(F, N, 2, "5", "6")                \
+    asm(QSV_NONE("m", "9") QSV_ROT8(F, N, 0, "1", "2") QSV_ROT8(F, N, 1, "3", "4")                          \
+            QSV_ROT8(F, N, 2, "5", "6") "9:"                                                               \
         : QSV_E8(v)                                                                                        \
         : QSV_AB(c, 0), QSV_AB(c, 1), QSV_AB(c, 2), [m] "s"(rot)                                           \
         : "scc");                                                                                          \
@@ -415,12 +421,14 @@ QSV_ROTS(double, QSV_F64, QSV_N64)
   __device__ __forceinline__ void lane16(cx<T>* v, cx<T> C, const M* f, const cx<T>* h, uint32_t flags,     \
                                          const uint32_t* rsg) {                                             \
     T t, u;                                                                                                 \
-    asm("s_and_b32 vcc_lo, %[m], 0xfff2\n\ts_cbranch_scc0 7f\n\t" QSV_UNLESS("m", "1", "1")                 \
-        QSV_X(QSV_FAC8, O, QSV_N8A) QSV_X(QSV_FAC8, O, QSV_N8B) "1:\n\t" QSV_UNLESS("m", "8", "1")          \
+    asm(QSV_WITHOUT("m", "0xfff2", "7") QSV_UNLESS("m", "1", "1")                                            \
+        QSV_X(QSV_FAC8, O, QSV_N8A) QSV_X(QSV_FAC8, O, QSV_N8B) "1:\n\t"                                    \
+        QSV_WITHOUT("m", "0xf00", "2") QSV_UNLESS("m", "8", "1")                                            \
         QSV_X(QSV_FL, OP, "0", QSV_B0) QSV_X(QSV_FL, OP, "0", QSV_D0) "1:\n\t" QSV_UNLESS("m", "9", "1")    \
         QSV_X(QSV_FL, OP, "1", QSV_B1) QSV_X(QSV_FL, OP, "1", QSV_D1) "1:\n\t" QSV_UNLESS("m", "10", "1")   \
         QSV_X(QSV_FL, OP, "2", QSV_B2) QSV_X(QSV_FL, OP, "2", QSV_D2) "1:\n\t" QSV_UNLESS("m", "11", "1")   \
-        QSV_X(QSV_FL, OP, "3", QSV_B3) QSV_X(QSV_FL, OP, "3", QSV_D3) "1:\n\t" QSV_UNLESS("m", "4", "7")    \
+        QSV_X(QSV_FL, OP, "3", QSV_B3) QSV_X(QSV_FL, OP, "3", QSV_D3) "1:\n2:\n\t"                         \
+        QSV_UNLESS("m", "4", "7")                                                                           \
         QSV_STR16(O, "0") QSV_UNLESS("m", "5", "7") QSV_STR16(O, "1") QSV_UNLESS("m", "6", "7")             \
         QSV_STR16(O, "2") QSV_UNLESS("m", "7", "7") QSV_STR16(O, "3") "7:"                                  \
         : QSV_E16(v), [t] "=&v"(t), [u] "=&v"(u)                                                            \
@@ -433,11 +441,11 @@ QSV_ROTS(double, QSV_F64, QSV_N64)
   __device__ __forceinline__ void lane8(cx<T>* v, cx<T> C, const M* f, const cx<T>* h, uint32_t flags,      \
                                         const uint32_t* rsg) {                                              \
     T t, u;                                                                                                 \
-    asm("s_and_b32 vcc_lo, %[m], 0xfff2\n\ts_cbranch_scc0 7f\n\t" QSV_UNLESS("m", "1", "1")                 \
-        QSV_X(QSV_FAC8, O, QSV_N8A) "1:\n\t" QSV_UNLESS("m", "8", "1")                                      \
+    asm(QSV_WITHOUT("m", "0xfff2", "7") QSV_UNLESS("m", "1", "1")                                            \
+        QSV_X(QSV_FAC8, O, QSV_N8A) "1:\n\t" QSV_WITHOUT("m", "0x700", "2") QSV_UNLESS("m", "8", "1")       \
         QSV_X(QSV_FL, OP, "0", QSV_B0) "1:\n\t" QSV_UNLESS("m", "9", "1")                                   \
         QSV_X(QSV_FL, OP, "1", QSV_B1) "1:\n\t" QSV_UNLESS("m", "10", "1")                                  \
-        QSV_X(QSV_FL, OP, "2", QSV_B2) "1:\n\t" QSV_UNLESS("m", "4", "7")                                   \
+        QSV_X(QSV_FL, OP, "2", QSV_B2) "1:\n2:\n\t" QSV_UNLESS("m", "4", "7")                              \
         QSV_STR8(O, "0") QSV_UNLESS("m", "5", "7") QSV_STR8(O, "1") QSV_UNLESS("m", "6", "7")               \
         QSV_STR8(O, "2") QSV_UNLESS("m", "7", "7") QSV_STR8(O, "3") "7:"                                    \
         : QSV_E8(v), [t] "=&v"(t), [u] "=&v"(u)                                                             \
@@ -521,6 +529,30 @@ __device__ __forceinline__ T unset() {
   return x;
 }
 
+// Uniform values in scalar registers, whichever way they were read.
+__device__ __forceinline__ int su(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t su(uint64_t x) { return uint64_t(su(uint32_t(x >> 32))) << 32 | su(uint32_t(x)); }
+__device__ __forceinline__ float su(float x) { return __uint_as_float(su(__float_as_uint(x))); }
+__device__ __forceinline__ double su(double x) {
+  return __hiloint2double(su(__double2hiint(x)), su(__double2loint(x)));
+}
+template <typename R>
+__device__ __forceinline__ cx<R> su(cx<R> x) {
+  return {su(x.re), su(x.im)};
+}
+
+// Keeps a uniform value read here: the read is neither moved to its use nor repeated.
+template <typename T>
+__device__ __forceinline__ void read_now(T& x) {
+  x = su(x);
+  asm volatile("" : "+s"(x));
+}
+template <typename R>
+__device__ __forceinline__ void read_now(cx<R>& x) {
+  read_now(x.re);
+  read_now(x.im);
+}
+
 __device__ __forceinline__ float sgn_xor(float x, uint32_t m) { return __uint_as_float(__float_as_uint(x) ^ m); }
 __device__ __forceinline__ double sgn_xor(double x, uint32_t m) {
   return __hiloint2double(__double2hiint(x) ^ int(m), __double2loint(x));
@@ -554,41 +586,99 @@ __device__ __forceinline__ void phase_apply(cx<R> (&v)[NS][1 << RB], const RegHe
   for (int a = 0; a < RB; ++a) f[a] = unset<M>();
 #pragma unroll
   for (int h = 0; h < kRegMaxH; ++h) H[h] = {unset<R>(), unset<R>()};
-  if (fl & 2u) {
-    uint32_t sg = 0;
-    C = {R(1), R(0)};
-    for (int e = hd.ent_begin; e < hd.ent_begin + hd.ent_count; ++e) {
-      const PhaseEntDev E = ents[e];
-      const uint32_t p = ph_par(tau, E.tm, base, E.gm);
-      if (E.kind == 0) {
-        C = csel(p != 0, pool[E.moff + 1], pool[E.moff]) * C;
-      } else if (E.kind == 1) {
-        const cx<R> z = pool[E.moff];
-        C = cx<R>{z.re, sgn_xor(z.im, p << 31)} * C;
-      } else {
-        sg ^= p & ph_par(tau, E.tm2, base, E.gm2);
+  if (fl & 0xf6u) {
+    if (fl & 2u) {
+      // kEntStep entries at a time, their records and values read together (one by
+      // one, each entry waits for both in turn: parametric RY RZ CNOT ring of 8 layers
+      // on 13 qubits complex64, 8 entries in most passes, 118.4 and 115.2 us)
+      uint32_t sg = 0;
+      C = {R(1), R(0)};
+      const int n0 = int(hd.ent_counts & 0xffffu), n2 = int(hd.ent_counts >> 16);
+      const PhaseEntDev* E = ents + hd.ent_begin;
+      const cx<R>* V = pool + hd.ent_moff;
+      for (int e = 0; e < n0; e += kEntStep) {
+        uint32_t t[kEntStep];
+        uint64_t g[kEntStep];
+        cx<R> z0[kEntStep], z1[kEntStep];
+#pragma unroll
+        for (int j = 0; j < kEntStep; ++j) {
+          t[j] = E[e + j].tm;
+          g[j] = E[e + j].gm;
+          z0[j] = V[2 * (e + j)];
+          z1[j] = V[2 * (e + j) + 1];
+        }
+#pragma unroll
+        for (int j = 0; j < kEntStep; ++j) {
+          read_now(t[j]);
+          read_now(g[j]);
+          read_now(z0[j]);
+          read_now(z1[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < kEntStep; ++j)
+          if (e + j < n0) C = csel(ph_par(tau, t[j], base, g[j]) != 0, z1[j], z0[j]) * C;
+      }
+      E += n0;
+      for (int e = 0; e < n2; e += kEntStep) {
+        uint32_t t[kEntStep], t2[kEntStep];
+        uint64_t g[kEntStep], g2[kEntStep];
+#pragma unroll
+        for (int j = 0; j < kEntStep; ++j) {
+          t[j] = E[e + j].tm;
+          t2[j] = E[e + j].tm2;
+          g[j] = E[e + j].gm;
+          g2[j] = E[e + j].gm2;
+        }
+#pragma unroll
+        for (int j = 0; j < kEntStep; ++j) {
+          read_now(t[j]);
+          read_now(t2[j]);
+          read_now(g[j]);
+          read_now(g2[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < kEntStep; ++j)
+          if (e + j < n2) sg ^= ph_par(tau, t[j], base, g[j]) & ph_par(tau, t2[j], base, g2[j]);
+      }
+      C = {sgn_xor(C.re, sg << 31), sgn_xor(C.im, sg << 31)};
+    }
+    if (fl & 4u) {
+#pragma unroll
+      for (int a = 0; a < RB; ++a) {
+        const uint32_t w = a < 2 ? hd.tm01 : (a < 4 ? hd.tm23 : hd.tm4);
+        f[a] = flip_arg(R(0), ph_par(tau, (w >> (16 * (a & 1))) & 0xffffu, base, op.gm[a]));
       }
     }
-    C = {sgn_xor(C.re, sg << 31), sgn_xor(C.im, sg << 31)};
-  }
-  if (fl & 4u) {
+    if (fl & 0xf0u) {
 #pragma unroll
-    for (int a = 0; a < RB; ++a) {
-      const uint32_t w = a < 2 ? hd.tm01 : (a < 4 ? hd.tm23 : hd.tm4);
-      f[a] = flip_arg(R(0), ph_par(tau, (w >> (16 * (a & 1))) & 0xffffu, base, op.gm[a]));
-    }
-  }
-  if (fl & 0xf0u) {
+      for (int h = 0; h < kRegMaxH; ++h) {
+        if (!(fl >> (4 + h) & 1u)) continue;
+        cx<R> z = {R(1), R(0)};
+        const int nh = op.h_count[h];
+        const PhaseEntDev* E = ents + op.h_begin[h];
+        const cx<R>* V = pool + op.h_moff[h];
+        for (int e = 0; e < nh; e += kEntStep) {
+          uint32_t t[kEntStep];
+          uint64_t g[kEntStep];
+          cx<R> f[kEntStep];
 #pragma unroll
-    for (int h = 0; h < kRegMaxH; ++h) {
-      if (!(fl >> (4 + h) & 1u)) continue;
-      cx<R> z = {R(1), R(0)};
-      for (int e = op.h_begin[h]; e < op.h_begin[h] + op.h_count[h]; ++e) {
-        const PhaseEntDev E = ents[e];
-        const cx<R> g = pool[E.moff];
-        z = cx<R>{g.re, sgn_xor(g.im, ph_par(tau, E.tm, base, E.gm) << 31)} * z;
+          for (int j = 0; j < kEntStep; ++j) {
+            t[j] = E[e + j].tm;
+            g[j] = E[e + j].gm;
+            f[j] = V[e + j];
+          }
+#pragma unroll
+          for (int j = 0; j < kEntStep; ++j) {
+            read_now(t[j]);
+            read_now(g[j]);
+            read_now(f[j]);
+          }
+#pragma unroll
+          for (int j = 0; j < kEntStep; ++j)
+            if (e + j < nh) z = cx<R>{f[j].re, sgn_xor(f[j].im, ph_par(tau, t[j], base, g[j]) << 31)} * z;
+        }
+        H[h] = z;
       }
-      H[h] = z;
     }
   }
   const uint32_t rsg[4] = {su(hd.h_rsg[0]), su(hd.h_rsg[1]), su(hd.h_rsg[2]), su(hd.h_rsg[3])};
@@ -867,6 +957,20 @@ __device__ __forceinline__ uint64_t pass_base(const TilePassDev& P, uint32_t g) 
   return base;
 }
 
+// A pass's tables are read through the scalar cache, a record when it is due, and
+// every launch finds that cache empty: where few workgroups share them, each read
+// is a trip to memory in a chain of dozens. So every thread reads a cache line of
+// each table first, all at once, into the L2 of its XCD -- in the first workgroups of
+// a pass (32 per XCD): later ones find them there. Measured with fewer taken
+// branches per op (rot16, lane16): that ring 115.2 -> 110.1 us, on 17 qubits
+// complex128 209.5 -> 196.3. The value has to be kept until the reads have come back.
+constexpr uint32_t kWarmTiles = 256;
+__device__ __forceinline__ uint32_t touch(const void* p, uint32_t bytes, uint32_t tau) {
+  uint32_t x = 0;
+  if (tau * 128u < bytes) x = *reinterpret_cast<const uint32_t*>(static_cast<const char*>(p) + tau * 128u);
+  return x;
+}
+
 // KMAX 0: passes of kind-11 ops only. Workgroups are persistent: workgroup b
 // takes tiles b, b + grid, ... and (KMAX 0) issues the loads of its next tile before
 // it computes on the current one. General products need those registers: with
@@ -895,7 +999,16 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
   const uint32_t tau = threadIdx.x;
   const ThrMask<TB> tm(tau);
   const RegSegDev* const S0 = &segs[P.seg_begin];
-  const RegSegDev* const SL = &segs[P.seg_begin + P.seg_count - 1];
+  int nseg = P.seg_count;
+  read_now(nseg);
+  uint32_t warm = 0;
+  if (g < kWarmTiles)
+    warm = touch(S0, uint32_t(nseg) * uint32_t(sizeof(RegSegDev)), tau) ^
+           touch(heads + P.rop_begin, uint32_t(P.rop_count) * uint32_t(sizeof(RegHeadDev)), tau) ^
+           touch(rops + P.rop_begin, uint32_t(P.rop_count) * uint32_t(sizeof(RegOpDev)), tau) ^
+           touch(ents + P.ent_begin, uint32_t(P.ent_count) * uint32_t(sizeof(PhaseEntDev)), tau) ^
+           touch(pool + P.pool_begin, uint32_t(P.pool_count) * uint32_t(sizeof(cx<R>)), tau);
+  const RegSegDev* const SL = S0 + (nseg - 1);
   uint64_t th0 = 0, thL = 0;
 #pragma unroll
   for (int k = 0; k < TB; ++k) {
@@ -920,8 +1033,9 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
     const RegSegDev* S = S0;
     int oi = S->op_begin;
     RegHeadDev next = heads[oi];  // the next op's head, read one op ahead
-    for (int sgi = 0; sgi < P.seg_count; ++sgi) {
-      const RegSegDev* Sn = &segs[P.seg_begin + sgi];
+    for (int sgi = 0; sgi < nseg; ++sgi) {
+      const RegSegDev* Sn = S0 + sgi;
+      int oe = Sn->op_begin + Sn->op_count;
       if (sgi > 0) {
         // re-map through LDS, applying the ops folded into it on the way; when
         // both layouts share the wave bits (and no folded op targets one), every
@@ -933,6 +1047,7 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
         const uint32_t j = tm.map(Sn->tcst, Sn->tcol);
         const LdsMap<R, RB> mo(Sn->put_reg, j & 0xffffu);
         const LdsMap<R, RB> mn(Sn->get_reg, j >> 16);
+        read_now(oe);
         if (xpre) __syncthreads();
 #pragma unroll
         for (int i = 0; i < NR; ++i) mo.put(smem, i, v[0][i]);
@@ -947,7 +1062,7 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
       }
       S = Sn;
       // (a pass's ops are contiguous: the read ahead goes on across segments)
-      for (const int oe = S->op_begin + S->op_count; oi < oe;) {
+      while (oi < oe) {
         const RegHeadDev hd = next;
         const RegOpDev& op = rops[oi];
         next = heads[++oi];
@@ -973,6 +1088,7 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
     base = nbase;
     __syncthreads();  // every wavefront has read its last re-map: LDS is free
   }
+  asm volatile("" ::"v"(warm));
 }
 
 template <typename R, int RB, int KMAX, int TB>
