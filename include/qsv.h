@@ -385,7 +385,9 @@ int qsv_apply_observable(const qsv_state* in, const qsv_observable* o, qsv_state
  * forward_plan: optional fused plan of the same circuit and dtype for the
  * forward pass (NULL = one launch per gate). grad: circuit nparams doubles,
  * overwritten; a slot used by several gates receives the sum of their
- * contributions. Gradients accumulate in double. Parametric multi-qubit Pauli
+ * contributions. Gradients accumulate in double; complex64 sweeps of 20 qubits
+ * and more form the products, and a thread's sums of 8 or 16 of them, in FP32
+ * (all others in double). Parametric multi-qubit Pauli
  * rotations (qsv_circuit_add_pauli_rotation) are differentiated too. From 3
  * qubits the reverse sweep runs in tile passes (register-resident from 9);
  * its tables stay with the forward plan, or live in psi's work buffer

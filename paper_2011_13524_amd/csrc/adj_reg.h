@@ -31,22 +31,22 @@ __device__ __forceinline__ double neg_im_phase(double sr, double si, int ph) {
 // and write one FP64 partial per (row, workgroup) at the end of the pass.
 
 // This thread's share of -Im<lambda|P|psi> for P = Y (YAX) or X on register bit
-// P: v[0] is psi, v[1] lambda. Summed in the amplitude precision over the
-// thread's pairs (complex64: FP32 products and 8-term sums, relative error <=
-// 11 x 2^-24 of sum |lambda_x||psi_y| <= |lambda||psi|; the caller sums in
-// FP64).
-template <typename R, int NR, int P, bool YAX>
-__device__ __forceinline__ R grad_xy(const cx<R> (&v)[2][NR]) {
-  R acc = R(0);
+// P: v[0] is psi, v[1] lambda. Products and the thread's sum in G; the caller sums in
+// FP64. G is FP64, but for complex64 states of at least 20 qubits alone (FP32
+// products and 8-term sums, relative error <= 11 x 2^-24 of sum |lambda_x||psi_y|
+// <= |lambda||psi|), where the passes are bound by their vector instructions.
+template <typename R, typename G, int NR, int P, bool YAX>
+__device__ __forceinline__ G grad_xy(const cx<R> (&v)[2][NR]) {
+  G acc = G(0);
   if constexpr ((1 << P) < NR) {
 #pragma unroll
     for (int g = 0; g < NR / 2; ++g) {
       const int i = ins1<P>(g), j = i | (1 << P);
       const cx<R> a0 = v[0][i], a1 = v[0][j], l0 = v[1][i], l1 = v[1][j];
       if constexpr (YAX)
-        acc += fma(l0.re, a1.re, l0.im * a1.im) - fma(l1.re, a0.re, l1.im * a0.im);
+        acc += fma(G(l0.re), G(a1.re), G(l0.im) * G(a1.im)) - fma(G(l1.re), G(a0.re), G(l1.im) * G(a0.im));
       else
-        acc += fma(l0.im, a1.re, -(l0.re * a1.im)) + fma(l1.im, a0.re, -(l1.re * a0.im));
+        acc += fma(G(l0.im), G(a1.re), -(G(l0.re) * G(a1.im))) + fma(G(l1.im), G(a0.re), -(G(l1.re) * G(a0.im)));
     }
   }
   return acc;
@@ -61,14 +61,14 @@ __device__ __forceinline__ void add_row(double acc, double* wslot, int row, uint
 
 // The rotations of a kind-11 op with their gradients: per register bit, the
 // gradient's share from both states, then the uncompute exp(-i t P/2) of both.
-template <typename R, int RB, int TB, int P = 0>
+template <typename R, typename G, int RB, int TB, int P = 0>
 __device__ __forceinline__ void grad_layer(cx<R> (&v)[2][1 << RB], uint32_t rot, const RegOpDev& op,
                                            const cx<R>* __restrict__ coef, double* wslot, uint32_t tau) {
   if constexpr (P < RB) {
     if (rot >> (16 + P) & 1u) {
       double acc;
-      if (rot >> P & 1u) acc = double(grad_xy<R, 1 << RB, P, true>(v));
-      else acc = double(grad_xy<R, 1 << RB, P, false>(v));
+      if (rot >> P & 1u) acc = double(grad_xy<R, G, 1 << RB, P, true>(v));
+      else acc = double(grad_xy<R, G, 1 << RB, P, false>(v));
       add_row<TB>(acc, wslot, op.aux[P], tau);
     }
     const cx<R> c = coef[P];
@@ -77,7 +77,7 @@ __device__ __forceinline__ void grad_layer(cx<R> (&v)[2][1 << RB], uint32_t rot,
       if constexpr (RB == 3) rot8_bit<P>(v[s], c, rot);
       else rot16_bit<P>(v[s], c, rot);
     }
-    grad_layer<R, RB, TB, P + 1>(v, rot, op, coef, wslot, tau);
+    grad_layer<R, G, RB, TB, P + 1>(v, rot, op, coef, wslot, tau);
   }
 }
 
@@ -85,19 +85,20 @@ __device__ __forceinline__ void grad_layer(cx<R> (&v)[2][1 << RB], uint32_t rot,
 // -sum_x (-1)^(x_q) w_x, w_x = Im(conj(lambda_x) psi_x). Diagonal factors of
 // modulus one leave w alone, so the rows of every rotation that waits in the
 // op share one evaluation of w: its sums with the sign of each register bit
-// (s[0..RB-1]) and without (s[RB]) come from one tree of additions, and a row
+// (s[0..RB-1]) and without (s[RB]) come from one tree of additions (in G, as in
+// grad_xy), and a row
 // on a thread bit or a non-local qubit takes the plain sum with its sign.
-template <typename R, int RB, int TB>
+template <typename R, typename G, int RB, int TB>
 __device__ __forceinline__ void phase_rows(const cx<R> (&v)[2][1 << RB], const RegHeadDev& hd,
                                            const RegOpDev& op, const PhaseEntDev* __restrict__ ents, double* wslot, uint32_t tau,
                                            uint64_t base) {
   constexpr int NR = 1 << RB;
-  R w[NR], s[RB + 1];
+  G w[NR], s[RB + 1];
 #pragma unroll
-  for (int r = 0; r < NR; ++r) w[r] = fma(v[1][r].im, v[0][r].re, -(v[1][r].re * v[0][r].im));
+  for (int r = 0; r < NR; ++r) w[r] = fma(G(v[1][r].im), G(v[0][r].re), -(G(v[1][r].re) * G(v[0][r].im)));
 #pragma unroll
   for (int b = RB - 1; b >= 0; --b) {
-    R d = w[0] - w[1 << b];
+    G d = w[0] - w[1 << b];
 #pragma unroll
     for (int r = 1; r < (1 << b); ++r) d += w[r] - w[r | (1 << b)];
     s[b] = d;
@@ -107,7 +108,7 @@ __device__ __forceinline__ void phase_rows(const cx<R> (&v)[2][1 << RB], const R
   s[RB] = w[0];
   for (int e = op.row_begin; e < op.row_begin + hd.row_count; ++e) {
     const PhaseEntDev E = ents[e];
-    R x = s[RB];
+    G x = s[RB];
 #pragma unroll
     for (int b = 0; b < RB; ++b) x = E.ra == b ? s[b] : x;
     add_row<TB>(double(sgn_xor(x, ph_par(tau, E.tm, base, E.gm) << 31)), wslot, E.moff, tau);
@@ -147,13 +148,13 @@ __device__ __forceinline__ void adj_lds_op(cx<R>* v, const LdsMap<R, RB>& ms, ch
 
 // An op of the reverse sweep on both states, in place; gradient ops add this
 // wavefront's share to its slot. Kind 11:
-template <typename R, int RB, int TB>
+template <typename R, typename G, int RB, int TB>
 __device__ __forceinline__ void adj_super(const RegHeadDev& hd, const RegOpDev& op, cx<R> (&v)[2][1 << RB],
                                           uint32_t tau, uint64_t base, const PhaseEntDev* __restrict__ ents,
                                           const cx<R>* __restrict__ pool, double* wslot) {
-  if (hd.flags & 8u) phase_rows<R, RB, TB>(v, hd, op, ents, wslot, tau, base);
+  if (hd.flags & 8u) phase_rows<R, G, RB, TB>(v, hd, op, ents, wslot, tau, base);
   phase_apply<R, RB, 2>(v, hd, op, ents, pool, tau, base);
-  grad_layer<R, RB, TB>(v, su(hd.rot), op, pool + hd.roff, wslot, tau);
+  grad_layer<R, G, RB, TB>(v, su(hd.rot), op, pool + hd.roff, wslot, tau);
   const uint64_t xm = exchange_mask(hd.xch, op, tau, base);
   exchange<R, RB>(v[0], su(hd.xch), xm);
   exchange<R, RB>(v[1], su(hd.xch), xm);
@@ -226,7 +227,7 @@ __device__ __forceinline__ void adj_general(const RegHeadDev& hd, const RegOpDev
 // enters it as phi E <P>. Measured against FP64, 24 qubits, 960 rotations,
 // complex64, four sets of angles: relative error of the gradient 0.7e-5 to 4.5e-5
 // on lambda itself, 0.3e-5 to 0.5e-5 here.
-template <typename R, int RB, int KMAX, int TB>
+template <typename R, typename G, int RB, int KMAX, int TB>
 __device__ __forceinline__ void adj_pass(R* __restrict__ psi, R* __restrict__ lam, const TilePassDev& P, uint64_t g0,
                                          uint64_t gend, const RegSegDev* __restrict__ segs,
                                          const RegHeadDev* __restrict__ heads, const RegOpDev* __restrict__ rops,
@@ -318,7 +319,7 @@ __device__ __forceinline__ void adj_pass(R* __restrict__ psi, R* __restrict__ la
             continue;
           }
         }
-        adj_super<R, RB, TB>(hd, op, v, tau, base, ents, pool, &slot[0][wave]);
+        adj_super<R, G, RB, TB>(hd, op, v, tau, base, ents, pool, &slot[0][wave]);
       }
     }
     if (P.scale_off >= 0) {  // the sign left by the pass's rotations, when no phase op took it
@@ -358,7 +359,7 @@ __device__ __forceinline__ void adj_pass(R* __restrict__ psi, R* __restrict__ la
   }
 }
 
-template <typename R, int RB, int KMAX, int TB>
+template <typename R, typename G, int RB, int KMAX, int TB>
 __global__ void __launch_bounds__(1 << TB)
     k_adj_reg(R* __restrict__ psi, R* __restrict__ lam, const TilePassDev* __restrict__ passes, int pass_idx,
               const RegSegDev* __restrict__ segs, const RegHeadDev* __restrict__ heads,
@@ -369,7 +370,7 @@ __global__ void __launch_bounds__(1 << TB)
   const uint64_t per = (ntiles + gridDim.x - 1) / gridDim.x;
   const uint64_t g0 = uint64_t(blockIdx.x) * per;
   const uint64_t gend = g0 + per < ntiles ? g0 + per : ntiles;
-  adj_pass<R, RB, KMAX, TB>(psi, lam, passes[pass_idx], g0, gend, segs, heads, rops, lops, ents, pool, prow, partial,
+  adj_pass<R, G, RB, KMAX, TB>(psi, lam, passes[pass_idx], g0, gend, segs, heads, rops, lops, ents, pool, prow, partial,
                             gridDim.x, blockIdx.x, e_in, e_out, smem);
 }
 

@@ -627,21 +627,30 @@ using AdjRegFn = void (*)(R*, R*, const TilePassDev*, int, const RegSegDev*, con
 
 template <typename R, int TB>
 static AdjRegFn<R> adj_reg_small(int km) {
-  return km == 0 ? &k_adj_reg<R, 3, 0, TB> : (km <= 3 ? &k_adj_reg<R, 3, 3, TB> : &k_adj_reg<R, 3, 5, TB>);
+  return km == 0   ? &k_adj_reg<R, double, 3, 0, TB>
+         : km <= 3 ? &k_adj_reg<R, double, 3, 3, TB>
+                   : &k_adj_reg<R, double, 3, 5, TB>;
+}
+template <typename R, typename G>
+static AdjRegFn<R> adj_reg_full(int km) {
+  constexpr int RB = sizeof(R) == 4 ? 4 : 3;
+  return km == 0   ? &k_adj_reg<R, G, RB, 0, 8>
+         : km <= 2 ? &k_adj_reg<R, G, RB, 2, 8>
+         : km <= 3 ? &k_adj_reg<R, G, RB, 3, 8>
+                   : &k_adj_reg<R, G, RB, 5, 8>;
 }
 
-// The sweep's kernel for register bits rb, thread bits tb and the widest dense op
-// (0: no general products).
+// Qubits from which complex64 gradients form their products in FP32 (grad_xy).
+constexpr int kAdjFp32Min = 20;
+
+// The sweep's kernel for n qubits, register bits rb, thread bits tb and the widest
+// dense op (0: no general products).
 template <typename R>
-static AdjRegFn<R> adj_reg_fn(int rb, int tb, int km) {
-  constexpr int RBs = sizeof(R) == 4 ? 4 : 3;
+static AdjRegFn<R> adj_reg_fn(int n, int rb, int tb, int km) {
   if (tb == 6) return adj_reg_small<R, 6>(km);
   if (tb == 7) return adj_reg_small<R, 7>(km);
-  if (rb < RBs) return adj_reg_small<R, 8>(km);
-  return km == 0   ? &k_adj_reg<R, RBs, 0, 8>
-         : km <= 2 ? &k_adj_reg<R, RBs, 2, 8>
-         : km <= 3 ? &k_adj_reg<R, RBs, 3, 8>
-                   : &k_adj_reg<R, RBs, 5, 8>;
+  if (rb < (sizeof(R) == 4 ? 4 : 3)) return adj_reg_small<R, 8>(km);
+  return n >= kAdjFp32Min ? adj_reg_full<R, R>(km) : adj_reg_full<R, double>(km);
 }
 
 // Reverse sweep by tile passes. On entry psi = psi_L, lam = H psi_L and energy =
@@ -680,7 +689,7 @@ int adjoint_backward_tiled(const AdjTables& T, std::vector<cd>& vals, AdjCache* 
   uint64_t gmax = kAdjTileGrid;
   if (reg) {
     int per_cu = 0, cus = 0;
-    const AdjRegFn<R> fn = adj_reg_fn<R>(L - T.thread_bits, T.thread_bits, general ? kmax : 0);
+    const AdjRegFn<R> fn = adj_reg_fn<R>(n, L - T.thread_bits, T.thread_bits, general ? kmax : 0);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, nt, reg_lds) != hipSuccess || per_cu < 1)
       per_cu = 1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, psi->device) != hipSuccess || cus < 1)
@@ -731,7 +740,7 @@ int adjoint_backward_tiled(const AdjTables& T, std::vector<cd>& vals, AdjCache* 
     if (reg) {
       for (size_t pi = 0; pi < hp.size(); ++pi) {
         ProfScope ps("adjoint", 4.0 * sizeof(cx<R>) * double(dim(n)), st);
-        hipLaunchKernelGGL((adj_reg_fn<R>(L - T.thread_bits, T.thread_bits, hp[pi].general ? kmax : 0)), dim3(G),
+        hipLaunchKernelGGL((adj_reg_fn<R>(n, L - T.thread_bits, T.thread_bits, hp[pi].general ? kmax : 0)), dim3(G),
                            dim3(nt), reg_lds, st, static_cast<R*>(psi->ptr), static_cast<R*>(lam->ptr),
                            reinterpret_cast<const TilePassDev*>(tab + lo.pass), int(pi),
                            reinterpret_cast<const RegSegDev*>(tab + lo.segs),

@@ -190,7 +190,7 @@ __global__ void __launch_bounds__(1 << kRegThreadBits, (tile_waves_per_simd<R, 4
   const MWork w = work[blockIdx.x];
   const MItem& I = items[w.item];
   tile_pass<R, 4, KMAX, kRegThreadBits>(reinterpret_cast<R*>(states + I.psi), passes[circs[I.circ].pass[0] + round], w.g,
-                                        I.cols[0], I.ntiles[0], segs, heads, rops, ops, ents, pool + I.pool[0], smem);
+                                        I.cols[0], I.ntiles[0], 0u, segs, heads, rops, ops, ents, pool + I.pool[0], smem);
 }
 
 template <typename R, int KMAX>
@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(1 << kRegThreadBits)
   const MWork w = work[blockIdx.x];
   const MItem& I = items[w.item];
   const uint64_t per = I.ntiles[1] / I.cols[1];  // (both powers of two)
-  adj_pass<R, sizeof(R) == 4 ? 4 : 3, KMAX, kRegThreadBits>(
+  adj_pass<R, double, sizeof(R) == 4 ? 4 : 3, KMAX, kRegThreadBits>(
       reinterpret_cast<R*>(states + I.psi), reinterpret_cast<R*>(states + I.lam), passes[circs[I.circ].pass[1] + round],
       w.g * per, (w.g + 1) * per, segs, heads, rops, ops, ents, pool + I.pool[1], prow, part + I.part, I.cols[1], w.g,
       round == 0 ? R(energies[I.index]) : R(0), R(0), smem);

@@ -988,7 +988,7 @@ __device__ __forceinline__ uint32_t touch(const void* p, uint32_t bytes, uint32_
 // 5.6 to 6.3 ms, over fresh workgroups per tile.
 template <typename R, int RB, int KMAX, int TB>
 __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev& P, uint32_t g, uint32_t step,
-                                          uint32_t ntiles, const RegSegDev* __restrict__ segs,
+                                          uint32_t ntiles, uint32_t warm_tiles, const RegSegDev* __restrict__ segs,
                                           const RegHeadDev* __restrict__ heads, const RegOpDev* __restrict__ rops,
                                           const TileOpDev* __restrict__ lops, const PhaseEntDev* __restrict__ ents,
                                           const cx<R>* __restrict__ pool, char* smem) {
@@ -1002,7 +1002,7 @@ __device__ __forceinline__ void tile_pass(R* __restrict__ psi, const TilePassDev
   int nseg = P.seg_count;
   read_now(nseg);
   uint32_t warm = 0;
-  if (g < kWarmTiles)
+  if (g < warm_tiles)
     warm = touch(S0, uint32_t(nseg) * uint32_t(sizeof(RegSegDev)), tau) ^
            touch(heads + P.rop_begin, uint32_t(P.rop_count) * uint32_t(sizeof(RegHeadDev)), tau) ^
            touch(rops + P.rop_begin, uint32_t(P.rop_count) * uint32_t(sizeof(RegOpDev)), tau) ^
@@ -1099,8 +1099,8 @@ __global__ void __launch_bounds__(1 << TB, (tile_waves_per_simd<R, RB>()))
                const cx<R>* __restrict__ pool) {
   extern __shared__ __align__(16) char smem[];
   // (the grid has at most ntiles workgroups)
-  tile_pass<R, RB, KMAX, TB>(psi, passes[pass_idx], blockIdx.x, gridDim.x, ntiles, segs, heads, rops, lops, ents, pool,
-                             smem);
+  tile_pass<R, RB, KMAX, TB>(psi, passes[pass_idx], blockIdx.x, gridDim.x, ntiles, kWarmTiles, segs, heads, rops, lops,
+                             ents, pool, smem);
 }
 
 }  // namespace qsv
