@@ -17,6 +17,7 @@
 // are constants per tile. The same passes give lambda = O psi (adjoint).
 #include <algorithm>
 #include <cstdlib>
+#include <initializer_list>
 #include <mutex>
 
 #include "dev_common.h"
@@ -182,21 +183,34 @@ struct ExpPlan {
   std::vector<ExpPassDev> passes;
   std::vector<ExpGroupDev> groups;
   std::vector<ExpTermDev> terms;
-  std::vector<ExpSpanDev> spans;  // (full tiles only)
+  // full tiles only, made for the first expectation / lambda: the records in spans /
+  // for lambda, and the passes with their ranges (passes itself never changes)
+  std::vector<ExpPassDev> span_passes, obs_passes;
+  std::vector<ExpSpanDev> spans;
   std::vector<ExpRecDev> recs;
-  std::vector<ObsRecDev> orecs;  // (full tiles only)
+  std::vector<ObsRecDev> orecs;
   std::vector<ObsCoefDev> ocoef;
   std::vector<ExpWide> wide;
   std::vector<ExpTermDev> wide_terms;
-  void* dev = nullptr;  // passes | groups | terms | wide_terms | spans | recs
-  size_t off_groups = 0, off_terms = 0, off_wide = 0, off_spans = 0, off_recs = 0, off_orecs = 0, off_ocoef = 0;
-  int device = -1;
+  // device copies, each made once per device and kept: what one call uses is never
+  // replaced by another kind of call
+  struct Copy {
+    void* p = nullptr;
+    int device = -1;
+  };
+  Copy dev;        // passes | groups | terms | wide_terms
+  Copy dev_spans;  // span_passes | spans | recs
+  Copy dev_obs;    // obs_passes | orecs | ocoef
   bool spans_tried = false, orecs_tried = false;
 };
+// Guards the lazy parts of every observable's plans (building, upload); a plan's
+// host tables and device copies do not change once made.
+std::mutex g_plan_mu;
 
 void free_exp_plan(ExpPlan* p) {
   if (!p) return;
-  if (p->dev) (void)hipFree(p->dev);
+  for (ExpPlan::Copy* c : {&p->dev, &p->dev_spans, &p->dev_obs})
+    if (c->p) (void)hipFree(c->p);
   delete p;
 }
 
@@ -1319,7 +1333,8 @@ void ensure_obs_recs(ExpPlan* p, bool c64) {
     if (d.single_count > kSpanRecs) return;
   constexpr int tb = 10;  // 1024 threads
   static_assert(obs_threads<float>() == 1 << tb && obs_threads<double>() == 1 << tb, "thread part of an index");
-  for (ExpPassDev& d : p->passes) {
+  p->obs_passes = p->passes;
+  for (ExpPassDev& d : p->obs_passes) {
     const ExpGroupDev* g = p->groups.data() + d.grp_begin;
     std::vector<int> order;
     for (int i = 0; i < d.single_count; ++i) order.push_back(i);
@@ -1354,7 +1369,6 @@ void ensure_obs_recs(ExpPlan* p, bool c64) {
     }
     d.obs_last = int(cur);
   }
-  p->device = -1;  // (tables already uploaded are uploaded again, with them)
 }
 
 // The spans of a plan of full tiles (built for the first expectation; lambda
@@ -1365,49 +1379,102 @@ void ensure_spans(ExpPlan* p, bool c64) {
   if (p->L != (c64 ? exp_tile_bits<float>() : exp_tile_bits<double>())) return;
   for (const ExpPassDev& d : p->passes)
     if (d.single_count > kSpanRecs) return;
-  for (ExpPassDev& d : p->passes) build_spans(p, d, p->L - 9, c64);
-  p->device = -1;  // (tables already uploaded are uploaded again, with them)
+  p->span_passes = p->passes;
+  for (ExpPassDev& d : p->span_passes) build_spans(p, d, p->L - 9, c64);
 }
 
-int upload_exp_plan(ExpPlan* p, int device) {
-  if (p->dev && p->device == device) return QSV_OK;
-  if (p->dev) (void)hipFree(p->dev);
-  p->dev = nullptr;
-  const size_t a = p->passes.size() * sizeof(ExpPassDev);
-  p->off_groups = (a + 255) / 256 * 256;
-  const size_t bsz = p->groups.size() * sizeof(ExpGroupDev);
-  p->off_terms = (p->off_groups + bsz + 255) / 256 * 256;
-  p->off_wide = (p->off_terms + p->terms.size() * sizeof(ExpTermDev) + 255) / 256 * 256;
-  p->off_spans = (p->off_wide + std::max<size_t>(1, p->wide_terms.size()) * sizeof(ExpTermDev) + 255) / 256 * 256;
-  p->off_recs = (p->off_spans + p->spans.size() * sizeof(ExpSpanDev) + 255) / 256 * 256;
-  p->off_orecs = (p->off_recs + p->recs.size() * sizeof(ExpRecDev) + 255) / 256 * 256;
-  p->off_ocoef = (p->off_orecs + p->orecs.size() * sizeof(ObsRecDev) + 255) / 256 * 256;
-  const size_t total = p->off_ocoef + p->ocoef.size() * sizeof(ObsCoefDev);
-  if (hipMalloc(&p->dev, total) != hipSuccess) return fail(QSV_ENOMEM, "observable plan allocation failed");
-  char* d = static_cast<char*>(p->dev);
-  if (a) QSV_HIP_CHECK(hipMemcpy(d, p->passes.data(), a, hipMemcpyHostToDevice));
-  if (bsz) QSV_HIP_CHECK(hipMemcpy(d + p->off_groups, p->groups.data(), bsz, hipMemcpyHostToDevice));
-  if (!p->terms.empty())
-    QSV_HIP_CHECK(hipMemcpy(d + p->off_terms, p->terms.data(), p->terms.size() * sizeof(ExpTermDev),
-                            hipMemcpyHostToDevice));
-  if (!p->wide_terms.empty())
-    QSV_HIP_CHECK(hipMemcpy(d + p->off_wide, p->wide_terms.data(), p->wide_terms.size() * sizeof(ExpTermDev),
-                            hipMemcpyHostToDevice));
-  if (!p->spans.empty()) {
-    QSV_HIP_CHECK(hipMemcpy(d + p->off_spans, p->spans.data(), p->spans.size() * sizeof(ExpSpanDev), hipMemcpyHostToDevice));
-    QSV_HIP_CHECK(hipMemcpy(d + p->off_recs, p->recs.data(), p->recs.size() * sizeof(ExpRecDev), hipMemcpyHostToDevice));
+constexpr size_t al256(size_t x) { return (x + 255) / 256 * 256; }
+
+// Host tables that go to the device one after the other, each from a multiple of
+// 256 bytes.
+struct TablePart {
+  const void* src;
+  size_t bytes;
+};
+
+// The device copy c of the parts (one allocation, one transfer), made if `device` has
+// none yet.
+int upload_parts(ExpPlan::Copy& c, int device, std::initializer_list<TablePart> parts) {
+  if (c.p && c.device == device) return QSV_OK;
+  if (c.p) (void)hipFree(c.p);
+  c.p = nullptr;
+  size_t total = 0;
+  for (const TablePart& t : parts) total += al256(std::max<size_t>(t.bytes, 1));
+  if (hipMalloc(&c.p, total) != hipSuccess) {
+    (void)hipGetLastError();
+    c.p = nullptr;
+    return fail(QSV_ENOMEM, "observable plan allocation failed");
   }
-  if (!p->orecs.empty()) {
-    QSV_HIP_CHECK(hipMemcpy(d + p->off_orecs, p->orecs.data(), p->orecs.size() * sizeof(ObsRecDev), hipMemcpyHostToDevice));
-    QSV_HIP_CHECK(hipMemcpy(d + p->off_ocoef, p->ocoef.data(), p->ocoef.size() * sizeof(ObsCoefDev), hipMemcpyHostToDevice));
+  c.device = -1;  // (until everything is there)
+  std::vector<char> stage(total);
+  size_t at = 0;
+  for (const TablePart& t : parts) {
+    if (t.bytes) std::copy_n(static_cast<const char*>(t.src), t.bytes, stage.data() + at);
+    at += al256(std::max<size_t>(t.bytes, 1));
   }
-  p->device = device;
+  QSV_HIP_CHECK(hipMemcpy(c.p, stage.data(), total, hipMemcpyHostToDevice));
+  c.device = device;
   return QSV_OK;
 }
 
-constexpr size_t kNoAllocBytes = size_t(1) << 20;
+template <typename T>
+TablePart part_of(const std::vector<T>& v) {
+  return {v.data(), v.size() * sizeof(T)};
+}
+// Offset of the k-th part.
+template <typename... V>
+size_t part_offset(const V&... before) {
+  size_t o = 0;
+  ((o += al256(std::max<size_t>(part_of(before).bytes, 1))), ...);
+  return o;
+}
 
-size_t al256(size_t x) { return (x + 255) / 256 * 256; }
+// The tables as a call uses them.
+struct ExpTables {
+  const ExpPassDev* passes = nullptr;
+  const ExpGroupDev* groups = nullptr;
+  const ExpTermDev *terms = nullptr, *wide = nullptr;
+  const ExpSpanDev* spans = nullptr;
+  const ExpRecDev* recs = nullptr;
+  const ObsRecDev* orecs = nullptr;
+  const ObsCoefDev* ocoef = nullptr;
+};
+
+int upload_exp_plan(ExpPlan* p, int device, ExpTables* t) {
+  if (int rc = upload_parts(p->dev, device, {part_of(p->passes), part_of(p->groups), part_of(p->terms), part_of(p->wide_terms)}))
+    return rc;
+  const char* d = static_cast<const char*>(p->dev.p);
+  t->passes = reinterpret_cast<const ExpPassDev*>(d);
+  t->groups = reinterpret_cast<const ExpGroupDev*>(d + part_offset(p->passes));
+  t->terms = reinterpret_cast<const ExpTermDev*>(d + part_offset(p->passes, p->groups));
+  t->wide = reinterpret_cast<const ExpTermDev*>(d + part_offset(p->passes, p->groups, p->terms));
+  return QSV_OK;
+}
+int upload_spans(ExpPlan* p, int device, ExpTables* t) {
+  if (int rc = upload_parts(p->dev_spans, device, {part_of(p->span_passes), part_of(p->spans), part_of(p->recs)})) return rc;
+  const char* d = static_cast<const char*>(p->dev_spans.p);
+  t->passes = reinterpret_cast<const ExpPassDev*>(d);
+  t->spans = reinterpret_cast<const ExpSpanDev*>(d + part_offset(p->span_passes));
+  t->recs = reinterpret_cast<const ExpRecDev*>(d + part_offset(p->span_passes, p->spans));
+  return QSV_OK;
+}
+int upload_obs_recs(ExpPlan* p, int device, ExpTables* t) {
+  if (int rc = upload_parts(p->dev_obs, device, {part_of(p->obs_passes), part_of(p->orecs), part_of(p->ocoef)})) return rc;
+  const char* d = static_cast<const char*>(p->dev_obs.p);
+  t->passes = reinterpret_cast<const ExpPassDev*>(d);
+  t->orecs = reinterpret_cast<const ObsRecDev*>(d + part_offset(p->obs_passes));
+  t->ocoef = reinterpret_cast<const ObsCoefDev*>(d + part_offset(p->obs_passes, p->orecs));
+  return QSV_OK;
+}
+
+// The plan of o for dtype dt (g_plan_mu held).
+ExpPlan* exp_plan_of(qsv_observable* o, qsv_dtype dt) {
+  ExpPlan*& pl = o->exp_plan[dt];
+  if (!pl) pl = build_exp_plan(o, dt);
+  return pl;
+}
+
+constexpr size_t kNoAllocBytes = size_t(1) << 20;
 
 // Launch shape of an expectation: all passes in one launch (merged, full tiles in
 // spans), each split over nz ranges of its spans and groups where the passes' tiles leave the chip idle
@@ -1443,7 +1510,7 @@ ExpShape exp_shape(const ExpPlan* pl, int n) {
   if (h.np == 0) return h;
   int most = 1;
   const bool spans = !pl->spans.empty();
-  for (const ExpPassDev& P : pl->passes)
+  for (const ExpPassDev& P : spans ? pl->span_passes : pl->passes)
     most = std::max(most, spans ? P.span_count + P.grp_count - P.single_count : P.grp_count);
   h.nz = unsigned(std::min<uint64_t>(uint64_t(most), std::max<uint64_t>(1, kExpSplitGrid / (h.grid * h.np))));
   const uint64_t parts = h.grid * h.np * h.nz;
@@ -1455,9 +1522,7 @@ ExpShape exp_shape(const ExpPlan* pl, int n) {
 
 // Enqueues the passes, the wide groups and the sum (into part[h.parts]).
 template <typename R>
-int exp_launch(const ExpPlan* pl, const ExpShape& h, int n, const R* psi, const ExpPassDev* pd, const ExpGroupDev* gd,
-               const ExpTermDev* td, const ExpTermDev* wt, const ExpSpanDev* sd, const ExpRecDev* rd, double* part,
-               hipStream_t st) {
+int exp_launch(const ExpPlan* pl, const ExpShape& h, int n, const R* psi, const ExpTables& t, double* part, hipStream_t st) {
   const size_t lds = (size_t(1) << pl->L) * sizeof(cx<R>);
   // kernel variant: tile of the default size (compile-time trip counts), at
   // least two amplitudes per thread, or any size
@@ -1470,15 +1535,15 @@ int exp_launch(const ExpPlan* pl, const ExpShape& h, int n, const R* psi, const 
   const unsigned launches = h.merged ? 1u : h.np;
   for (unsigned pi = 0; pi < launches; ++pi) {
     ProfScope ps("expect", double(sizeof(cx<R>)) * double(dim(n)) * (h.merged ? h.np : 1u), st);
-    hipLaunchKernelGGL(kfn, dim3(unsigned(h.grid), h.merged ? h.np : 1u, h.nz), dim3(kExpThreadsE), lds, st, psi, pd,
-                       int(pi), gd, td, sd, rd, part, pi > 0 ? 1 : 0, h.tiles);
+    hipLaunchKernelGGL(kfn, dim3(unsigned(h.grid), h.merged ? h.np : 1u, h.nz), dim3(kExpThreadsE), lds, st, psi,
+                       t.passes, int(pi), t.groups, t.terms, t.spans, t.recs, part, pi > 0 ? 1 : 0, h.tiles);
     QSV_HIP_CHECK(hipGetLastError());
   }
   for (size_t wi = 0; wi < pl->wide.size(); ++wi) {
     ProfScope ps("expect_wide", double(sizeof(cx<R>)) * double(dim(n)), st);
     const ExpWide& w = pl->wide[wi];
     hipLaunchKernelGGL((k_expect_wide<R>), dim3(unsigned(h.grid)), dim3(kExpThreadsE), 0, st, psi, w.flip, w.hbit,
-                       wt + w.term_begin, w.term_count, dim(n - 1), part, pl->passes.empty() && wi == 0 ? 0 : 1);
+                       t.wide + w.term_begin, w.term_count, dim(n - 1), part, pl->passes.empty() && wi == 0 ? 0 : 1);
     QSV_HIP_CHECK(hipGetLastError());
   }
   hipLaunchKernelGGL(k_exp_sum, dim3(1), dim3(kExpThreads), 0, st, part, h.parts, part + h.parts);
@@ -1488,24 +1553,24 @@ int exp_launch(const ExpPlan* pl, const ExpShape& h, int n, const R* psi, const 
 
 template <typename R>
 int expect_tiled_t(qsv_state* s, qsv_observable* o, double* out) {
-  ExpPlan*& pl = o->exp_plan[s->dtype];
-  if (!pl) pl = build_exp_plan(o, s->dtype);
-  if (pl->passes.empty() && pl->wide.empty()) {
-    *out = 0.0;
-    return QSV_OK;
+  ExpPlan* pl = nullptr;
+  ExpTables t;
+  ExpShape h{};
+  int rc = QSV_OK;
+  {
+    std::lock_guard<std::mutex> lk(g_plan_mu);
+    pl = exp_plan_of(o, s->dtype);
+    if (pl->passes.empty() && pl->wide.empty()) {
+      *out = 0.0;
+      return QSV_OK;
+    }
+    ensure_spans(pl, sizeof(R) == 4);
+    h = exp_shape(pl, s->n);
+    if ((rc = upload_exp_plan(pl, s->device, &t))) return rc;
+    if (h.merged && !pl->spans.empty() && (rc = upload_spans(pl, s->device, &t))) return rc;
   }
-  ensure_spans(pl, sizeof(R) == 4);
-  int rc = upload_exp_plan(pl, s->device);
-  if (rc) return rc;
-  const ExpShape h = exp_shape(pl, s->n);
   if ((rc = ensure_reduce_scratch(s, size_t(h.parts) + 1))) return rc;
-  char* d = static_cast<char*>(pl->dev);
-  rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), reinterpret_cast<const ExpPassDev*>(d),
-                     reinterpret_cast<const ExpGroupDev*>(d + pl->off_groups),
-                     reinterpret_cast<const ExpTermDev*>(d + pl->off_terms),
-                     reinterpret_cast<const ExpTermDev*>(d + pl->off_wide),
-                     reinterpret_cast<const ExpSpanDev*>(d + pl->off_spans),
-                     reinterpret_cast<const ExpRecDev*>(d + pl->off_recs), s->red, s->stream);
+  rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), t, s->red, s->stream);
   if (rc) return rc;
   QSV_HIP_CHECK(hipMemcpyAsync(s->red_host, s->red + h.parts, sizeof(double), hipMemcpyDeviceToHost, s->stream));
   QSV_HIP_CHECK(hipStreamSynchronize(s->stream));
@@ -1515,9 +1580,19 @@ int expect_tiled_t(qsv_state* s, qsv_observable* o, double* out) {
 
 template <typename R>
 int apply_obs_tiled_t(const qsv_state* in, qsv_observable* o, qsv_state* out) {
-  ExpPlan*& pl = o->exp_plan[in->dtype];
-  if (!pl) pl = build_exp_plan(o, in->dtype);
   const uint64_t N = dim(in->n);
+  ExpPlan* pl = nullptr;
+  ExpTables t;
+  {
+    std::lock_guard<std::mutex> lk(g_plan_mu);
+    pl = exp_plan_of(o, in->dtype);
+    if (!pl->passes.empty() || !pl->wide.empty()) {
+      ensure_obs_recs(pl, sizeof(R) == 4);
+      if (int rc = upload_exp_plan(pl, in->device, &t)) return rc;
+      if (!pl->orecs.empty())
+        if (int rc = upload_obs_recs(pl, in->device, &t)) return rc;
+    }
+  }
   if (pl->passes.empty() && pl->wide.empty()) {  // no terms: lambda = 0
     const uint64_t blocks = std::min<uint64_t>((N + kExpThreads - 1) / kExpThreads, 65536);
     hipLaunchKernelGGL((k_zero_amps<R>), dim3(unsigned(blocks)), dim3(kExpThreads), 0, in->stream,
@@ -1525,9 +1600,6 @@ int apply_obs_tiled_t(const qsv_state* in, qsv_observable* o, qsv_state* out) {
     QSV_HIP_CHECK(hipGetLastError());
     return QSV_OK;
   }
-  ensure_obs_recs(pl, sizeof(R) == 4);
-  int rc = upload_exp_plan(pl, in->device);
-  if (rc) return rc;
   const uint64_t tiles = dim(in->n - pl->L);
   const size_t lds = (size_t(1) << pl->L) * sizeof(cx<R>);
   // compile-time output count when every thread has obs_out<R>() outputs
@@ -1538,26 +1610,20 @@ int apply_obs_tiled_t(const qsv_state* in, qsv_observable* o, qsv_state* out) {
                                                : &k_apply_obs_tile<R, false, NTo, false>;
   QSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     int(lds)));
-  char* d = static_cast<char*>(pl->dev);
   for (size_t pi = 0; pi < pl->passes.size(); ++pi) {
     ProfScope ps("apply_obs", double(sizeof(cx<R>)) * double(N) * (pi > 0 ? 3.0 : 2.0), in->stream);
     hipLaunchKernelGGL(kfn, dim3(unsigned(std::min<uint64_t>(tiles, obs_grid_max()))), dim3(NTo), lds, in->stream,
-                       static_cast<const R*>(in->ptr), static_cast<R*>(out->ptr),
-                       reinterpret_cast<const ExpPassDev*>(d), int(pi),
-                       reinterpret_cast<const ExpGroupDev*>(d + pl->off_groups),
-                       reinterpret_cast<const ExpTermDev*>(d + pl->off_terms),
-                       reinterpret_cast<const ObsRecDev*>(d + pl->off_orecs),
-                       reinterpret_cast<const ObsCoefDev*>(d + pl->off_ocoef), pi > 0 ? 1 : 0, tiles);
+                       static_cast<const R*>(in->ptr), static_cast<R*>(out->ptr), t.passes, int(pi), t.groups, t.terms,
+                       t.orecs, t.ocoef, pi > 0 ? 1 : 0, tiles);
     QSV_HIP_CHECK(hipGetLastError());
   }
-  const auto* wt = reinterpret_cast<const ExpTermDev*>(d + pl->off_wide);
   for (size_t wi = 0; wi < pl->wide.size(); ++wi) {
     const bool acc = !pl->passes.empty() || wi > 0;
     ProfScope ps("apply_obs_wide", double(sizeof(cx<R>)) * double(N) * (acc ? 3.0 : 2.0), in->stream);
     const ExpWide& w = pl->wide[wi];
     const unsigned blocks = unsigned(std::min<uint64_t>((N + kExpThreads - 1) / kExpThreads, 8192));
     hipLaunchKernelGGL((k_apply_obs_wide<R>), dim3(blocks), dim3(kExpThreads), 0, in->stream,
-                       static_cast<const R*>(in->ptr), static_cast<R*>(out->ptr), w.flip, wt + w.term_begin,
+                       static_cast<const R*>(in->ptr), static_cast<R*>(out->ptr), w.flip, t.wide + w.term_begin,
                        w.term_count, N, acc ? 1 : 0);
     QSV_HIP_CHECK(hipGetLastError());
   }
@@ -1601,14 +1667,19 @@ int noalloc_scratch(int device, char** out) {
 
 template <typename R>
 int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
-  ExpPlan*& pl = o->exp_plan[s->dtype];
-  if (!pl) pl = build_exp_plan(o, s->dtype);  // host tables only
-  if (pl->passes.empty() && pl->wide.empty()) {
-    *out = 0.0;
-    return QSV_OK;
+  ExpPlan* pl = nullptr;
+  ExpShape h{};
+  {
+    std::lock_guard<std::mutex> lk(g_plan_mu);
+    pl = exp_plan_of(o, s->dtype);  // host tables only
+    if (pl->passes.empty() && pl->wide.empty()) {
+      *out = 0.0;
+      return QSV_OK;
+    }
+    ensure_spans(pl, sizeof(R) == 4);
+    h = exp_shape(pl, s->n);
   }
-  ensure_spans(pl, sizeof(R) == 4);
-  const ExpShape h = exp_shape(pl, s->n);
+  const bool in_spans = h.merged && !pl->spans.empty();
   // scratch layout: partials[parts + 1] | passes | groups | terms (256-byte aligned)
   const size_t o_pass = al256((size_t(h.parts) + 1) * sizeof(double));
   const size_t o_grp = o_pass + al256(pl->passes.size() * sizeof(ExpPassDev));
@@ -1625,8 +1696,8 @@ int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
   if (rc) return rc;
   hipStream_t st = s->stream;
   if (!pl->passes.empty())
-    QSV_HIP_CHECK(hipMemcpyAsync(d + o_pass, pl->passes.data(), pl->passes.size() * sizeof(ExpPassDev),
-                                 hipMemcpyHostToDevice, st));
+    QSV_HIP_CHECK(hipMemcpyAsync(d + o_pass, (in_spans ? pl->span_passes : pl->passes).data(),
+                                 pl->passes.size() * sizeof(ExpPassDev), hipMemcpyHostToDevice, st));
   if (!pl->groups.empty())
     QSV_HIP_CHECK(hipMemcpyAsync(d + o_grp, pl->groups.data(), pl->groups.size() * sizeof(ExpGroupDev),
                                  hipMemcpyHostToDevice, st));
@@ -1636,7 +1707,7 @@ int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
   if (!pl->wide_terms.empty())
     QSV_HIP_CHECK(hipMemcpyAsync(d + o_wide, pl->wide_terms.data(), pl->wide_terms.size() * sizeof(ExpTermDev),
                                  hipMemcpyHostToDevice, st));
-  if (h.merged && !pl->spans.empty()) {
+  if (in_spans) {
     QSV_HIP_CHECK(hipMemcpyAsync(d + o_span, pl->spans.data(), pl->spans.size() * sizeof(ExpSpanDev),
                                  hipMemcpyHostToDevice, st));
     QSV_HIP_CHECK(hipMemcpyAsync(d + o_rec, pl->recs.data(), pl->recs.size() * sizeof(ExpRecDev),
@@ -1645,10 +1716,14 @@ int expect_noalloc_t(qsv_state* s, qsv_observable* o, double* out) {
   double* part = reinterpret_cast<double*>(d);
   // (the first launch writes every partial that is summed: nothing left from an
   // earlier call is read)
-  rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), reinterpret_cast<const ExpPassDev*>(d + o_pass),
-                     reinterpret_cast<const ExpGroupDev*>(d + o_grp), reinterpret_cast<const ExpTermDev*>(d + o_term),
-                     reinterpret_cast<const ExpTermDev*>(d + o_wide), reinterpret_cast<const ExpSpanDev*>(d + o_span),
-                     reinterpret_cast<const ExpRecDev*>(d + o_rec), part, st);
+  ExpTables t;
+  t.passes = reinterpret_cast<const ExpPassDev*>(d + o_pass);
+  t.groups = reinterpret_cast<const ExpGroupDev*>(d + o_grp);
+  t.terms = reinterpret_cast<const ExpTermDev*>(d + o_term);
+  t.wide = reinterpret_cast<const ExpTermDev*>(d + o_wide);
+  t.spans = reinterpret_cast<const ExpSpanDev*>(d + o_span);
+  t.recs = reinterpret_cast<const ExpRecDev*>(d + o_rec);
+  rc = exp_launch<R>(pl, h, s->n, static_cast<const R*>(s->ptr), t, part, st);
   if (rc) return rc;
   double v = 0.0;
   QSV_HIP_CHECK(hipMemcpyAsync(&v, part + h.parts, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1677,8 +1752,8 @@ int apply_observable_tiled(const qsv_state* in, const qsv_observable* o, qsv_sta
 
 int expectation_passes(const qsv_observable* o, qsv_dtype dt) {
   qsv_observable* mo = const_cast<qsv_observable*>(o);
-  ExpPlan*& pl = mo->exp_plan[dt];
-  if (!pl) pl = build_exp_plan(mo, dt);
+  std::lock_guard<std::mutex> lk(g_plan_mu);
+  const ExpPlan* pl = exp_plan_of(mo, dt);
   return int(pl->passes.size() + pl->wide.size());
 }
 
