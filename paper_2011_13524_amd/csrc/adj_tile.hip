@@ -280,7 +280,6 @@ int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T) {
   T.thread_bits = L - RB;
   const SegCfg cfg{RB, T.thread_bits, sizeof(R) == 4};
   const int b = std::min(L, sizeof(R) == 4 ? 4 : 3);  // 128-byte contiguous runs
-  const double utol = sizeof(R) == 4 ? 1e-9 : 2e-15;
   // reversed, daggered op list with gradient terms
   std::vector<BOp> ops;
   std::vector<int>& row_slot = T.row_slot;
@@ -381,7 +380,7 @@ int adjoint_tables(const qsv_circuit* c, const double* theta, AdjTables& T) {
         op.ctrl_vals.clear();
         op.val.clear();
       }
-    } else if (reg && tq.size() == 1 && cm == 0 && !exch && is_unitary2(m.data(), utol)) {
+    } else if (reg && tq.size() == 1 && cm == 0 && !exch && runs_as_rotation(m.data(), sizeof(R) == 4)) {
       // diagonal, rotation, diagonal
       cd u[6];
       unitary_to_rotation(m.data(), u);

@@ -354,8 +354,7 @@ static void build_lops(qsv_plan* p) {
     p->nvals += nv;
     p->lops.push_back(std::move(l));
   };
-  // rounding-level tolerance: a matrix further from unitary keeps the general product
-  const double tol = p->dtype == QSV_C64 ? 1e-9 : 2e-15;
+  const bool c64 = p->dtype == QSV_C64;
   for (size_t bi = 0; bi < p->blocks.size(); ++bi) {
     const Block& B = p->blocks[bi];
     Lop whole;
@@ -437,12 +436,13 @@ static void build_lops(qsv_plan* p) {
       // one-qubit block: diagonals around a single RX / RY, or any unitary
       std::vector<int> pre, post;
       int rot = -1, axis = 0;
-      bool single = true, unitary = true;
+      bool single = true, unitary = true, fixed = true;
       for (int gi : B.gates) {
         const Gate& g = C.gates[size_t(gi)];
         const GateInfo& I = p->info[size_t(gi)];
         if (I.targets.size() != 1 || !I.controls.empty()) single = unitary = false;
-        if (g.kind == Gate::MATRIX && unitary && !is_unitary2(I.mat.data(), tol)) unitary = false;
+        fixed = fixed && g.slot < 0;
+        if (g.kind == Gate::MATRIX && unitary && !runs_as_rotation(I.mat.data(), c64)) unitary = false;
         if (I.diagonal) {
           (rot < 0 ? pre : post).push_back(gi);
         } else if (rot < 0 && g.kind != Gate::MATRIX) {
@@ -474,6 +474,15 @@ static void build_lops(qsv_plan* p) {
           add(l, 2);
         }
         continue;
+      }
+      if (unitary && fixed && B.gates.size() > 1) {  // (the product itself)
+        std::vector<cd> acc = {{1, 0}, {0, 0}, {0, 0}, {1, 0}}, gm, tmp;
+        for (int gi : B.gates) {
+          extracted_matrix(C.gates[size_t(gi)], p->info[size_t(gi)], nullptr, gm);
+          matmul(gm, acc, 2, tmp);
+          acc.swap(tmp);
+        }
+        unitary = runs_as_rotation(acc.data(), c64);
       }
       if (unitary) {
         const int base = p->nvals;
