@@ -3,7 +3,7 @@
 Usage: python -m paper_2011_13524_amd.build   (or build() from Python)
 
 Every translation unit is compiled by hipcc for gfx950 only, with packed FP32
-instructions disabled and matrix-core results in VGPRs, then linked into paper_2011_13524_amd/libqsv.so.
+instructions disabled, then linked into paper_2011_13524_amd/libqsv.so.
 """
 from __future__ import annotations
 

@@ -514,11 +514,12 @@ __device__ __forceinline__ double span_record(const cx<R>* v, const ExpRecDev& r
 // guards); 1: the tile has at least two amplitudes per thread, so every loop
 // below has a workgroup-uniform trip count; 2: the tile has exp_tile_bits<R>()
 // qubits (trip counts known at compile time).
-// 3: as 2, with the single-term records evaluated in spans. Bound by instruction
-// issue (200 strings of weight 4 at 30 qubits complex64: 45 vector and 34 scalar
-// instructions per record and wavefront, vector units 55% busy, four wavefronts
-// per SIMD): 32.0 ms reading LDS for each record, 27.5 ms in spans; complex128, 250
-// strings, 26 qubits 4.38 and 3.91 ms. The records' factors with the tile's
+// 3: as 2, with the single-term records evaluated in spans: 200 strings of weight 4
+// at 30 qubits complex64 32.0 ms reading LDS for each record, 27.5 ms in spans;
+// complex128, 250 strings, 26 qubits 4.38 and 3.91 ms. What is left is the number of
+// passes: 18 read 154.6 GB in 30.1 ms, 5.1 TB/s where streaming in place reaches
+// 5.64 on this card (45 vector and 34 scalar instructions per record and wavefront
+// keep the vector units 55% busy beside it). The records' factors with the tile's
 // signs come from LDS (formed by one lane each; on the scalar unit 31.3 ms), and
 // records are read where they are used (two at a time 28.2 ms).
 // gridDim.y passes run in one launch, each split over gridDim.z ranges of its

@@ -252,7 +252,7 @@ bool is_unitary2(const cd* u, double tol);
 // Whether u runs as a rotation between diagonals in passes of that dtype (else as a
 // general product). complex64: unitary to 1e-9 (the factors are rounded to 6e-8
 // anyway, as the entries would be). complex128: the factors have to give u back to
-// half a unit in the last place of 1 (the named gates do): entries are used as they
+// half a unit in the last place of 1 (H does): entries are used as they
 // come in a product, while three phases and two shears, each rounded, are off by
 // 2e-16 for a matrix whose rows are orthogonal only to rounding -- the same error on
 // every amplitude. Ten layers of Haar one-qubit gates and CZ on 16 qubits: 8.6e-15

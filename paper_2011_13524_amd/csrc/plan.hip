@@ -26,18 +26,19 @@
 //     qubit, so they commute), and joins the first block sharing a qubit
 //     where the merge rules above allow it. On circuits whose gates all
 //     commute (diagonal layers) this compresses the depth to a constant.
-//  3. Passes: a pass fixes a set of L local qubits (always including the low b
-//     qubits, so that each run of 2^b amplitudes is contiguous in HBM) and
-//     greedily takes, in order, every block whose non-diagonal targets are
-//     local or can still be made local, skipping blocks that share a qubit
-//     with one already deferred. Diagonal blocks and controls may sit on any
-//     qubit: for one tile their non-local bits are constants.
+//  3. Passes: the blocks, broken into rotations, diagonals, exchanges and general
+//     products, are scheduled into passes (segments.hip). A pass fixes a set of L
+//     local qubits (always including the low b qubits, so that each run of 2^b
+//     amplitudes is contiguous in HBM), the one of those tried that lets it take
+//     the most ops in order. Diagonal ops and controls may sit on any qubit: for
+//     one tile their non-local bits are constants.
 //
-// Execution: one kernel launch per pass; workgroup g owns tile g, the 2^L
-// amplitudes whose non-local bits spell g. It streams the tile from HBM into
-// LDS (non-temporal 16-byte vectors), applies the pass's blocks in order with a
-// barrier between them, and streams the tile back. Each pass therefore reads
-// and writes the state once however many gates it applies.
+// Execution: one kernel launch per pass; a tile is the 2^L amplitudes whose
+// non-local bits spell its number. Persistent workgroups hold a tile in registers,
+// re-mapped through LDS between segments (tile_reg.h); tiles that match no
+// register shape (8 qubits and fewer, tile sizes set by hand) go through LDS, a
+// barrier between blocks (k_tile). Each pass reads and writes the state once however
+// many gates it applies.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>

@@ -33,27 +33,26 @@ bool is_unitary2(const cd* u, double tol) {
   return std::fabs(xr) + std::fabs(xi) <= tol * n0;
 }
 
-// Largest difference between u and what unitary_to_rotation's values stand for,
-// relative to u's size.
+// Largest difference between an entry of u and what unitary_to_rotation's values
+// stand for, relative to a column of u.
 static double rotation_error(const cd* u) {
   typedef long double F;
   cd o[6];
   unitary_to_rotation(u, o);
   const F a = o[2].re, b = o[2].im, m[4] = {1 + a * b, a * (2 + a * b), b, 1 + a * b};
-  F worst = 0, big = 0;
+  F worst = 0;
   for (int r = 0; r < 2; ++r)
     for (int c = 0; c < 2; ++c) {
       const cd l = o[4 + r], f = o[c];
       const F pr = F(l.re) * f.re - F(l.im) * f.im, pi = F(l.re) * f.im + F(l.im) * f.re;
       const cd z = u[2 * r + c];
       worst = std::max(worst, std::hypot(pr * m[2 * r + c] - z.re, pi * m[2 * r + c] - z.im));
-      big = std::max(big, std::hypot(F(z.re), F(z.im)));
     }
-  return double(worst / big);
+  return double(worst / std::hypot(std::hypot(F(u[0].re), F(u[0].im)), std::hypot(F(u[2].re), F(u[2].im))));
 }
 
 bool runs_as_rotation(const cd* u, bool c64) {
-  return c64 ? is_unitary2(u, 1e-9) : is_unitary2(u, 2e-15) && rotation_error(u) <= 1.2e-16;
+  return c64 ? is_unitary2(u, 1e-9) : is_unitary2(u, 2e-15) && rotation_error(u) <= 1.15e-16;
 }
 
 void unitary_to_rotation(const cd* u, cd* out) {

@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from oracle import oracle as O
-from paper_2011_13524_amd import Circuit, Plan, State, apply_fused
+from paper_2011_13524_amd import Batch, Circuit, Observable, Plan, State, adjoint_gradient, apply_fused
 from paper_2011_13524_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -27,3 +27,26 @@ def test_haar_layers(n):
         apply_fused(s, Plan(Circuit.from_records(n, gates), "c128"))
         ref = O.run_circuit(n, gates)
         assert np.linalg.norm(s.store() - ref) <= 2.8e-15 + 1.4e-15  # (the oracle's own rounding)
+
+
+@pytest.mark.parametrize("dt,tol", [("c128", 1e-11), ("c64", 2e-5)])
+@pytest.mark.parametrize("n", [9, 12, 13])
+def test_haar_gates_in_gradients_and_batches(dt, tol, n):
+    rng = np.random.default_rng(n)
+    gates = []
+    for layer in range(2):
+        gates += [{"op": "dense", "q": [q], "mat": W.haar_unitary(rng, 2)} for q in range(n)]
+        gates += [{"op": ("ry", "rx", "rz")[q % 3], "q": [q], "slot": layer * n + q} for q in range(n)]
+        gates += [{"op": "cnot" if q % 2 else "cz", "q": [q, q + 1]} for q in range(n - 1)]
+    theta = rng.uniform(-6.0, 6.0, 2 * n)
+    obs = W.random_pauli_observable(n, 10, (1, 4), seed_key=(n, 5)) + [(0.4, [])]
+    scale = sum(abs(a) for a, _ in obs)
+    c, o, b = Circuit.from_records(n, gates), Observable(n, obs), Batch()
+    b.add(c, o, theta)
+    be, bg = b.run(dt)
+    psi, lam = State(n, dt), State(n, dt)
+    slots = [0, n // 2, n, 2 * n - 1]
+    ref = O.param_shift_grad(n, gates, theta, obs, slots=slots)
+    for e, g in [adjoint_gradient(c, theta, o, psi, lam, Plan(c, dt)), (be[0], bg[0])]:
+        assert abs(e - O.energy(n, gates, theta, obs)) <= tol * scale
+        assert np.max(np.abs(g[slots] - ref)) <= tol * scale

@@ -39,8 +39,9 @@ def test_rotations_give_their_matrix_back():
     split.restype = None
     split.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
     rng = np.random.default_rng(5)
-    h = np.array([[1, 1], [1, -1]]) / np.sqrt(2.0)
+    h = np.array([[1, 1], [1, -1]]) * np.sqrt(0.5)  # (the named gate's entries)
     y = np.array([[0, -1j], [1j, 0]])
+    assert runs(np.ascontiguousarray(h, dtype=np.complex128).ctypes.data, False)
     taken = 0
     for u in [h, y] + [W.haar_unitary(rng, 2) for _ in range(200)]:
         u = np.ascontiguousarray(u, dtype=np.complex128)
