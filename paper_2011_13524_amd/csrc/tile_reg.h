@@ -982,7 +982,7 @@ __device__ __forceinline__ uint32_t touch(const void* p, uint32_t bytes, uint32_
 // holds four workgroups on a compute unit, four wavefronts per SIMD, so a
 // wavefront has 128 registers: 32 amplitude words, 32 of the next tile. Bound
 // by vector issue: at 30 qubits complex64 (15 passes of the layered circuit,
-// 1858 vector instructions per wavefront and tile) a pass takes 5.06 ms, 68%
+// 1897 vector instructions per wavefront and tile) a pass takes 4.91 ms, 66%
 // of it vector issue; its read and write of the state alone take 3.9 ms. With
 // matrix products in two register arrays (3320 to 4740 instructions) it took
 // 5.6 to 6.3 ms, over fresh workgroups per tile.
